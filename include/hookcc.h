@@ -64,7 +64,10 @@ extern "C" {
                             entries the Atomic-Hook with the giant filter when
                             m / n >= 8 and the hybrid plan below otherwise; the
                             atomic-free Hook for smaller lists (the hybrid plan for a
-                            no-sync call); the Atomic-Hook with the symmetric flag    */
+                            no-sync call); the Atomic-Hook with the symmetric flag.
+                            The smallest lists (n <= 32,768, 2 n + m <= 131,072, no
+                            max_rounds) are solved by one workgroup in LDS, in one
+                            launch, and counted as one round of the atomic-free Hook  */
 #define CC_HOOK_ATOMIC 1 /* Atomic-Hook (Fig. 3, CAS on roots) + segmentation (Fig. 4) */
 #define CC_HOOK_PLAIN 2  /* atomic-free Hook (Fig. 2) rounds until no change (Fig. 1),
                             convergence test and active-edge frontier on the device   */

@@ -86,7 +86,23 @@ struct Plan {
     bool graph = false;      // capture the launch sequence in a hipGraph and replay it
     bool no_sync = false;    // enqueue only; status read later by cc_stream_status
     uint32_t tau = 0xffffffffu;  // atomic-free Hook: frontier rewrite threshold (1/1000)
+    bool lds_single = false;     // one workgroup solves the whole graph in LDS
 };
+
+// Small lists that the automatic choice gives to one LDS workgroup.  The
+// launch costs ~4 us plus ~0.5 us per 1,000 vertices (init, Multi-Jump,
+// labels: up to 32,768 vertices, where the slots are 32 bits wide) and
+// ~0.22 us per 1,000 entries, against ~70 us for the atomic-free rounds' 14
+// commands whatever the size (C call, median: n = 1,000, m = 4,000 17 against
+// 68 us; n = 8,192, m = 65,536 34 against 80; n = 32,768, m = 65,536 50
+// against 85; n = 65,536, m = 131,072 111 against 76).
+bool fits_lds_single(int64_t n, int64_t m) {
+    return n > 0 && n <= 32768 && 2 * n + m <= 131072;
+}
+// Its segments: a second one (a Multi-Jump half-way) pays from ~2^15 entries
+// on when the graph is dense (n = 1,000, m = 65,536: 30.0 against 33.5 us;
+// m = 16,000: 20.5 against 20.1).
+int32_t lds_single_segments(int64_t n, int64_t m) { return m > 32768 && m >= 4 * n ? 2 : 1; }
 
 // Hook variants an input form supports: pair lists all of them; CSR input the
 // Atomic-Hook and the hybrid plan (its atomic-free pass needs no frontier);
@@ -162,6 +178,9 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
         } else {
             p.hook = CC_HOOK_PLAIN;
         }
+        // an explicit round cap is a question about the rounds: they run
+        p.lds_single = allow_plain && op.symmetric == 0 && op.max_rounds == 0 &&
+                       fits_lds_single(n, m);
     } else {
         p.hook = op.hook;
     }
@@ -248,6 +267,10 @@ struct Layout {
 Layout layout(int32_t n, int64_t m, const Plan& p) {
     Layout L;
     size_t off = 256;
+    if (p.lds_single) {  // the status word only
+        L.total = off;
+        return L;
+    }
     if (p.hook == CC_HOOK_ATOMIC && p.filter == CC_FILTER_GIANT) {
         L.bits = off;
         off += align256(((size_t)n + 31) / 32 * 4);
@@ -797,6 +820,28 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
     tm.s = s;
     int64_t rounds = 0;
     const bool use_graph = p.graph && s != nullptr && !p.profile && pe != nullptr;
+    if (p.lds_single) {
+        // one launch, which reports the status straight to pinned host memory
+        // where the call waits for it
+        HIPCHK(prepare_batch_lds());
+        const GraphDesc d = {u, v, out, m, n, lds_single_segments(n, m)};
+        Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
+        const bool direct = pe && !p.no_sync;
+        TIMED(kPhaseHook, launch_single_lds(d, direct ? &hctrl->status : &ctrl->status, p.halve, s));
+        if (st) st->hook_launches = 1;
+        if (p.no_sync && pe) return post_async(pe, s, ctrl);
+        if (!direct)
+            HIPCHK(hipMemcpyAsync(&hctrl->status, &ctrl->status, 4, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        tm.collect(st);
+        if (st) {
+            st->host_syncs = 1;
+            st->rounds = 1;
+        }
+        const int32_t status = *(volatile int32_t*)&hctrl->status;
+        if (status & kStatusRange) return fail(CC_ERR_RANGE, "edge endpoint outside [0, n)");
+        return CC_OK;
+    }
     if (p.hook == CC_HOOK_ATOMIC || p.hook == CC_HOOK_HYBRID) {
         // fixed launch sequences: no host read until the end
         auto enqueue = [&](cc_stats* sx) {

@@ -165,6 +165,11 @@ hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n
                             int32_t* queue_head, int32_t* status, bool halve, int grid,
                             hipStream_t s, int block = 1024);
 
+// One graph of at most 65,536 vertices solved by one workgroup in LDS
+// (prepare_batch_lds first); *status (device or pinned host) = 0 or
+// kStatusRange.
+hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hipStream_t s);
+
 // Descriptors of a batch with device offsets, largest first (two launches,
 // one thread per graph, with a scan launch between them above 32,768
 // graphs); `rows` is scratch of (ceil(B / 1024) + 1) x 256 int32.

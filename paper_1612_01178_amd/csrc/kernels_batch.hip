@@ -249,6 +249,22 @@ __global__ __launch_bounds__(1024) void k_batch_lds(const GraphDesc* __restrict_
     if (bad) __hip_atomic_store(status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// One small graph, given by value, by one workgroup: the whole solve is this
+// launch.  *status receives 0 or kStatusRange (device or pinned host memory).
+template <bool HALVE>
+__global__ __launch_bounds__(1024) void k_single_lds(GraphDesc d, int32_t* status) {
+    extern __shared__ uint16_t spi[];
+    bool bad = false;
+    if ((uint32_t)d.n <= kWideMaxN)
+        solve_graph(reinterpret_cast<uint32_t*>(spi), d, HALVE, bad);
+    else
+        solve_graph(spi, d, HALVE, bad);
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(status, any ? kStatusRange : 0, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------------------
 // Preparation of a batch whose offsets are in device memory, in two launches
 // of one thread per graph: every graph is checked and given its size class
@@ -610,13 +626,33 @@ hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int
 hipError_t prepare_batch_lds() {
     // Allows up to 128 KiB of dynamic LDS; set once, outside any capture.
     static hipError_t once = [] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_lds<true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 65536 * 2);
-        if (e != hipSuccess) return e;
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_lds<false>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, 65536 * 2);
+        const void* fn[] = {reinterpret_cast<const void*>(&k_batch_lds<true>),
+                            reinterpret_cast<const void*>(&k_batch_lds<false>),
+                            reinterpret_cast<const void*>(&k_single_lds<true>),
+                            reinterpret_cast<const void*>(&k_single_lds<false>)};
+        for (const void* f : fn) {
+            const hipError_t e =
+                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 65536 * 2);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }();
     return once;
+}
+
+// LDS bytes of the tree array of a graph of at most n vertices: 32-bit slots
+// up to kWideMaxN vertices, 16-bit above.
+static size_t lds_tree_bytes(int32_t n) {
+    return (uint32_t)n <= kWideMaxN ? (size_t)n * 4 : (size_t)kWideMaxN * 4;
+}
+
+hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hipStream_t s) {
+    if (d.n < 1 || d.n > 65536) return hipErrorInvalidValue;
+    if (halve)
+        k_single_lds<true><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, status);
+    else
+        k_single_lds<false><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, status);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n,
@@ -625,8 +661,7 @@ hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n
     if (count <= 0) return hipSuccess;
     if (max_n < 1 || max_n > 65536) return hipErrorInvalidValue;
     if (block < 64 || block > 1024 || block % 64) return hipErrorInvalidValue;
-    // 32-bit slots for graphs of at most kWideMaxN vertices, 16-bit above
-    const size_t lds = (uint32_t)max_n <= kWideMaxN ? (size_t)max_n * 4 : (size_t)kWideMaxN * 4;
+    const size_t lds = lds_tree_bytes(max_n);
     // persistent: as many workgroups as fit on the CUs at once (LDS, with a
     // margin for the kernel's own static LDS, and thread limits), at most 32
     // waves per CU
