@@ -296,11 +296,12 @@ int32_t cc_labels_batch(int32_t num_graphs, const int64_t* vtx_off, const int64_
  * LDS-solved graphs `opts` sets `path_halving` (CC_HALVE_AUTO / ON: the LDS
  * climb re-points passed non-roots at their grandparents; OFF: Fig. 3
  * exactly) and `segments`, a cap S on each graph's round(m_g / n_g) segments:
- * 0 = default, 2 with halving and no cap without it (in LDS a climb is
- * cheap, so fewer segments -- fewer Multi-Jump passes and barriers -- are
- * faster; the autotuner picks S) and `block`, the workgroup size of the LDS
- * solver (64..1024, multiple of 64; 0 = 1024; as many workgroups share a CU
- * as the LDS of the largest graph allows).  The LDS solver has no frontier
+ * 0 = default, with halving one (two for large dense graphs) and no cap
+ * without it (in LDS a climb is cheap, so fewer segments -- fewer Multi-Jump
+ * passes and barriers -- are faster; the autotuner picks S) and `block`, the
+ * workgroup size of the LDS solver (64..1024, multiple of 64; 0 = by the
+ * number and sizes of the graphs; as many workgroups share a CU as the LDS of
+ * the largest graph allows).  The LDS solver has no frontier
  * compaction and so no compaction threshold: each graph's entries are read
  * once per segment and hooked in LDS, with nothing left to compact.  `graph`
  * = 1 captures the launch sequence.  Larger graphs use the default
@@ -316,6 +317,9 @@ int32_t cc_labels_batch_ex(int32_t num_graphs, const int64_t* vtx_off, const int
  * their descriptors; then the persistent LDS launch solves them.  A call is
  * three launches (four above 32,768 graphs, where a scan launch keeps the
  * ordering linear in the graph count) and one synchronisation on `stream`.
+ * When the order does not matter (every graph gets a workgroup at once, or
+ * max_n <= 256) the solving launch reads and checks the offsets itself and
+ * is the only one.
  *   vtx_off, edge_off  [device] int64[B+1], as for cc_labels_batch
  *   edges_u/v          [device] int32[edge_off[B]], local ids (NULL only if no graph
  *                      has entries)
@@ -329,7 +333,7 @@ int32_t cc_labels_batch_ex(int32_t num_graphs, const int64_t* vtx_off, const int
  * label is written for the offending graphs and the call returns
  * CC_ERR_ARG after the synchronisation.  `opts` (nullable) takes
  * `segments`, `path_halving`, `block` and `graph` as for cc_labels_batch_ex;
- * the device memory it needs (256 B, plus 40 B per graph, plus 1 KiB per
+ * the device memory it needs (1 KiB, plus 40 B per graph, plus 1 KiB per
  * 1,024 graphs and 1 KiB) comes from the stream's pool.  Returns CC_OK, CC_ERR_ARG, CC_ERR_RANGE, CC_ERR_NOMEM or CC_ERR_HIP. */
 int32_t cc_labels_batch_device(int32_t num_graphs, const int64_t* vtx_off,
                                const int64_t* edge_off, const int32_t* edges_u,

@@ -18,7 +18,7 @@ struct Ctrl {
     int32_t rounds;       // atomic-free Hook: rounds that found an active edge
     uint32_t count[2];    // atomic-free Hook: frontier sizes, ping-pong by round parity
     uint32_t nofilter;    // giant sample: 1 when no component is large enough to filter
-    int32_t queue_head;   // batched solve: next position of the graph work queue
+    int32_t unused;
     int64_t active_round1;  // atomic-free Hook: frontier size after round 1
     int32_t hook_changed;   // host-loop form of Fig. 1: a Hook pass found an active edge
     int32_t jump_changed;   // host-loop form of Fig. 1: a Jump pass moved a pointer

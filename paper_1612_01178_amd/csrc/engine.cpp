@@ -99,10 +99,6 @@ struct Plan {
 bool fits_lds_single(int64_t n, int64_t m) {
     return n > 0 && n <= 32768 && 2 * n + m <= 131072;
 }
-// Its segments: a second one (a Multi-Jump half-way) pays from ~2^15 entries
-// on when the graph is dense (n = 1,000, m = 65,536: 30.0 against 33.5 us;
-// m = 16,000: 20.5 against 20.1).
-int32_t lds_single_segments(int64_t n, int64_t m) { return m > 32768 && m >= 4 * n ? 2 : 1; }
 
 // Hook variants an input form supports: pair lists all of them; CSR input the
 // Atomic-Hook and the hybrid plan (its atomic-free pass needs no frontier);
@@ -824,7 +820,7 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
         // one launch, which reports the status straight to pinned host memory
         // where the call waits for it
         HIPCHK(prepare_batch_lds());
-        const GraphDesc d = {u, v, out, m, n, lds_single_segments(n, m)};
+        const GraphDesc d = {u, v, out, m, n, lds_auto_segments(m, n)};
         Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
         const bool direct = pe && !p.no_sync;
         TIMED(kPhaseHook, launch_single_lds(d, direct ? &hctrl->status : &ctrl->status, p.halve, s));
@@ -1226,8 +1222,10 @@ size_t workspace_bytes_impl(int32_t n, int64_t m, const cc_options* opts) {
 
 // ---------------------------------------------------------------------- graph lists
 // Segments of an LDS-solved graph: min(cap, round(m / n)) (at least 1), or
-// round(m / n) for cap 0; small caps by comparison, without a division.
+// round(m / n) for cap 0, the default rule for kSegAuto; small caps by
+// comparison, without a division.
 int32_t lds_segments(int64_t m, int64_t n, int32_t cap) {
+    if (cap == kSegAuto) return lds_auto_segments(m, n);
     if (cap > 0 && cap <= 16 && m < (int64_t(1) << 61)) {
         int32_t k = cap;  // round(m / n) >= k  <=>  2m >= (2k - 1) n
         while (k > 1 && 2 * m < (2 * (int64_t)k - 1) * n) --k;
@@ -1253,20 +1251,19 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
     if (opts && opts->no_sync)
         return fail(CC_ERR_ARG, "cc_options.no_sync is for cc_labels_ex and cc_labels_csr only");
     // Per-graph segment count of the LDS solver: min(S, round(m/n)) for a
-    // cap S > 0.  Default (S = 0): 2 with path halving in the LDS climb (the
-    // default; measured best, batch of 10,000 ER graphs 1.54 ms against 1.78
-    // for the paper's schedule without halving), the paper's round(m/n)
-    // (no cap) with halving off.
+    // cap S > 0.  Default (S = 0): one or two by lds_auto_segments with path
+    // halving in the LDS climb (the default), the paper's round(m/n) (no cap)
+    // with halving off.
     const int32_t ph = opts ? opts->path_halving : CC_HALVE_AUTO;
     if (ph < CC_HALVE_AUTO || ph > CC_HALVE_OFF) return fail(CC_ERR_ARG, "unknown cc_options.path_halving");
     const bool lds_halve = ph != CC_HALVE_OFF;
     int32_t seg_cap = opts ? opts->segments : 0;
     if (seg_cap < 0) return fail(CC_ERR_ARG, "cc_options.segments < 0");
-    // workgroup size of the LDS solver (0 = 1024)
-    const int32_t lds_block = (opts && opts->block) ? opts->block : 1024;
-    if (lds_block < 64 || lds_block > 1024 || lds_block % 64)
+    // workgroup size of the LDS solver (0 = by the graphs' sizes)
+    int32_t lds_block = opts ? opts->block : 0;
+    if (lds_block != 0 && (lds_block < 64 || lds_block > 1024 || lds_block % 64))
         return fail(CC_ERR_ARG, "cc_options.block must be a multiple of 64 in [64, 1024]");
-    if (seg_cap == 0 && lds_halve) seg_cap = 2;
+    if (seg_cap == 0 && lds_halve) seg_cap = kSegAuto;
     if (st) {
         std::memset(st, 0, sizeof *st);
         st->giant_label = -1;
@@ -1314,14 +1311,15 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
         small.swap(sorted);
     }
     const int32_t ns = (int32_t)small.size();
+    if (lds_block == 0) lds_block = batch_block(ns, (int32_t)maxn_small);
     const int32_t nl = (int32_t)large.size();
     std::vector<Plan> plans(nl);
     std::vector<size_t> region_off(nl, 0);
     std::vector<Layout> layouts(nl);
-    // Workspace: the LDS launch's control block, its descriptors right after
-    // (one copy from the staging buffer uploads both and clears the block),
+    // Workspace: the LDS launch's queue counters, its descriptors right after
+    // (one copy from the staging buffer uploads both and clears the counters),
     // then the large graphs' control blocks and their regions.
-    const size_t desc_off = sizeof(Ctrl);
+    const size_t desc_off = kQueueBytes;
     const size_t desc_bytes = align256((size_t)ns * sizeof(GraphDesc));
     const size_t lctrl_off = desc_off + desc_bytes;
     size_t off = lctrl_off + align256((size_t)nl * sizeof(Ctrl));
@@ -1357,13 +1355,13 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
         if (rc != CC_OK) return rc;
     }
     char* ws = workspace ? static_cast<char*>(workspace) : static_cast<char*>(pe->dev);
-    Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);                 // the LDS launch's
+    uint32_t* heads = reinterpret_cast<uint32_t*>(ws);        // the LDS launch's queues
     Ctrl* lctrls = reinterpret_cast<Ctrl*>(ws + lctrl_off);   // the large graphs'
     // The LDS launch reports a bad endpoint in a pinned host word, so a call
     // without large graphs needs no copy back before its synchronisation.
     *pe->batch_status = 0;
     if (ns > 0) {
-        std::memset(pe->host_stage, 0, desc_off);  // the cleared control block
+        std::memset(pe->host_stage, 0, desc_off);  // the cleared queue counters
         GraphDesc* hd = reinterpret_cast<GraphDesc*>(static_cast<char*>(pe->host_stage) + desc_off);
         for (int32_t i = 0; i < ns; ++i) {
             const cc_graph G = graph_at(small[i]);
@@ -1377,14 +1375,14 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
             d.segments = lds_segments(G.m, G.n, seg_cap);
         }
     }
-    // The launch sequence: clear the LDS solver's control block, upload the
+    // The launch sequence: clear the LDS solver's queue counters, upload the
     // descriptors, one persistent LDS launch, then every large graph's solve.
     Timer tm;
     auto enqueue = [&]() -> int32_t {
         if (ns > 0) {
             HIPCHK(hipMemcpyAsync(ws, pe->host_stage, desc_off + desc_bytes, hipMemcpyHostToDevice, s));
             HIPCHK(launch_batch_lds(reinterpret_cast<GraphDesc*>(ws + desc_off), ns,
-                                    (int32_t)maxn_small, &ctrl->queue_head, pe->batch_status,
+                                    (int32_t)maxn_small, heads, pe->batch_status,
                                     lds_halve, device_cu_count(), s, lds_block));
         }
         for (int32_t i = 0; i < nl; ++i) {
@@ -1490,6 +1488,12 @@ int32_t batch_impl(int32_t B, const int64_t* vo, const int64_t* eo, const int32_
 // The LDS batch with offsets in device memory (vo, eo), or in host memory
 // (hvo, heo non-null: copied through the pinned staging buffer into the
 // workspace first, one copy per call).
+// Host offsets of up to this many graphs are read by the solving launch from
+// the pinned staging buffer, larger batches copy them first (one launch for
+// graphs of up to 256 vertices, against a copy and the launch: 2,000 graphs
+// 32.4 against 35.4 us, 8,000 graphs 55.5 against 50.8 us).
+constexpr int32_t kZeroCopyGraphs = 4096;
+
 int32_t batch_lds_impl(int32_t B, const int64_t* vo, const int64_t* eo, const int64_t* hvo,
                        const int64_t* heo, const int32_t* u, const int32_t* v, int32_t* out,
                        int32_t max_n, const cc_options* opts, hipStream_t s, cc_stats* st) {
@@ -1501,9 +1505,9 @@ int32_t batch_lds_impl(int32_t B, const int64_t* vo, const int64_t* eo, const in
     const bool lds_halve = ph != CC_HALVE_OFF;
     int32_t seg_cap = opts ? opts->segments : 0;
     if (seg_cap < 0) return fail(CC_ERR_ARG, "cc_options.segments < 0");
-    if (seg_cap == 0 && lds_halve) seg_cap = 2;
-    const int32_t lds_block = (opts && opts->block) ? opts->block : 1024;
-    if (lds_block < 64 || lds_block > 1024 || lds_block % 64)
+    if (seg_cap == 0 && lds_halve) seg_cap = kSegAuto;
+    int32_t lds_block = opts ? opts->block : 0;
+    if (lds_block != 0 && (lds_block < 64 || lds_block > 1024 || lds_block % 64))
         return fail(CC_ERR_ARG, "cc_options.block must be a multiple of 64 in [64, 1024]");
     if (max_n < 1 || max_n > CC_BATCH_LDS_MAX_N)
         return fail(CC_ERR_ARG, "max_n must be in [1, CC_BATCH_LDS_MAX_N]");
@@ -1516,12 +1520,15 @@ int32_t batch_lds_impl(int32_t B, const int64_t* vo, const int64_t* eo, const in
     // vertices; the preparation launch checks that on the device
     const bool staged = hvo && heo;
     if (!staged && (!vo || !eo)) return fail(CC_ERR_ARG, "null offsets");
-    if ((size_t)B > (SIZE_MAX - sizeof(Ctrl)) / sizeof(GraphDesc)) return fail(CC_ERR_ARG, "too many graphs");
-    const size_t desc_off = sizeof(Ctrl);
+    if (lds_block == 0) lds_block = batch_block(B, max_n);
+    const bool direct = batch_direct(B, max_n, lds_block, device_cu_count());
+    const bool zero_copy = direct && staged && B <= kZeroCopyGraphs;
+    if ((size_t)B > (SIZE_MAX - kQueueBytes) / sizeof(GraphDesc)) return fail(CC_ERR_ARG, "too many graphs");
+    const size_t desc_off = kQueueBytes;
     const size_t rows_off = desc_off + align256((size_t)B * sizeof(GraphDesc));
     const size_t off_bytes = align256(((size_t)B + 1) * 8);  // one offset array
     const size_t offs_off = rows_off + align256((((size_t)B + 1023) / 1024 + 1) * 256 * 4);
-    const size_t total = offs_off + (staged ? 2 * off_bytes : 0);
+    const size_t total = offs_off + (staged && !zero_copy ? 2 * off_bytes : 0);
     HIPCHK(prepare_batch_lds());
     PoolEntry* pe = pool_entry(s);
     std::lock_guard<std::mutex> lk(pe->mu);
@@ -1538,19 +1545,26 @@ int32_t batch_lds_impl(int32_t B, const int64_t* vo, const int64_t* eo, const in
     pe->batch_status[0] = pe->batch_status[1] = pe->batch_status[2] = 0;
     char* ws = static_cast<char*>(pe->dev);
     if (staged) {
-        vo = reinterpret_cast<const int64_t*>(ws + offs_off);
-        eo = reinterpret_cast<const int64_t*>(ws + offs_off + off_bytes);
+        const char* at = zero_copy ? static_cast<const char*>(pe->host_stage) : ws + offs_off;
+        vo = reinterpret_cast<const int64_t*>(at);
+        eo = reinterpret_cast<const int64_t*>(at + off_bytes);
     }
-    Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
+    uint32_t* heads = reinterpret_cast<uint32_t*>(ws);
     GraphDesc* descs = reinterpret_cast<GraphDesc*>(ws + desc_off);
     int32_t* rows = reinterpret_cast<int32_t*>(ws + rows_off);
     auto enqueue = [&]() -> int32_t {
-        if (staged)
+        if (staged && !zero_copy)
             HIPCHK(hipMemcpyAsync(ws + offs_off, pe->host_stage, 2 * off_bytes,
                                   hipMemcpyHostToDevice, s));
-        HIPCHK(launch_batch_prep(vo, eo, B, u, v, out, max_n, seg_cap, descs, rows, ctrl,
+        if (direct) {
+            const BatchSrc src = {vo, eo, u, v, out, max_n, seg_cap};
+            HIPCHK(launch_batch_direct(src, B, pe->batch_status, lds_halve, device_cu_count(), s,
+                                       lds_block));
+            return CC_OK;
+        }
+        HIPCHK(launch_batch_prep(vo, eo, B, u, v, out, max_n, seg_cap, descs, rows, heads,
                                  pe->batch_status, s));
-        HIPCHK(launch_batch_lds(descs, B, max_n, &ctrl->queue_head, pe->batch_status, lds_halve,
+        HIPCHK(launch_batch_lds(descs, B, max_n, heads, pe->batch_status, lds_halve,
                                 device_cu_count(), s, lds_block));
         return CC_OK;
     };

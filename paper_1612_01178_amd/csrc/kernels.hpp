@@ -158,12 +158,50 @@ hipError_t launch_probe_bitgather(const int32_t* u, const int32_t* v, int64_t m,
                                   hipStream_t s);
 
 // Batched solve: one workgroup per graph, tree array in LDS, graphs taken
-// from a device work queue in the order of `descs`; `grid` = CU count, and
+// from device work queues in the order of `descs`; `cus` = CU count, and
 // each CU runs as many `block`-thread workgroups as the LDS allows.
+// `heads` points at the queues' counters, kQueueBytes of zeroed device memory.
+constexpr int kQueues = 8;
+constexpr int kQueueStride = 32;  // words between two counters (a cache line each)
+constexpr size_t kQueueBytes = sizeof(uint32_t) * kQueues * kQueueStride;
 hipError_t prepare_batch_lds();  // once per process, before the first launch
-hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n,
-                            int32_t* queue_head, int32_t* status, bool halve, int grid,
-                            hipStream_t s, int block = 1024);
+hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n, uint32_t* heads,
+                            int32_t* status, bool halve, int cus, hipStream_t s, int block);
+
+// A batch by its offsets (vo, eo: int64[count + 1], device or pinned host
+// memory) and packed arrays.
+struct BatchSrc {
+    const int64_t* vo;
+    const int64_t* eo;
+    const int32_t* u;
+    const int32_t* v;
+    int32_t* out;
+    int32_t max_n;
+    int32_t seg_cap;
+};
+// Batched solve straight from the offsets, in the given order, without a
+// preparation launch; status[0 .. 2] as for launch_batch_lds and
+// launch_batch_prep.
+hipError_t launch_batch_direct(const BatchSrc& src, int32_t count, int32_t* status, bool halve,
+                               int cus, hipStream_t s, int block);
+
+// Whether a batch is solved without preparation launches.
+bool batch_direct(int32_t count, int32_t max_n, int block, int cus);
+// Workgroup size of the LDS solver for a launch of `count` graphs of at most
+// max_n vertices.
+int batch_block(int32_t count, int32_t max_n);
+// Segment cap that stands for the default: lds_auto_segments per graph.
+constexpr int32_t kSegAuto = -1;
+// Segments of one LDS-solved graph.  A second one (a Multi-Jump half-way)
+// costs two barriers and a pass over the vertices and shortens the climbs of
+// the second half: it pays for large dense graphs only (alone, n = 1,000,
+// m = 65,536 30.0 against 33.5 us; n = 8,192, m = 131,072 46.0 against 54.0;
+// n = 8,192, m = 32,768 28.5 against 28.1).  Of 10,000 graphs of average
+// degree up to 16 none gets a second one (868 us; two where m / n >= 4 886,
+// two where m / n >= 1.5 925 us).
+__host__ __device__ inline int32_t lds_auto_segments(int64_t m, int64_t n) {
+    return m > 32768 && m / 8 > n ? 2 : 1;
+}
 
 // One graph of at most 65,536 vertices solved by one workgroup in LDS
 // (prepare_batch_lds first); *status (device or pinned host) = 0 or
@@ -173,11 +211,11 @@ hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hi
 // Descriptors of a batch with device offsets, largest first (two launches,
 // one thread per graph, with a scan launch between them above 32,768
 // graphs); `rows` is scratch of (ceil(B / 1024) + 1) x 256 int32.
-// Clears ctrl->queue_head; status[1] / status[2] get kStatusBadGraph /
+// Clears the queue counters; status[1] / status[2] get kStatusBadGraph /
 // kStatusRange for invalid graphs (status may be pinned host memory).
 hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, const int32_t* u,
                              const int32_t* v, int32_t* out, int32_t max_n, int32_t seg_cap,
-                             GraphDesc* descs, int32_t* rows, Ctrl* ctrl, int32_t* status,
+                             GraphDesc* descs, int32_t* rows, uint32_t* heads, int32_t* status,
                              hipStream_t s);
 
 // Zeroes `words` 32-bit words with a kernel (graph-capture friendly).

@@ -1,8 +1,8 @@
 // Batched solve of many small graphs in one persistent launch (CDNA4).
 //
 // Persistent workgroups (1024 threads, 16 waves, by default; as many per CU as
-// the LDS of the launch's largest graph allows) take graphs from a device
-// work queue (an atomic counter over descriptors ordered largest first, by
+// the LDS of the launch's largest graph allows) take graphs from device
+// work queues (atomic counters over descriptors ordered largest first, by
 // the host or, for offsets in device memory, by the preparation launches
 // below) and solve each one entirely in LDS: the graph's tree array pi lives in LDS as
 // local ids, 32-bit for n <= 32768 and 16-bit up to 65536 (at most 128 KiB of
@@ -217,30 +217,38 @@ __device__ __forceinline__ void solve_graph(T* spi, const GraphDesc& d, bool hal
     }
 }
 
+// Workgroup b takes graph b first and then draws from work queue b mod
+// kQueues, which holds every kQueues-th of the graphs past the first
+// gridDim.x, in order.  A single counter served one draw in ~13 ns and every
+// workgroup drew its first graph from it, so 2,000 graphs of at most 64
+// vertices took 60 us at 512 workgroups and 146 us at 8,192 (20,000 graphs:
+// 270 us), whatever their size.
 template <bool HALVE>
 __global__ __launch_bounds__(1024) void k_batch_lds(const GraphDesc* __restrict__ descs,
-                                                    int32_t count, int32_t* queue_head,
+                                                    int32_t count, uint32_t* heads,
                                                     int32_t* status) {
     constexpr bool halve = HALVE;  // a compile-time constant: no branch in the hook loop
     extern __shared__ uint16_t spi[];
-    __shared__ int32_t next;
+    __shared__ uint32_t next;
     bool bad = false;
-    if (threadIdx.x == 0) next = atomicAdd(queue_head, 1);
-    __syncthreads();
-    int32_t idx = next;
-    while (idx < count) {
+    const uint32_t q = blockIdx.x % kQueues;
+    const uint32_t k0 = (gridDim.x - q + kQueues - 1) / kQueues;  // first position of queue q past the grid
+    const bool more = (uint32_t)count > gridDim.x;
+    uint32_t idx = blockIdx.x;
+    while (idx < (uint32_t)count) {
         const GraphDesc d = descs[idx];
         // The next position is fetched while this graph is solved, so the
         // queue's latency is paid once per workgroup, not once per graph.
         // Thread 0 writes `next` again only after the barriers inside
         // solve_graph, which every thread passes after reading it.
-        int32_t pre = 0;
-        if (threadIdx.x == 0) pre = atomicAdd(queue_head, 1);
+        uint32_t pre = 0;
+        if (more && threadIdx.x == 0) pre = atomicAdd(heads + q * kQueueStride, 1u);
         if ((uint32_t)d.n <= kWideMaxN)
             solve_graph(reinterpret_cast<uint32_t*>(spi), d, halve, bad);
         else
             solve_graph(spi, d, halve, bad);
-        if (threadIdx.x == 0) next = pre;
+        if (!more) break;
+        if (threadIdx.x == 0) next = q + kQueues * (k0 + pre);
         __syncthreads();
         idx = next;
     }
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(1024) void k_single_lds(GraphDesc d, int32_t* statu
 // invalid (not starting at 0, decreasing, more than max_n vertices) or that
 // has entries but no vertex gets an empty descriptor (nothing is read or
 // written for it); status[1] / status[2] (host memory) then receive
-// kStatusBadGraph / kStatusRange.  ctrl->queue_head is cleared for the
+// kStatusBadGraph / kStatusRange.  The queue counters are cleared for the
 // solve.
 
 __device__ __forceinline__ int batch_size_class(uint64_t w) {
@@ -284,8 +292,10 @@ __device__ __forceinline__ int batch_size_class(uint64_t w) {
     return lg * 4 + frac;
 }
 
-// min(cap, round(m / n)), at least 1 (cap 0: round(m / n) up to 2^20)
+// min(cap, round(m / n)), at least 1 (cap 0: round(m / n) up to 2^20;
+// kSegAuto: the default rule)
 __device__ __forceinline__ int32_t batch_segments(int64_t m, int64_t n, int32_t cap) {
+    if (cap == kSegAuto) return lds_auto_segments(m, n);
     if (cap > 0 && cap <= 16 && m < (int64_t(1) << 61)) {
         int32_t k = cap;
         while (k > 1 && 2 * m < (2 * (int64_t)k - 1) * n) --k;
@@ -324,13 +334,46 @@ __device__ __forceinline__ PrepGraph prep_graph(const int64_t* vo, const int64_t
     return p;
 }
 
+// The batch without preparation: workgroup b takes graphs b, b + gridDim.x,
+// ... in the given order and reads each one's offsets itself (from pinned
+// host memory when the offsets are there).  For small graphs the order does
+// not matter (no graph takes much longer than another), and the call is one
+// launch instead of three and a copy.  Invalid graphs are skipped and
+// reported as by the preparation launches.
+template <bool HALVE>
+__global__ __launch_bounds__(1024) void k_batch_direct(BatchSrc src, int32_t count,
+                                                       int32_t* status) {
+    extern __shared__ uint16_t spi[];
+    bool bad = false;
+    int32_t flags = 0;
+    for (int64_t g = blockIdx.x; g < count; g += gridDim.x) {
+        const PrepGraph p = prep_graph(src.vo, src.eo, (int32_t)g, src.max_n, src.u && src.v,
+                                       src.out != nullptr);
+        flags |= p.flag;
+        GraphDesc d;
+        d.u = src.u + p.e0;
+        d.v = src.v + p.e0;
+        d.out = src.out + p.v0;
+        d.m = p.m;
+        d.n = (int32_t)p.n;
+        d.segments = p.n > 0 ? batch_segments(p.m, p.n, src.seg_cap) : 1;
+        solve_graph(reinterpret_cast<uint32_t*>(spi), d, HALVE, bad);
+        __syncthreads();  // the label reads before the next graph's init
+    }
+    if (bad) __hip_atomic_store(status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0 && (flags & kStatusBadGraph))
+        __hip_atomic_store(status + 1, kStatusBadGraph, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0 && (flags & kStatusRange))
+        __hip_atomic_store(status + 2, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Step 1 (one thread per graph, kPrepGraphs per workgroup): each workgroup
 // counts its graphs per class into its row of `rows` (W x 256).
 __global__ __launch_bounds__(1024) void k_batch_prep_count(const int64_t* __restrict__ vo,
                                                            const int64_t* __restrict__ eo,
                                                            int32_t B, int32_t max_n, bool edges,
                                                            bool labels, int32_t* __restrict__ rows,
-                                                           Ctrl* ctrl) {
+                                                           uint32_t* __restrict__ heads) {
     __shared__ int32_t hist[256];
     const int32_t tid = threadIdx.x;
     if (tid < 256) hist[tid] = 0;
@@ -339,7 +382,7 @@ __global__ __launch_bounds__(1024) void k_batch_prep_count(const int64_t* __rest
     if (g < B) atomicAdd(&hist[prep_graph(vo, eo, g, max_n, edges, labels).cls], 1);
     __syncthreads();
     if (tid < 256) rows[blockIdx.x * 256 + tid] = hist[tid];
-    if (blockIdx.x == 0 && tid == 0) ctrl->queue_head = 0;
+    if (blockIdx.x == 0 && tid < kQueues * kQueueStride) heads[tid] = 0;
 }
 
 // Up to this many preparation workgroups, each placing workgroup sums the
@@ -453,12 +496,12 @@ __global__ __launch_bounds__(1024) void k_batch_prep_place(
 
 hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, const int32_t* u,
                              const int32_t* v, int32_t* out, int32_t max_n, int32_t seg_cap,
-                             GraphDesc* descs, int32_t* rows, Ctrl* ctrl, int32_t* status,
+                             GraphDesc* descs, int32_t* rows, uint32_t* heads, int32_t* status,
                              hipStream_t s) {
     if (B <= 0) return hipSuccess;
     const int32_t W = (int32_t)(((int64_t)B + kPrepGraphs - 1) / kPrepGraphs);
     k_batch_prep_count<<<W, kPrepGraphs, 0, s>>>(vo, eo, B, max_n, u && v, out != nullptr, rows,
-                                                 ctrl);
+                                                 heads);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int32_t* totals = nullptr;
@@ -628,6 +671,8 @@ hipError_t prepare_batch_lds() {
     static hipError_t once = [] {
         const void* fn[] = {reinterpret_cast<const void*>(&k_batch_lds<true>),
                             reinterpret_cast<const void*>(&k_batch_lds<false>),
+                            reinterpret_cast<const void*>(&k_batch_direct<true>),
+                            reinterpret_cast<const void*>(&k_batch_direct<false>),
                             reinterpret_cast<const void*>(&k_single_lds<true>),
                             reinterpret_cast<const void*>(&k_single_lds<false>)};
         for (const void* f : fn) {
@@ -655,22 +700,64 @@ hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hi
     return hipGetLastError();
 }
 
-hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n,
-                            int32_t* queue_head, int32_t* status, bool halve, int grid,
-                            hipStream_t s, int block) {
+// Workgroups of a persistent LDS launch that fit on the CUs at once (LDS, with
+// a margin for the kernel's own static LDS, and thread limits, at most 32
+// waves per CU).
+static int64_t batch_resident(int32_t max_n, int block, int cus) {
+    const size_t lds = lds_tree_bytes(max_n);
+    const size_t per_cu = std::min<size_t>((size_t)(160 * 1024) / (lds + 256), (size_t)(2048 / block));
+    return cus * (int64_t)std::max<size_t>(1, per_cu);
+}
+
+// A small graph does not fill 1024 threads, and smaller workgroups keep more
+// graphs in flight; a few graphs are solved faster by large ones.  Per call,
+// device offsets, at 128 / 256 / 512 / 1024 threads (us): 20,000 graphs of
+// up to 256 vertices 75 / 76 / 99 / 167; 8,000 of up to 1,024 vertices 61 /
+// 60 / 69 / 98, 20 of them 33 / 30 / 29 / 29; 8,000 of up to 4,096 vertices
+// 85 / 73 / 82 / 110, 2,000 of them 65 / 50 / 47 / 50, 200 of them 53 / 40 /
+// 35 / 33; 2,000 of up to 8,192 vertices 109 / 75 / 61 / 62.
+int batch_block(int32_t count, int32_t max_n) {
+    if (count <= 512) return max_n <= 1024 ? 512 : 1024;
+    if (max_n <= 256) return 128;
+    if (max_n <= 1024) return 256;
+    if (max_n <= 4096) return count > 4096 ? 256 : 512;
+    return max_n <= 8192 ? 512 : 1024;
+}
+
+// The order of the graphs only matters when workgroups take several each, and
+// hardly for the smallest ones: otherwise the preparation launches are left
+// out (200 graphs of up to 4,096 vertices 28.6 against 33.3 us, 2,000 of up
+// to 1,024 vertices 32.8 against 36.0; where it matters: 8,000 of up to 4,096
+// vertices 102 against 82; 100,000 of up to 256 vertices 175 against 219).
+bool batch_direct(int32_t count, int32_t max_n, int block, int cus) {
+    return max_n <= 256 || ((uint32_t)max_n <= kWideMaxN && count <= batch_resident(max_n, block, cus));
+}
+
+hipError_t launch_batch_lds(const GraphDesc* descs, int32_t count, int32_t max_n, uint32_t* heads,
+                            int32_t* status, bool halve, int cus, hipStream_t s, int block) {
     if (count <= 0) return hipSuccess;
     if (max_n < 1 || max_n > 65536) return hipErrorInvalidValue;
     if (block < 64 || block > 1024 || block % 64) return hipErrorInvalidValue;
     const size_t lds = lds_tree_bytes(max_n);
-    // persistent: as many workgroups as fit on the CUs at once (LDS, with a
-    // margin for the kernel's own static LDS, and thread limits), at most 32
-    // waves per CU
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>((size_t)(160 * 1024) / (lds + 256),
-                                                                 (size_t)(2048 / block)));
+    const int grid = (int)std::min<int64_t>(count, batch_resident(max_n, block, cus));
     if (halve)
-        k_batch_lds<true><<<grid * per_cu, block, lds, s>>>(descs, count, queue_head, status);
+        k_batch_lds<true><<<grid, block, lds, s>>>(descs, count, heads, status);
     else
-        k_batch_lds<false><<<grid * per_cu, block, lds, s>>>(descs, count, queue_head, status);
+        k_batch_lds<false><<<grid, block, lds, s>>>(descs, count, heads, status);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_direct(const BatchSrc& src, int32_t count, int32_t* status, bool halve,
+                               int cus, hipStream_t s, int block) {
+    if (count <= 0) return hipSuccess;
+    if (src.max_n < 1 || (uint32_t)src.max_n > kWideMaxN) return hipErrorInvalidValue;
+    if (block < 64 || block > 1024 || block % 64) return hipErrorInvalidValue;
+    const size_t lds = lds_tree_bytes(src.max_n);
+    const int grid = (int)std::min<int64_t>(count, batch_resident(src.max_n, block, cus));
+    if (halve)
+        k_batch_direct<true><<<grid, block, lds, s>>>(src, count, status);
+    else
+        k_batch_direct<false><<<grid, block, lds, s>>>(src, count, status);
     return hipGetLastError();
 }
 

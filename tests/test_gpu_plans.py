@@ -61,3 +61,51 @@ def test_small_lists(dev, n, m):
                 torch.cuda.synchronize()
                 cc.stream_status()
             assert ei.value.code == cc.CC_ERR_RANGE
+
+
+# (count, lo, hi): vertex counts log-uniform in [lo, hi].  One graph, a launch
+# without preparation at each workgroup size, the last and first counts on
+# either side of its rule, more graphs than workgroups (every queue drawn
+# from), the first sizes with 16-bit slots
+@pytest.mark.parametrize("count,lo,hi", [(1, 1, 1), (7, 1, 3), (512, 200, 256), (513, 200, 256),
+                                         (9000, 1, 40), (512, 300, 1024), (2049, 257, 1024),
+                                         (300, 1025, 4096), (1100, 1025, 4096), (4100, 700, 1025),
+                                         (600, 4097, 8192), (40, 30000, 32768), (40, 30000, 32769)])
+def test_batches_by_rule(dev, count, lo, hi):
+    rng = np.random.default_rng(count + hi)
+    nv = np.exp(rng.uniform(np.log(lo), np.log(hi + 0.5), count)).astype(np.int64)
+    nv[rng.integers(0, count)] = hi
+    me = (nv * rng.uniform(0, 3, count)).astype(np.int64)
+    if count > 5:
+        nv[3] = me[3] = me[4] = 0
+    vo = np.concatenate([[0], np.cumsum(nv)])
+    eo = np.concatenate([[0], np.cumsum(me)])
+    top = np.repeat(nv, me)
+    u = (rng.random(len(top)) * top).astype(np.int32)
+    v = (rng.random(len(top)) * top).astype(np.int32)
+    want = oracle.labels_batch(u, v, vo, eo)
+    du, dv = put(u, dev), put(v, dev)
+    dvo, deo = torch.from_numpy(vo).to(dev), torch.from_numpy(eo).to(dev)
+    side = torch.cuda.Stream()
+    for opt in (cc.Options(), cc.Options(path_halving="off"), cc.Options(block=64, segments=3),
+                cc.Options(graph=True)):
+        print("batch", count, lo, hi, opt.block, opt.graph, flush=True)
+        for rep in range(2 if opt.graph else 1):
+            assert np.array_equal(cc.labels_batch(du, dv, vo, eo, options=opt,
+                                                  stream=side).cpu().numpy(), want), opt
+            out = torch.full((len(want),), -7, dtype=torch.int32, device=dev)
+            torch.cuda.synchronize()
+            cc.labels_batch_device(du, dv, dvo, deo, hi, out, options=opt, stream=side)
+            assert np.array_equal(out.cpu().numpy(), want), opt
+    if me[-1] > 0:
+        u[-1] = nv[-1]
+        du = put(u, dev)
+        for call in (lambda: cc.labels_batch(du, dv, vo, eo),
+                     lambda: cc.labels_batch_device(du, dv, dvo, deo, hi, out)):
+            with pytest.raises(cc.CCError) as ei:
+                call()
+            assert ei.value.code == cc.CC_ERR_RANGE
+    if hi > 1:
+        with pytest.raises(cc.CCError) as ei:
+            cc.labels_batch_device(put(v, dev), dv, dvo, deo, hi - 1, out)
+        assert ei.value.code == cc.CC_ERR_ARG
