@@ -186,7 +186,7 @@ def main():
     traffic = None
     if st.get("hook") == 1:
         alg_bytes = 8.0 * m  # each int32 (u, v) entry read once across the Atomic-Hook launches
-        kernel = "k_ahook + k_ahook_hotv (all Atomic-Hook launches of one solve)"
+        kernel = "k_ahook_short + k_filter (all Atomic-Hook launches of one solve)"
         if args.hook == "auto" and args.filter == "auto" and args.hot == "auto" and not (
                 args.segments or args.ept or args.block or args.coherent or args.symmetric):
             traffic = measured_traffic(args.workload, "atomic")

@@ -60,9 +60,10 @@ extern "C" {
 #define CC_ERR_NOCONVERGE (-5) /* the atomic-free Hook hit opts->max_rounds       */
 
 /* ---------------------------------------------------------------- options */
-#define CC_HOOK_AUTO 0   /* library choice (the default): for lists of m >= 2^22
-                            entries the Atomic-Hook with the giant filter when
-                            m / n >= 8 and the hybrid plan below otherwise; the
+#define CC_HOOK_AUTO 0   /* library choice (the default): the Atomic-Hook with the
+                            giant filter for lists of m >= 2^21 entries (CSR: 2^22) with
+                            m / n >= 8, the hybrid plan below for the other lists of
+                            m >= 2^22 entries; the
                             atomic-free Hook for smaller lists (the hybrid plan for a
                             no-sync call); the Atomic-Hook with the symmetric flag.
                             The smallest lists (n <= 32,768, 2 n + m <= 131,072, no
@@ -91,7 +92,9 @@ typedef struct cc_options {
     int32_t segments;         /* Atomic-Hook: number of edge segments s; 0 = default
                                  max(1, round(m / n)) (16x that when CC_HOOK_AUTO picks the
                                  filtered Atomic-Hook, so the first segment is ~n/16
-                                 entries); clamped to [1, ceil(m / 4)]                  */
+                                 entries; up to 2^19 vertices atomic-free rounds over the
+                                 first n entries take its place); clamped to
+                                 [1, ceil(m / 4)]                                       */
     int32_t filter;           /* CC_FILTER_* (Atomic-Hook only); default CC_FILTER_AUTO  */
     int32_t filter_after;     /* segments hooked before the giant-component sample
                                  (0 = default 1)                                        */
@@ -126,6 +129,7 @@ typedef struct cc_options {
                                  while they are in the giant component); CC_HOT_LARGE:
                                  32,768 bitmap-word slots (160 KiB); CC_HOT_ON: 16,384
                                  word slots; CC_HOT_OFF: none.  CC_HOT_AUTO (default):
+                                 the whole bitmap in LDS for n <= 1,310,720, then
                                  CC_HOT_VERTEX for n <= 255 * 81920, else CC_HOT_LARGE  */
     int32_t path_halving;     /* Atomic-Hook climb: CC_HALVE_AUTO (default, on), CC_HALVE_ON
                                  or CC_HALVE_OFF (Fig. 3 exactly) -- re-point a non-root

@@ -67,6 +67,26 @@ int64_t segment_start(int64_t m, int64_t i, int64_t S) {
 }
 
 
+// The automatic filtered plan starts with kPrefixRounds atomic-free rounds
+// over the first n entries and a contracting hook of the same entries up to
+// kPrefixMaxN vertices, and with an Atomic-Hook of the first n / 16 entries
+// above (R-MAT 18, m = 2.6 M: 98 against 106 us; R-MAT 20, m = 2^24: 202
+// against 197; R-MAT 21, m = 50 M: 515 against 481; uniform n = 262,144,
+// m = 2^22: 182 against 191).  Rounds alone leave fragments that then meet
+// in the filtered launches, thousands of entries on a few roots (R-MAT 18
+// 170 us, uniform n = 65,536 743 us).  The launches after the rounds take
+// kPrefixStart * n entries and then kPrefixGrowth times more each.
+//
+// The Atomic-Hook of the first n / 16 entries runs two entries per thread up
+// to kShortMaxN vertices, 8 per thread above, where more climbs at once
+// contend for the hubs (R-MAT 20 197 against 229 us, 22 667 and 670, 23
+// 1,348 against 1,325, 24 3,313 against 3,257).
+constexpr int32_t kShortMaxN = 1 << 22;
+constexpr int32_t kPrefixMaxN = 1 << 19;
+constexpr int kPrefixRounds = 3;
+constexpr int64_t kPrefixStart = 2;
+constexpr int64_t kPrefixGrowth = 8;
+
 struct Plan {
     int hook = CC_HOOK_ATOMIC;  // resolved variant: CC_HOOK_ATOMIC, CC_HOOK_PLAIN or CC_HOOK_HYBRID
     int segments = 1;
@@ -87,6 +107,9 @@ struct Plan {
     bool no_sync = false;    // enqueue only; status read later by cc_stream_status
     uint32_t tau = 0xffffffffu;  // atomic-free Hook: frontier rewrite threshold (1/1000)
     bool lds_single = false;     // one workgroup solves the whole graph in LDS
+    bool lds_bits = false;       // hot: the whole giant bitmap in LDS
+    bool auto_filter = false;    // the filtered schedule of the automatic choice
+    bool prefix = false;         // auto_filter: atomic-free rounds over a prefix come first
 };
 
 // Small lists that the automatic choice gives to one LDS workgroup.  The
@@ -127,11 +150,13 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     p.symmetric = op.symmetric == 1;
     if (op.hot_cache < CC_HOT_AUTO || op.hot_cache > CC_HOT_VERTEX)
         return fail(CC_ERR_ARG, "unknown cc_options.hot_cache");
-    // Hot cache: the vertex table where every id fits its tags (n <= 255 *
+    // Hot cache: the whole bitmap where it fits the LDS (n <= 1,310,720),
+    // then the vertex table where every id fits its tags (n <= 255 *
     // 81,920; R-MAT 24: 3.9 ms against 4.52 with 32,768 word slots), else the
     // word table.
     const bool vert = op.hot_cache == CC_HOT_VERTEX ||
                       (op.hot_cache == CC_HOT_AUTO && n <= (int64_t)kVertTagNone * kVertSets);
+    p.lds_bits = op.hot_cache == CC_HOT_AUTO && n <= kLdsBitsMaxN;
     p.hot_slots = op.hot_cache == CC_HOT_ON ? 16384 : vert ? kVertSlots : 32768;
     if (op.path_halving < CC_HALVE_AUTO || op.path_halving > CC_HALVE_OFF)
         return fail(CC_ERR_ARG, "unknown cc_options.path_halving");
@@ -161,7 +186,8 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     // rounds: its large sparse inputs take the hybrid plan (grid as CSR 0.73
     // ms against 1.47 Atomic-Hook), the rest the Atomic-Hook.
     const bool large = m >= (int64_t(1) << 22);
-    const bool dense_large = large && n > 0 && m >= 8 * (int64_t)n;
+    const bool dense_large = m >= int64_t(1) << (input == kInputCsr ? 22 : 21) &&
+                             n > 0 && m >= 8 * (int64_t)n;
     bool auto_filtered = false;
     if (op.hook == CC_HOOK_AUTO) {
         if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large) {
@@ -209,6 +235,9 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     }
     if (p.filter == CC_FILTER_GIANT && p.filter_after >= p.segments) p.filter = CC_FILTER_OFF;
     p.hot = p.filter == CC_FILTER_GIANT && op.hot_cache != CC_HOT_OFF && !p.coherent;
+    p.auto_filter = auto_filtered && p.filter == CC_FILTER_GIANT && p.hot && op.segments == 0 &&
+                    op.filter_after == 0 && op.block == 0 && op.edges_per_thread == 0;
+    p.prefix = p.auto_filter && n <= kPrefixMaxN;
     if (op.block != 0) {
         if (op.block < 64 || op.block > 1024 || op.block % 64)
             return fail(CC_ERR_ARG, "cc_options.block must be a multiple of 64 in [64, 1024]");
@@ -270,7 +299,8 @@ Layout layout(int32_t n, int64_t m, const Plan& p) {
     if (p.hook == CC_HOOK_ATOMIC && p.filter == CC_FILTER_GIANT) {
         L.bits = off;
         off += align256(((size_t)n + 31) / 32 * 4);
-        if (p.hot && p.hot_slots == kVertSlots) {  // selection scratch, byte table
+        if (p.hot && p.lds_bits) {  // nothing but the bitmap
+        } else if (p.hot && p.hot_slots == kVertSlots) {  // selection scratch, byte table
             L.hot_counts = off;
             off += align256((size_t)kVertScratchWords * 4);
             L.hot_tags = L.hot_vals = off;  // tags, then member flags
@@ -559,6 +589,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     uint32_t* bits = fb.bits;
     const bool hot = p.hot && fb.hot_tags != nullptr;
     const bool vhot = p.hot && fb.vtab != nullptr;
+    const bool lds_bits = p.hot && p.lds_bits;
     const int S = p.segments;
     auto bound = [&](int64_t i) -> int64_t {
         if (i >= S) return m;
@@ -577,52 +608,84 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
         }
     } else {
         const int fa = p.filter_after;
-        for (int i = 0; i < fa; ++i) {
-            TIMED(kPhaseHook, launch_ahook(u, v, bound(i), bound(i + 1), pi, n, ctrl, nullptr,
-                                           p.block, p.ept, p.coherent, p.halve, p.symmetric, s));
+        // The part of the list that finds the giant.
+        const int64_t prefix = std::min<int64_t>(m, n) & ~int64_t(3);
+        for (int i = 0; p.prefix && i <= kPrefixRounds; ++i) {
+            if (i < kPrefixRounds)
+                TIMED(kPhaseHook, launch_hook_prefix(u, v, prefix, pi, n, i == 0, s));
+            else
+                TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, s));
+            TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s));
+            ++hooks;
+            ++jumps;
+        }
+        for (int i = 0; !p.prefix && i < fa; ++i) {
+            if (p.auto_filter && n <= kShortMaxN)
+                TIMED(kPhaseHook, launch_ahook_short(u, v, bound(i), bound(i + 1), pi, n, ctrl,
+                                                     p.halve, p.symmetric, s));
+            else
+                TIMED(kPhaseHook, launch_ahook(u, v, bound(i), bound(i + 1), pi, n, ctrl, nullptr,
+                                               p.block, p.ept, p.coherent, p.halve, p.symmetric, s));
             TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
             ++hooks;
             ++jumps;
         }
-        TIMED(kPhaseOther, launch_sample_giant(u, m, pi, n, ctrl, 2048, s));
-        TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
+        if (vhot) TIMED(kPhaseOther, launch_hot_vprepare(u, v, m, n, fb.hot_counts, fb.vtab, s));
+        TIMED(kPhaseOther, launch_sample_giant(u, m, pi, n, ctrl, s));
+        if (vhot)  // the bitmap and the table's member flags
+            TIMED(kPhaseOther, launch_mj_bitmap(pi, n, ctrl, bits, nullptr, nullptr, 0, fb.vtab, s));
+        else
+            TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
         if (hot) {
             TIMED(kPhaseOther, launch_hot_prepare(u, v, m, n, fb.hot_counts, fb.hot_tags,
                                                   p.hot_slots, s));
             TIMED(kPhaseOther, launch_hot_values(bits, fb.hot_tags, fb.hot_vals, ctrl,
                                                  p.hot_slots, s));
         }
-        if (vhot) {
-            TIMED(kPhaseOther, launch_hot_vprepare(u, v, m, n, fb.hot_counts, fb.vtab, s));
-            TIMED(kPhaseOther, launch_hot_vvalues(bits, fb.vtab, ctrl, s));
-        }
         // The rest of the list in super-segments that grow by kSuperGrowth,
         // each followed by a Compress and a bitmap refresh.
-        int64_t g = fa, step = kSuperStart * fa;
-        while (g < S) {
-            const int64_t h = std::min<int64_t>(S, g + step);
-            if (hot)
-                TIMED(kPhaseHook, launch_ahook_hot(u, v, bound(g), bound(h), pi, n, ctrl, bits,
+        int64_t g = fa, step = kSuperStart * fa;                  // in segments
+        int again = 0;
+        int64_t from = p.prefix ? prefix : bound(fa), take = kPrefixStart * (int64_t)n;  // in entries
+        while (from < m) {
+            int64_t to;
+            if (p.prefix) {
+                to = std::min<int64_t>(m, (from + take) & ~int64_t(3));
+                if (m - to < take / 2) to = m;
+                take *= kPrefixGrowth;
+            } else {
+                g = std::min<int64_t>(S, g + step);
+                to = bound(g);
+                step *= kSuperGrowth;
+            }
+            if (lds_bits)
+                TIMED(kPhaseHook, launch_filter_bits(u, v, from, to, pi, n, ctrl, bits, p.halve,
+                                                     p.symmetric, s));
+            else if (hot)
+                TIMED(kPhaseHook, launch_ahook_hot(u, v, from, to, pi, n, ctrl, bits,
                                                    fb.hot_tags, fb.hot_vals, p.ept, p.hot_slots,
                                                    p.halve, p.symmetric, s));
             else if (vhot)
-                TIMED(kPhaseHook, launch_ahook_hotv(u, v, bound(g), bound(h), pi, n, ctrl, bits,
-                                                    fb.vtab, p.halve, p.symmetric, s));
+                TIMED(kPhaseHook, launch_filter_vertex(u, v, from, to, pi, n, ctrl, bits, fb.vtab,
+                                                       p.halve, p.symmetric, s));
             else
-                TIMED(kPhaseHook, launch_ahook(u, v, bound(g), bound(h), pi, n, ctrl, bits,
+                TIMED(kPhaseHook, launch_ahook(u, v, from, to, pi, n, ctrl, bits,
                                                p.block, p.ept, p.coherent, p.halve, p.symmetric, s));
-            if (h < S && !p.coherent) {
+            // A giant that the first part was too short for (uniform random
+            // lists need ~n / 2 entries) is looked for again after the next two.
+            if (p.auto_filter && to < m && ++again <= 2)
+                TIMED(kPhaseOther, launch_sample_giant(u, m, pi, n, ctrl, s, true));
+            if (to < m && !p.coherent) {
                 // Compress, bitmap refresh and hot-word refresh in one pass
                 TIMED(kPhaseCompress, launch_mj_bitmap(pi, n, ctrl, bits, hot ? fb.hot_tags : nullptr,
                                                        fb.hot_vals, p.hot_slots, fb.vtab, s));
             } else {
                 TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
-                if (h < S) TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
+                if (to < m) TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
             }
             ++hooks;
             ++jumps;
-            g = h;
-            step *= kSuperGrowth;
+            from = to;
         }
     }
     if (st) {
@@ -850,7 +913,8 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
             KeyHash k;
             k.add(n).add(m).add(u).add(v).add(out).add(ws).add(s).add(p.hook).add(p.segments)
                 .add(p.filter).add(p.filter_after).add(p.block).add(p.ept).add(p.coherent)
-                .add(p.hot).add(p.hot_slots).add(p.halve).add(p.symmetric);
+                .add(p.hot).add(p.hot_slots).add(p.lds_bits).add(p.auto_filter).add(p.prefix).add(p.halve)
+                .add(p.symmetric);
             rc = run_graph(pe, k.h, s, [&]() { return enqueue(st); });
         } else {
             rc = enqueue(st);
@@ -1076,7 +1140,7 @@ int32_t stream_impl(int32_t n, const int32_t* hu, const int32_t* hv, int64_t m, 
         HIPCHK(launch_mj(out, n, nullptr, p.coherent, s));
         ++hooks;
         ++jumps;
-        if (filter && i == 0) HIPCHK(launch_sample_giant(su[b], len, out, n, ctrl, 2048, s));
+        if (filter && i == 0) HIPCHK(launch_sample_giant(su[b], len, out, n, ctrl, s));
         if (filter && i + 1 < chunks) HIPCHK(launch_bitmap(out, n, ctrl, bits, s));
         HIPCHK(hipEventRecord(pe->consumed[b], s));
     }
@@ -1177,7 +1241,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
             ++jumps;
         }
         // endpoints sampled from col[] (the second endpoints of the entries)
-        TIMED(kPhaseOther, launch_sample_giant(col, m, out, n, ctrl, 2048, s));
+        TIMED(kPhaseOther, launch_sample_giant(col, m, out, n, ctrl, s));
         TIMED(kPhaseOther, launch_bitmap(out, n, ctrl, bits, s));
         int64_t g = fa, step = kSuperStart * fa;
         while (g < S) {

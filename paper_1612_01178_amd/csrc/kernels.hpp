@@ -16,6 +16,16 @@ hipError_t launch_ahook(const int32_t* u, const int32_t* v, int64_t begin, int64
                         int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, int block,
                         int ept, bool coherent, bool halve, bool sym, hipStream_t s);
 
+// Atomic-Hook of entries [begin, end), one entry per thread, no filter (short
+// segments).
+hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                              int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, bool sym,
+                              hipStream_t s);
+// One atomic-free Hook (Fig. 2) pass over entries [0, m), which are hooked
+// again later; `first`: pi is the identity.  No range check.
+hipError_t launch_hook_prefix(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi, int32_t n,
+                              bool first, hipStream_t s);
+
 // Multi-Jump (Fig. 3) over all n vertices.  When `gate` is non-null the
 // kernel does nothing if *gate == 0.  `coherent` selects agent-scope tree
 // loads and stores (see common.hpp).
@@ -31,10 +41,10 @@ hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t 
                       uint32_t limit = 0);
 
 // Giant-component sample: label of the component that holds the most of
-// `samples` edge endpoints drawn across entries [0, m); sets ctrl->giant and
-// ctrl->filter_on.  Requires pi to be a forest of stars (after Multi-Jump).
+// 1,024 edge endpoints drawn across entries [0, m); sets ctrl->giant and
+// ctrl->filter_on.  `again`: only when the filter is not on yet.
 hipError_t launch_sample_giant(const int32_t* u, int64_t m, const int32_t* pi, int32_t n,
-                               Ctrl* ctrl, int samples, hipStream_t s);
+                               Ctrl* ctrl, hipStream_t s, bool again = false);
 
 // bits[v] = (pi[v] == pi[ctrl->giant]) for v < n (stars required); no-op
 // unless ctrl->filter_on.
@@ -66,6 +76,11 @@ hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int
 hipError_t launch_ahook_pairs(const int2* fr, const uint32_t* count, int64_t cap, int32_t* pi,
                               bool halve, int grid_cap, hipStream_t s);
 
+// Atomic-Hook of entries [begin, end) with each workgroup's active roots joined
+// in LDS first; pi a forest of stars with few roots left.
+hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                                int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s);
+
 // tau: frontier rewrite threshold in thousandths (0xffffffff = every round).
 hipError_t launch_compact(int round, const int32_t* u, const int32_t* v, int64_t m, int2* f0,
                           int2* f1, int64_t cap, const int32_t* pi, int32_t n, Ctrl* ctrl,
@@ -94,7 +109,8 @@ constexpr uint32_t kVertTagNone = 255;
 // Selection sample: up to kVertRuns runs of 64 entries, kVRunsPerPart runs per
 // workgroup part; sets grouped in kVBuckets buckets of kVBucketSets.
 constexpr int64_t kVertRuns = int64_t(1) << 15;
-constexpr int kVRunsPerPart = 128;
+constexpr int kVRunsPerPart = 128;       // runs of one part
+constexpr int kVRunsPerPartShort = 32;   // where that gives at most kVPartsMax parts
 constexpr int kVPartsMax = (int)(kVertRuns / kVRunsPerPart);
 constexpr int kVPartCap = kVRunsPerPart * 64 * 2;  // endpoints of one part
 constexpr int kVBucketSets = 64;
@@ -102,15 +118,20 @@ constexpr int kVBuckets = kVertSets / kVBucketSets;
 // Scratch words used by launch_hot_vprepare.
 constexpr int64_t kVertScratchWords = (int64_t)kVPartsMax * kVPartCap + 2LL * kVPartsMax * kVBuckets;
 // For every set, the kVertWays most sampled vertices (scratch:
-// kVertScratchWords words); member flags are filled by launch_hot_vvalues.
+// kVertScratchWords words); member flags are cleared (launch_mj_bitmap fills
+// them).
 hipError_t launch_hot_vprepare(const int32_t* u, const int32_t* v, int64_t m, int32_t n,
                                uint32_t* scratch, uint8_t* table, hipStream_t s);
-// Every slot's member flag from the bitmap; no-op unless ctrl->filter_on.
-hipError_t launch_hot_vvalues(const uint32_t* bits, uint8_t* table, const Ctrl* ctrl, hipStream_t s);
-// Filtered Atomic-Hook of entries [begin, end) with the vertex table in LDS.
-hipError_t launch_ahook_hotv(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
-                             int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits,
-                             const uint8_t* table, bool halve, bool sym, hipStream_t s);
+// Filtered Atomic-Hook of entries [begin, end), membership tests answered in
+// LDS from the whole bitmap (n <= kLdsBitsMaxN) or from the vertex table.
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int32_t kLdsBitsMaxN = kLdsBytes * 8;  // 1,310,720
+hipError_t launch_filter_bits(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                              int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, bool halve,
+                              bool sym, hipStream_t s);
+hipError_t launch_filter_vertex(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                                int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits,
+                                const uint8_t* table, bool halve, bool sym, hipStream_t s);
 // Counts sampled endpoints per bitmap word (counts: ceil(n/32) words of
 // scratch) and picks the hottest word for every slot.
 hipError_t launch_hot_prepare(const int32_t* u, const int32_t* v, int64_t m, int32_t n,

@@ -230,6 +230,86 @@ hipError_t launch_ahook(const int32_t* u, const int32_t* v, int64_t begin, int64
     return hipGetLastError();
 }
 
+// Atomic-Hook of a short segment (the filtered plan's first one), two entries
+// per thread: the segment is bound by the chain of each thread's climbs, not
+// by the number of climbs in flight, and at 8 entries per thread it keeps a
+// fraction of the CUs busy (R-MAT 21, 131,072 entries: 62 us on 32 CUs).  The
+// climb begins with the compare-and-swap where the larger start is the
+// endpoint itself (see hook_pair).
+template <bool HALVE>
+__global__ __launch_bounds__(256) void k_ahook_short(const int32_t* __restrict__ eu,
+                                                     const int32_t* __restrict__ ev, int64_t begin,
+                                                     int64_t end, int32_t* pi, int32_t n,
+                                                     Ctrl* ctrl, bool sym) {
+    const int64_t t0 = begin + (int64_t)blockIdx.x * blockDim.x * 2 + threadIdx.x;
+    int32_t a[2], b[2];
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int64_t e = t0 + (int64_t)j * blockDim.x;
+        a[j] = e < end ? __builtin_nontemporal_load(eu + e) : 0;
+        b[j] = e < end ? __builtin_nontemporal_load(ev + e) : 0;
+        const bool in = max((uint32_t)a[j], (uint32_t)b[j]) < (uint32_t)n;
+        bad |= !in;
+        if (!in || (sym && a[j] > b[j])) a[j] = b[j] = 0;
+    }
+    if (bad) atomicOr(&ctrl->status, kStatusRange);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) hook_pair<HALVE>(pi, a[j], b[j], kHalveEveryFiltered);
+}
+
+hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                              int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, bool sym,
+                              hipStream_t s) {
+    if (end <= begin) return hipSuccess;
+    const int64_t grid64 = (end - begin + 511) / 512;
+    if (grid64 > 0x7fffffff) return hipErrorInvalidValue;
+    if (halve) k_ahook_short<true><<<(int)grid64, 256, 0, s>>>(u, v, begin, end, pi, n, ctrl, sym);
+    else k_ahook_short<false><<<(int)grid64, 256, 0, s>>>(u, v, begin, end, pi, n, ctrl, sym);
+    return hipGetLastError();
+}
+
+// Atomic-free Hook (Fig. 2) of entries [0, m): a round over a prefix of the
+// list, whose entries are hooked again later, so a lost store costs nothing.
+// FIRST: every vertex is its own parent (the init's values), no gather.
+// Invalid endpoints are skipped (the later pass reports them).
+constexpr int kPrefixEPT = 2;
+
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_hook_prefix(const int32_t* __restrict__ eu,
+                                                     const int32_t* __restrict__ ev, int64_t m,
+                                                     int32_t* pi, int32_t n) {
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x * kPrefixEPT + threadIdx.x;
+    int32_t a[kPrefixEPT], b[kPrefixEPT];
+#pragma unroll
+    for (int j = 0; j < kPrefixEPT; ++j) {
+        const int64_t e = t0 + (int64_t)j * blockDim.x;
+        a[j] = e < m ? __builtin_nontemporal_load(eu + e) : 0;
+        b[j] = e < m ? __builtin_nontemporal_load(ev + e) : 0;
+        if (max((uint32_t)a[j], (uint32_t)b[j]) >= (uint32_t)n) a[j] = b[j] = 0;
+    }
+    if (!FIRST) {
+#pragma unroll
+        for (int j = 0; j < kPrefixEPT; ++j) {
+            a[j] = ld_rlx(pi + a[j]);
+            b[j] = ld_rlx(pi + b[j]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kPrefixEPT; ++j)
+        if (a[j] != b[j]) st_rlx(pi + max(a[j], b[j]), min(a[j], b[j]));
+}
+
+hipError_t launch_hook_prefix(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi, int32_t n,
+                              bool first, hipStream_t s) {
+    if (m <= 0) return hipSuccess;
+    const int64_t grid64 = (m + 256 * kPrefixEPT - 1) / (256 * kPrefixEPT);
+    if (grid64 > 0x7fffffff) return hipErrorInvalidValue;
+    if (first) k_hook_prefix<true><<<(int)grid64, 256, 0, s>>>(u, v, m, pi, n);
+    else k_hook_prefix<false><<<(int)grid64, 256, 0, s>>>(u, v, m, pi, n);
+    return hipGetLastError();
+}
+
 // ----------------------------------------------------------------------------- K-MJ
 // 256-vertex chunks per wave in k_mj and k_mj_bitmap (two measured the same as
 // one on R-MAT 24: the hoisted loads were what paid)
@@ -455,47 +535,57 @@ hipError_t launch_mj(int32_t* pi, int32_t n, const uint32_t* gate, bool coherent
 }
 
 // ----------------------------------------------------------------------------- giant sample
-// One workgroup.  Sample i reads edge entry floor(i * m / S) (evenly spread
-// over the list), takes the root of its first endpoint (pi is a forest of
-// stars, so that is pi[u]), and counts roots in an LDS hash table
-// (open addressing, 2*S slots).  The most frequent root is the giant label;
-// the filter is switched on when it holds at least 1/8 of the samples.
-constexpr int kSampleMax = 2048;
+// One workgroup, one sample per thread.  Sample i reads edge entry i * m / S
+// (evenly spread over the list), climbs to the root of its first endpoint, and
+// counts roots in an LDS hash table (open addressing, 2 * S slots).  The most
+// frequent root is the giant label; the filter is switched on when it holds
+// at least 1/8 of the samples.  `again`: nothing to do when it is on already.  Each
+// wave adds up its lanes with the first lane's root before it touches the
+// table (most samples have one root, and a wave's atomics on one slot are
+// served one by one).
+constexpr int kSamples = 1024;
 
-__global__ __launch_bounds__(1024) void k_sample(const int32_t* __restrict__ eu, int64_t m,
-                                                 const int32_t* pi, int32_t n, Ctrl* ctrl, int S) {
-    __shared__ int32_t keys[2 * kSampleMax];
-    __shared__ int32_t cnts[2 * kSampleMax];
-    __shared__ int32_t best_cnt[16];
-    __shared__ int32_t best_key[16];
-    constexpr int kSlots = 2 * kSampleMax;
-    for (int i = threadIdx.x; i < kSlots; i += blockDim.x) {
-        keys[i] = -1;
-        cnts[i] = 0;
-    }
+__global__ __launch_bounds__(kSamples) void k_sample(const int32_t* __restrict__ eu, int64_t m,
+                                                     double step, const int32_t* pi, int32_t n,
+                                                     Ctrl* ctrl, bool again) {
+    if (again && ctrl->filter_on) return;
+    constexpr int kSlots = 2 * kSamples;
+    __shared__ int32_t keys[kSlots];
+    __shared__ int32_t cnts[kSlots];
+    __shared__ int32_t best_cnt[kSamples / 64];
+    __shared__ int32_t best_key[kSamples / 64];
+    const int tid = threadIdx.x;
+    const int64_t e = (int64_t)((double)tid * step);
+    const int32_t x = eu[e < m ? e : m - 1];
+    keys[tid] = keys[tid + kSamples] = -1;
+    cnts[tid] = cnts[tid + kSamples] = 0;
+    int32_t r = -1;
+    if ((uint32_t)x < (uint32_t)n)
+        for (int32_t up = x; up != r;) {
+            r = up;
+            up = ld_rlx(pi + r);
+        }
     __syncthreads();
-    for (int i = threadIdx.x; i < S; i += blockDim.x) {
-        const int64_t e = (int64_t)i * m / S;
-        const int32_t x = eu[e];
-        if ((uint32_t)x >= (uint32_t)n) continue;
-        const int32_t r = ld_rlx(pi + x);
+    const int32_t first = __builtin_amdgcn_readfirstlane(r);
+    const uint64_t same = __ballot(r == first);
+    const bool leader = (tid & 63) == 0;
+    const int32_t weight = leader ? (int32_t)__popcll(same) : (r == first ? 0 : 1);
+    if (weight && r >= 0) {
         uint32_t slot = ((uint32_t)r * 2654435761u) & (kSlots - 1);
         for (int probe = 0; probe < kSlots; ++probe) {
             const int32_t k = atomicCAS(&keys[slot], -1, r);
             if (k == -1 || k == r) {
-                atomicAdd(&cnts[slot], 1);
+                atomicAdd(&cnts[slot], weight);
                 break;
             }
             slot = (slot + 1) & (kSlots - 1);
         }
     }
     __syncthreads();
-    int bc = -1, bk = -1;
-    for (int i = threadIdx.x; i < kSlots; i += blockDim.x) {
-        if (cnts[i] > bc) {
-            bc = cnts[i];
-            bk = keys[i];
-        }
+    int bc = cnts[tid], bk = keys[tid];
+    if (cnts[tid + kSamples] > bc) {
+        bc = cnts[tid + kSamples];
+        bk = keys[tid + kSamples];
     }
     // wave reduction (max count)
     for (int off = 32; off > 0; off >>= 1) {
@@ -506,21 +596,19 @@ __global__ __launch_bounds__(1024) void k_sample(const int32_t* __restrict__ eu,
             bk = ok;
         }
     }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        best_cnt[wave] = bc;
-        best_key[wave] = bk;
+    if (leader) {
+        best_cnt[tid >> 6] = bc;
+        best_key[tid >> 6] = bk;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int waves = (blockDim.x + 63) >> 6;
+    if (tid == 0) {
         int c = best_cnt[0], k = best_key[0];
-        for (int w = 1; w < waves; ++w)
+        for (int w = 1; w < kSamples / 64; ++w)
             if (best_cnt[w] > c) {
                 c = best_cnt[w];
                 k = best_key[w];
             }
-        const bool on = k >= 0 && c * 8 >= S;
+        const bool on = k >= 0 && c * 8 >= kSamples;
         ctrl->giant = on ? k : -1;
         ctrl->filter_on = on ? 1 : 0;
         ctrl->nofilter = on ? 0u : 1u;
@@ -528,10 +616,9 @@ __global__ __launch_bounds__(1024) void k_sample(const int32_t* __restrict__ eu,
 }
 
 hipError_t launch_sample_giant(const int32_t* u, int64_t m, const int32_t* pi, int32_t n,
-                               Ctrl* ctrl, int samples, hipStream_t s) {
-    if (samples > kSampleMax) samples = kSampleMax;
-    if (samples < 1 || m <= 0) return hipSuccess;
-    k_sample<<<1, 1024, 0, s>>>(u, m, pi, n, ctrl, samples);
+                               Ctrl* ctrl, hipStream_t s, bool again) {
+    if (m <= 0) return hipSuccess;
+    k_sample<<<1, kSamples, 0, s>>>(u, m, (double)m / kSamples, pi, n, ctrl, again);
     return hipGetLastError();
 }
 
@@ -995,6 +1082,114 @@ hipError_t launch_ahook_pairs(const int2* fr, const uint32_t* count, int64_t cap
     if (grid64 > grid_cap) grid64 = grid_cap;
     if (halve) k_ahook_pairs<EPT, true><<<(int)grid64, 256, 0, s>>>(fr, count, cap, pi);
     else k_ahook_pairs<EPT, false><<<(int)grid64, 256, 0, s>>>(fr, count, cap, pi);
+    return hipGetLastError();
+}
+
+// ----------------------------------------------------------------------------- contracting hook
+// Atomic-Hook of entries [begin, end) after rounds that have left few roots
+// (pi a forest of stars).  When thousands of entries join two dozen roots,
+// hooking each entry by itself is bound by the compare-and-swaps on those few
+// words (20-40 ns each on one word: 300,000 active entries over 24 roots took
+// 490 us).  Each workgroup first joins the roots of its own entries in LDS
+// (a hash table from root to slot, and Atomic-Hook over the slots in the
+// order of the roots' ids), and only the slots that lost their root status
+// there are hooked in device memory: at most one compare-and-swap per root and
+// workgroup.  A workgroup with few active entries hooks them directly.
+constexpr int kContractThreads = 1024;
+constexpr int kContractEPT = 2;
+constexpr int kContractSlots = 8192;  // at most 4,096 distinct roots per workgroup
+constexpr int kContractDirect = 128;  // active entries that are hooked directly
+
+// The slot of `key`.  A look at the slot first: with few distinct roots nearly
+// every lane finds its key there, and the atomic of a wave on one LDS word is
+// served lane by lane.
+__device__ __forceinline__ uint32_t contract_slot(int32_t* keys, int32_t key) {
+    uint32_t s = ((uint32_t)key * 2654435761u) >> 19;  // 13 bits
+    while (true) {
+        int32_t k = __hip_atomic_load(keys + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (k == -1) k = atomicCAS(&keys[s], -1, key);
+        if (k == -1 || k == key) return s;
+        s = (s + 1) & (kContractSlots - 1);
+    }
+}
+
+__global__ __launch_bounds__(kContractThreads) void k_hook_contract(
+    const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t begin, int64_t end,
+    int32_t* pi, int32_t n, Ctrl* ctrl) {
+    __shared__ int32_t keys[kContractSlots];
+    __shared__ uint32_t par[kContractSlots];
+    const int tid = threadIdx.x;
+    const int64_t t0 = begin + (int64_t)blockIdx.x * (kContractThreads * kContractEPT) + tid;
+    int32_t a[kContractEPT], b[kContractEPT];
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < kContractEPT; ++j) {
+        const int64_t e = t0 + j * kContractThreads;
+        a[j] = e < end ? __builtin_nontemporal_load(eu + e) : 0;
+        b[j] = e < end ? __builtin_nontemporal_load(ev + e) : 0;
+        if (max((uint32_t)a[j], (uint32_t)b[j]) >= (uint32_t)n) {
+            bad = true;
+            a[j] = b[j] = 0;
+        }
+    }
+    if (bad) atomicOr(&ctrl->status, kStatusRange);
+    int active = 0;
+#pragma unroll
+    for (int j = 0; j < kContractEPT; ++j) {
+        a[j] = ld_rlx(pi + a[j]);
+        b[j] = ld_rlx(pi + b[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kContractEPT; ++j) active += __syncthreads_count(a[j] != b[j]);
+    if (active <= kContractDirect) {
+#pragma unroll
+        for (int j = 0; j < kContractEPT; ++j) atomic_hook<false, true>(pi, a[j], b[j]);
+        return;
+    }
+    for (int i = tid; i < kContractSlots; i += kContractThreads) {
+        keys[i] = -1;
+        par[i] = i;
+    }
+    __syncthreads();
+    uint32_t sa[kContractEPT], sb[kContractEPT];
+#pragma unroll
+    for (int j = 0; j < kContractEPT; ++j) {
+        sa[j] = sb[j] = 0;
+        if (a[j] != b[j]) {
+            sa[j] = contract_slot(keys, a[j]);
+            sb[j] = contract_slot(keys, b[j]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kContractEPT; ++j) {
+        uint32_t x = sa[j], y = sb[j];
+        while (x != y) {
+            const bool up = keys[x] > keys[y];
+            const uint32_t H = up ? x : y, L = up ? y : x;
+            uint32_t found = __hip_atomic_load(par + H, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (found == H) found = atomicCAS(&par[H], H, L);
+            if (found == H) break;
+            x = __hip_atomic_load(par + found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            y = __hip_atomic_load(par + L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < kContractSlots; i += kContractThreads) {
+        uint32_t r = par[i];
+        if (r == (uint32_t)i) continue;
+        while (par[r] != r) r = par[r];
+        atomic_hook<false, true>(pi, keys[i], keys[r]);
+    }
+}
+
+hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                                int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s) {
+    if (end <= begin) return hipSuccess;
+    const int64_t tile = kContractThreads * kContractEPT;
+    const int64_t grid64 = (end - begin + tile - 1) / tile;
+    if (grid64 > 0x7fffffff) return hipErrorInvalidValue;
+    k_hook_contract<<<(int)grid64, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl);
     return hipGetLastError();
 }
 

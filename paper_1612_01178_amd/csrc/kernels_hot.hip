@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_hot_values(const uint32_t* __restrict__
 // entries spread evenly over the list.  Endpoints x < n with tag
 // x / kVertSets < kVertTagNone are candidates; bucket(x) is the range of
 // kVBucketSets sets that holds set x mod kVertSets.
-//   k_vsample  workgroup g takes kVRunsPerPart runs, histograms its
+//   k_vsample  workgroup g takes its part of the runs, histograms its
 //              candidates by bucket in LDS, scans, and writes them grouped by
 //              bucket into its own part of `region`, with the per-bucket
 //              counts and offsets (cnt, off: [part][bucket]).
@@ -128,26 +128,26 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t pair, uint32_t* wsum) {
     return base + incl - pair;
 }
 
-constexpr int kVPerThread = kVRunsPerPart * 64 / 256;  // sampled entries per thread
-
+template <int RUNS>  // of one part
 __global__ __launch_bounds__(256) void k_vsample(const int32_t* __restrict__ eu,
                                                  const int32_t* __restrict__ ev, int64_t m,
                                                  int32_t n, int64_t runs, double step,
                                                  uint32_t* __restrict__ region,
                                                  uint32_t* __restrict__ cnt,
                                                  uint32_t* __restrict__ off) {
+    constexpr int kVPerThread = RUNS * 64 / 256;  // sampled entries per thread
     constexpr int kPer = (kVBuckets + 255) / 256;  // buckets per thread in the scan
     __shared__ uint32_t hist[256 * kPer];
     __shared__ uint32_t cur[256 * kPer];
     __shared__ uint32_t wsum[4];
-    __shared__ uint32_t stage[kVPartCap];  // the part, grouped by bucket
+    __shared__ uint32_t stage[RUNS * 64 * 2];  // the part, grouped by bucket
     const int g = blockIdx.x;
     const int tid = threadIdx.x;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) hist[kPer * tid + q] = 0;
     // this thread's samples, all loads issued before any is used
-    const int64_t s0 = (int64_t)g * kVRunsPerPart * 64;
-    const int64_t s1 = min(runs, (int64_t)(g + 1) * kVRunsPerPart) * 64;
+    const int64_t s0 = (int64_t)g * RUNS * 64;
+    const int64_t s1 = min(runs, (int64_t)(g + 1) * RUNS) * 64;
     uint32_t x[kVPerThread], y[kVPerThread];
 #pragma unroll
     for (int i = 0; i < kVPerThread; ++i) {
@@ -292,23 +292,8 @@ __global__ __launch_bounds__(256) void k_vselect(const uint32_t* __restrict__ re
     if (part == 0) {
         tags[2 * s] = (uint8_t)k1;
         tags[2 * s + 1] = (uint8_t)k2;
+        tags[kVertSlots + 2 * s] = tags[kVertSlots + 2 * s + 1] = 0;  // member flags
     }
-}
-
-// Member flag of every slot from the bitmap (0 for an empty slot); no-op
-// unless ctrl->filter_on.
-__global__ __launch_bounds__(256) void k_hot_vvalues(const uint32_t* __restrict__ bits,
-                                                     uint8_t* __restrict__ vtab, const Ctrl* ctrl) {
-    if (!ctrl->filter_on) return;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= kVertSlots) return;
-    const uint32_t k = vtab[t];
-    uint8_t f = 0;
-    if (k < kVertTagNone) {
-        const int64_t v = (int64_t)k * kVertSets + t / kVertWays;
-        f = (uint8_t)(bits[v >> 5] >> (v & 31) & 1u);
-    }
-    vtab[kVertSlots + t] = f;
 }
 
 template <int EPT>
@@ -348,53 +333,6 @@ __device__ __forceinline__ void hot_climb(int32_t* pi, int32_t pu, int32_t pv, b
         pv = ld_tree<false>(pi + L);
         if (halve && pu != found && step++ % kHalveEveryFiltered == 0)
             halve_to(pi + H, pu);  // path halving
-    }
-}
-
-// K climbs of hot_climb advanced together (a finished one has pu == pv):
-// each step issues all their loads, then all their compare-and-swaps, then
-// all their reloads, so a thread keeps K dependent chains of tree accesses in
-// flight instead of one.  Every step of each climb is the step hot_climb
-// takes, except that a climb whose bit is set in `root` starts at the
-// compare-and-swap: the larger of its two starting values is an endpoint
-// that was its own parent when its parent was gathered, so the load that
-// would check that it is a root is skipped (if it no longer is one, the
-// compare-and-swap fails and returns its parent, the value the load would
-// have read, and the climb goes on from there as after that load).
-template <int K>
-__device__ __forceinline__ void hot_climb_k(int32_t* pi, int32_t* pu, int32_t* pv, bool halve,
-                                            uint32_t root) {
-    uint32_t step[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) step[k] = 0;
-    while (true) {
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < K; ++k) any |= pu[k] != pv[k];
-        if (!any) break;
-        int32_t H[K], L[K], f[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            H[k] = pu[k] > pv[k] ? pu[k] : pv[k];
-            L[k] = pu[k] > pv[k] ? pv[k] : pu[k];
-            f[k] = pu[k] != pv[k] && !(root >> k & 1) ? ld_tree<false>(pi + H[k]) : H[k];
-        }
-        root = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (pu[k] != pv[k] && f[k] == H[k]) f[k] = cas_root(pi + H[k], H[k], L[k]);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (pu[k] == pv[k]) continue;
-            if (f[k] == H[k]) {
-                pu[k] = pv[k] = L[k];  // hooked
-            } else {
-                pu[k] = ld_tree<false>(pi + f[k]);
-                pv[k] = ld_tree<false>(pi + L[k]);
-                if (halve && pu[k] != f[k] && step[k]++ % kHalveEveryFiltered == 0)
-                    halve_to(pi + H[k], pu[k]);
-            }
-        }
     }
 }
 
@@ -492,62 +430,142 @@ hipError_t launch_hot_values(const uint32_t* bits, const uint32_t* tags, uint32_
     return hipGetLastError();
 }
 
-// Filtered Atomic-Hook with the vertex table in LDS (loaded once per
-// workgroup, a slot's tag kept only while its member flag is set).  A test of
-// vertex x is answered with 1 in LDS when set x mod kVertSets holds the tag
-// x / kVertSets, else from the bitmap.
+// ----------------------------------------------------------------------------- filtered hook
+// Number of set bits of `mask` in lanes below this one.
+__device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// A wave's pending entries, one per lane in lanes 0 .. count - 1.  The
+// entries a filtered launch keeps are a few per wave and step, and hooking
+// them where they are found costs the whole wave their chain of dependent
+// tree accesses (2-4 us) for a few lanes' work, at every step.  Here they
+// move to the next free lanes (one ds_permute per word; every call is a
+// permutation of the 64 lanes, so no two lanes write one slot) and are
+// hooked 64 at a time.  Held in registers: the LDS belongs to the table.
+// All calls are made by whole waves.
+struct PairQueue {
+    int32_t a = 0, b = 0;
+    uint32_t count = 0;  // uniform
+
+    static __device__ __forceinline__ void hook_entry(int32_t x, int32_t y, int32_t* pi, bool halve) {
+        if (halve) hook_pair<true>(pi, x, y, kHalveEveryFiltered);
+        else hook_pair<false>(pi, x, y, kHalveEveryFiltered);
+    }
+
+    __device__ __forceinline__ void push(bool on, int32_t x, int32_t y, int32_t* pi, bool halve) {
+        const uint64_t mask = __ballot(on);
+        if (mask == 0) return;
+        const uint32_t added = (uint32_t)__popcll(mask);
+        const uint32_t rank = lane_prefix(mask);
+        const uint32_t lane = threadIdx.x & 63;
+        const uint32_t to = (on ? count + rank : count + added + (lane - rank)) & 63;
+        const int32_t nx = __builtin_amdgcn_ds_permute((int)(to << 2), x);
+        const int32_t ny = __builtin_amdgcn_ds_permute((int)(to << 2), y);
+        if (lane >= count && lane < count + added) {
+            a = nx;
+            b = ny;
+        }
+        count += added;
+        if (count < 64) return;
+        hook_entry(a, b, pi, halve);
+        count -= 64;
+        a = nx;  // lanes below count hold the entries that wrapped around
+        b = ny;
+    }
+    __device__ __forceinline__ void flush(int32_t* pi, bool halve) {
+        if ((threadIdx.x & 63) < count) hook_entry(a, b, pi, halve);
+        count = 0;
+    }
+};
+
+// Entries [t0, t0 + blockDim.x * EPT) of one edge array, 0 past `end`: groups
+// of four consecutive ones per lane, or single ones (EPT < 4).
 template <int EPT>
-__global__ __launch_bounds__(1024) void k_ahook_hotv(const int32_t* __restrict__ eu,
-                                                     const int32_t* __restrict__ ev, int64_t begin,
-                                                     int64_t end, bool vec, int32_t* pi, int32_t n,
-                                                     Ctrl* ctrl, const uint32_t* __restrict__ bits,
-                                                     const uint8_t* __restrict__ gtab, bool halve,
-                                                     bool sym) {
-    __shared__ uint32_t ltab[kVertSlots / 4];
+__device__ __forceinline__ void load_step(const int32_t* __restrict__ p, int64_t t0, int64_t end,
+                                          bool vec, int32_t (&x)[EPT]) {
+    if constexpr (EPT >= 4) {
+        load_tile<EPT>(p, t0 + (int64_t)threadIdx.x * 4, (int64_t)blockDim.x * 4, end, vec, x);
+    } else {
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) {
+            const int64_t e = t0 + (int64_t)j * blockDim.x + threadIdx.x;
+            x[j] = e < end ? __builtin_nontemporal_load(p + e) : 0;
+        }
+    }
+}
+
+// Filtered Atomic-Hook of entries [begin, end), persistent.  A membership
+// test is answered in LDS:
+//   kFilterBits    the whole giant bitmap (n <= kLdsBitsMaxN).  The pass is
+//                  then bound by the edge stream and by the climbs of the
+//                  entries it keeps (R-MAT 20, 2^24 entries: 413 us with the
+//                  vertex table and climbs in place, 194 us);
+//   kFilterVertex  the vertex table (a slot's tag kept only while its member
+//                  flag is set): 1 when set x mod kVertSets holds the tag
+//                  x / kVertSets, else the bitmap in device memory decides.
+//                  Bound by the L2 rate of those tests (R-MAT 24 3.46 ms with
+//                  the kept entries hooked in place, 3.16 with the queue;
+//                  R-MAT 21 616 and 544 us).
+enum { kFilterBits = 0, kFilterVertex = 1 };
+
+template <int EPT, int MODE>
+__global__ __launch_bounds__(1024) void k_filter(const int32_t* __restrict__ eu,
+                                                 const int32_t* __restrict__ ev, int64_t begin,
+                                                 int64_t end, bool vec, int32_t* pi, int32_t n,
+                                                 Ctrl* ctrl, const uint32_t* __restrict__ bits,
+                                                 const uint8_t* __restrict__ gtab, bool halve,
+                                                 bool sym) {
+    extern __shared__ uint32_t lds[];
     const bool filter = ctrl->filter_on != 0;
     const int32_t g = ctrl->giant;
     if (filter) {
-        // tag | 0xff per byte whose member flag (0 or 1) is 0: bytes of
-        // (0x01010101 - flags) are 1 - flag, times 0xff without carries
-        const v4i* tg = reinterpret_cast<const v4i*>(gtab);
-        const v4i* fl = reinterpret_cast<const v4i*>(gtab + kVertSlots);
-        v4i* dst = reinterpret_cast<v4i*>(ltab);
-        for (uint32_t i = threadIdx.x; i < (uint32_t)(kVertSlots / 16); i += blockDim.x) {
-            const v4i t = tg[i], f = fl[i];
-            v4i o;
-            o.x = (int32_t)((uint32_t)t.x | (0x01010101u - (uint32_t)f.x) * 0xffu);
-            o.y = (int32_t)((uint32_t)t.y | (0x01010101u - (uint32_t)f.y) * 0xffu);
-            o.z = (int32_t)((uint32_t)t.z | (0x01010101u - (uint32_t)f.z) * 0xffu);
-            o.w = (int32_t)((uint32_t)t.w | (0x01010101u - (uint32_t)f.w) * 0xffu);
-            dst[i] = o;
+        if (MODE == kFilterBits) {
+            const uint32_t words = ((uint32_t)n + 31) / 32;
+            for (uint32_t i = threadIdx.x * 4; i < words; i += blockDim.x * 4) {
+                if (i + 3 < words) {
+                    *reinterpret_cast<v4i*>(lds + i) = *reinterpret_cast<const v4i*>(bits + i);
+                } else {
+                    for (uint32_t k = i; k < words; ++k) lds[k] = bits[k];
+                }
+            }
+        } else {
+            // tag | 0xff per byte whose member flag (0 or 1) is 0: bytes of
+            // (0x01010101 - flags) are 1 - flag, times 0xff without carries
+            const v4i* tg = reinterpret_cast<const v4i*>(gtab);
+            const v4i* fl = reinterpret_cast<const v4i*>(gtab + kVertSlots);
+            v4i* dst = reinterpret_cast<v4i*>(lds);
+            for (uint32_t i = threadIdx.x; i < (uint32_t)(kVertSlots / 16); i += blockDim.x) {
+                const v4i t = tg[i], f = fl[i];
+                v4i o;
+                o.x = (int32_t)((uint32_t)t.x | (0x01010101u - (uint32_t)f.x) * 0xffu);
+                o.y = (int32_t)((uint32_t)t.y | (0x01010101u - (uint32_t)f.y) * 0xffu);
+                o.z = (int32_t)((uint32_t)t.z | (0x01010101u - (uint32_t)f.z) * 0xffu);
+                o.w = (int32_t)((uint32_t)t.w | (0x01010101u - (uint32_t)f.w) * 0xffu);
+                dst[i] = o;
+            }
         }
         __syncthreads();
     }
-    const uint16_t* lset = reinterpret_cast<const uint16_t*>(ltab);
-    const int64_t stride = (int64_t)blockDim.x * 4;
+    const uint16_t* lset = reinterpret_cast<const uint16_t*>(lds);
     const int64_t tile = (int64_t)blockDim.x * EPT;
     bool bad = false;
+    PairQueue q;
     for (int64_t t0 = begin + (int64_t)blockIdx.x * tile; t0 < end; t0 += (int64_t)gridDim.x * tile) {
-        const int64_t e0 = t0 + (int64_t)threadIdx.x * 4;
         int32_t a[EPT], b[EPT];
-        load_tile<EPT>(eu, e0, stride, end, vec, a);
-        load_tile<EPT>(ev, e0, stride, end, vec, b);
-        uint32_t act = 0;
+        load_step<EPT>(eu, t0, end, vec, a);
+        load_step<EPT>(ev, t0, end, vec, b);
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
-            const bool in = (uint32_t)a[j] < (uint32_t)n && (uint32_t)b[j] < (uint32_t)n;
+            const uint32_t xa = (uint32_t)a[j], xb = (uint32_t)b[j];
+            const bool in = max(xa, xb) < (uint32_t)n;
             bad |= !in;
-            if (in && a[j] != b[j] && !(sym && a[j] > b[j])) act |= 1u << j;
-        }
-        int32_t pa[EPT], pb[EPT];
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            if (!(act >> j & 1)) continue;
             uint32_t ba = 0, bb = 0;
-            if (filter) {
-                const uint32_t xa = (uint32_t)a[j], xb = (uint32_t)b[j];
-                // a tag of kVertTagNone or more never matches a stored byte's
-                // tag (stored tags are below it or mark an empty slot)
+            if (filter && MODE == kFilterBits) {
+                ba = lds[in ? xa >> 5 : 0u] >> (xa & 31) & 1;
+                bb = lds[in ? xb >> 5 : 0u] >> (xb & 31) & 1;
+            } else if (filter && in) {
                 // a tag of kVertTagNone (the empty marker) or more never hits
                 const uint32_t sa = lset[xa % kVertSets], sb = lset[xb % kVertSets];
                 const uint32_t ka = xa / kVertSets, kb = xb / kVertSets;
@@ -559,37 +577,12 @@ __global__ __launch_bounds__(1024) void k_ahook_hotv(const int32_t* __restrict__
                 ba = worda & 1;
                 bb = wordb & 1;
             }
-            if (ba & bb) {
-                act &= ~(1u << j);
-            } else {
-                pa[j] = ba ? g : ld_tree<false>(pi + a[j]);
-                pb[j] = bb ? g : ld_tree<false>(pi + b[j]);
-            }
-        }
-        // the kept entries' climbs, kClimbs at a time (entries j, j + EPT /
-        // kClimbs, ...; an entry not kept takes part as a finished climb)
-        constexpr int kClimbs = 2;
-#pragma unroll
-        for (int j = 0; j < EPT / kClimbs; ++j) {
-            int32_t cu[kClimbs], cv[kClimbs];
-            bool anyk = false;
-            // bit k of root: the larger start of climb k is an endpoint that
-            // was its own parent (a wrong bit would only cost a failed CAS)
-            uint32_t root = 0;
-#pragma unroll
-            for (int k = 0; k < kClimbs; ++k) {
-                const int e = j + k * (EPT / kClimbs);
-                const bool on = act >> e & 1;
-                cu[k] = on ? pa[e] : 0;
-                cv[k] = on ? pb[e] : 0;
-                anyk |= on;
-                const bool ra = cu[k] > cv[k] && cu[k] == a[e];
-                const bool rb = cv[k] > cu[k] && cv[k] == b[e];
-                root |= (uint32_t)(ra || rb) << k;
-            }
-            if (anyk) hot_climb_k<kClimbs>(pi, cu, cv, halve, root);
+            const bool keep = in && xa != xb && !(ba & bb) && !(sym && a[j] > b[j]);
+            // an endpoint in the giant starts its climb at the giant's root
+            q.push(keep, ba ? g : a[j], bb ? g : b[j], pi, halve);
         }
     }
+    q.flush(pi, halve);
     if (bad) atomicOr(&ctrl->status, kStatusRange);
 }
 
@@ -598,33 +591,75 @@ hipError_t launch_hot_vprepare(const int32_t* u, const int32_t* v, int64_t m, in
     uint32_t* region = scratch;
     uint32_t* cnt = region + (int64_t)kVPartsMax * kVPartCap;
     uint32_t* off = cnt + kVPartsMax * kVBuckets;
-    const int64_t runs = m >= 64 ? std::min<int64_t>(kVertRuns, m / 64) : 0;
-    const int parts = (int)((runs + kVRunsPerPart - 1) / kVRunsPerPart);
+    // one run of 64 in 8,192 entries, at most kVertRuns (R-MAT 21, 50 M
+    // entries: selection 59 us with 2^15 runs, 24 us with 6,144)
+    const int64_t want = std::max<int64_t>(64, std::min<int64_t>(kVertRuns, m / 8192));
+    const int64_t runs = m >= 64 ? std::min<int64_t>(want, m / 64) : 0;
+    const bool few = runs <= (int64_t)kVPartsMax * kVRunsPerPartShort;
+    const int per = few ? kVRunsPerPartShort : kVRunsPerPart;
+    const int parts = (int)((runs + per - 1) / per);
     const double step = runs > 0 ? (double)(m - 64) / (double)runs : 0.0;
-    if (parts > 0) k_vsample<<<parts, 256, 0, s>>>(u, v, m, n, runs, step, region, cnt, off);
+    if (parts > 0 && few)
+        k_vsample<kVRunsPerPartShort><<<parts, 256, 0, s>>>(u, v, m, n, runs, step, region, cnt, off);
+    else if (parts > 0)
+        k_vsample<kVRunsPerPart><<<parts, 256, 0, s>>>(u, v, m, n, runs, step, region, cnt, off);
     k_vselect<<<kVBuckets, 256, 0, s>>>(region, cnt, off, parts, n, table);  // tags
     return hipGetLastError();
 }
 
-hipError_t launch_hot_vvalues(const uint32_t* bits, uint8_t* table, const Ctrl* ctrl, hipStream_t s) {
-    k_hot_vvalues<<<kVertSlots / 256, 256, 0, s>>>(bits, table, ctrl);
+template <int MODE>
+static hipError_t filter_dispatch(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                                  int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits,
+                                  const uint8_t* table, bool halve, bool sym, hipStream_t s) {
+    if (end <= begin) return hipSuccess;
+    static hipError_t once = [] {
+        const void* fn[] = {reinterpret_cast<const void*>(&k_filter<1, MODE>),
+                            reinterpret_cast<const void*>(&k_filter<2, MODE>),
+                            reinterpret_cast<const void*>(&k_filter<4, MODE>),
+                            reinterpret_cast<const void*>(&k_filter<8, MODE>)};
+        for (const void* f : fn) {
+            const hipError_t e =
+                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (once != hipSuccess) return once;
+    const int block = 1024;
+    const size_t lds = MODE == kFilterBits ? ((size_t)n + 127) / 128 * 16 : (size_t)kVertSlots;
+    if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
+    // workgroups that are resident at once: two per CU where the LDS allows
+    const int64_t cap = (int64_t)device_cu_count() * (2 * lds <= (size_t)kLdsBytes ? 2 : 1);
+    // 8 entries per thread; with the bitmap in LDS fewer where that leaves
+    // CUs without a tile: a short segment is bound by the chain of climbs of
+    // each wave (R-MAT 18, 2^19 entries: 42 us at 8 entries, 64 CUs).  On the
+    // larger graphs of the vertex table the first segments' climbs contend for
+    // the hubs, and more of them at once are slower (R-MAT 23, 2^20 entries:
+    // 91 us at 2 entries, 256 CUs, 47 us at 8, 128 CUs).
+    int ept = 8;
+    while (MODE == kFilterBits && ept > 1 && end - begin < cap * block * ept) ept /= 2;
+    const int64_t tiles = (end - begin + (int64_t)block * ept - 1) / ((int64_t)block * ept);
+    const int grid = (int)std::min<int64_t>(tiles, cap);
+    const bool vec = (((uintptr_t)(u + begin) | (uintptr_t)(v + begin)) & 15) == 0;
+    switch (ept) {
+        case 1: k_filter<1, MODE><<<grid, block, lds, s>>>(u, v, begin, end, vec, pi, n, ctrl, bits, table, halve, sym); break;
+        case 2: k_filter<2, MODE><<<grid, block, lds, s>>>(u, v, begin, end, vec, pi, n, ctrl, bits, table, halve, sym); break;
+        case 4: k_filter<4, MODE><<<grid, block, lds, s>>>(u, v, begin, end, vec, pi, n, ctrl, bits, table, halve, sym); break;
+        default: k_filter<8, MODE><<<grid, block, lds, s>>>(u, v, begin, end, vec, pi, n, ctrl, bits, table, halve, sym); break;
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_ahook_hotv(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
-                             int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits,
-                             const uint8_t* table, bool halve, bool sym, hipStream_t s) {
-    if (end <= begin) return hipSuccess;
-    constexpr int EPT = 8;
-    const int block = 1024;
-    const int64_t tile = (int64_t)block * EPT;
-    const int64_t tiles = (end - begin + tile - 1) / tile;
-    const int64_t cap = (int64_t)device_cu_count();  // one 1024-thread workgroup per CU (LDS)
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, cap));
-    const bool vec = (((uintptr_t)(u + begin) | (uintptr_t)(v + begin)) & 15) == 0;
-    k_ahook_hotv<EPT><<<grid, block, 0, s>>>(u, v, begin, end, vec, pi, n, ctrl, bits, table, halve,
-                                             sym);
-    return hipGetLastError();
+hipError_t launch_filter_bits(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                              int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, bool halve,
+                              bool sym, hipStream_t s) {
+    return filter_dispatch<kFilterBits>(u, v, begin, end, pi, n, ctrl, bits, nullptr, halve, sym, s);
+}
+
+hipError_t launch_filter_vertex(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
+                                int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits,
+                                const uint8_t* table, bool halve, bool sym, hipStream_t s) {
+    return filter_dispatch<kFilterVertex>(u, v, begin, end, pi, n, ctrl, bits, table, halve, sym, s);
 }
 
 template <int SLOTS, typename TagT>

@@ -109,3 +109,61 @@ def test_batches_by_rule(dev, count, lo, hi):
         with pytest.raises(cc.CCError) as ei:
             cc.labels_batch_device(put(v, dev), dv, dvo, deo, hi - 1, out)
         assert ei.value.code == cc.CC_ERR_ARG
+
+
+# (scale, entries, both orientations): the filtered plan at the first list it
+# takes, with rounds over a prefix and without, the bitmap in LDS at one and
+# two workgroups per CU, a ragged end; the largest bitmap in LDS and the first
+# size with the vertex table are below
+@pytest.mark.parametrize("scale,m,sym", [(10, 1 << 21, False), (17, (1 << 21) + 5, False),
+                                         (19, 1 << 21, True), (20, (1 << 23) + 3, False)])
+def test_filtered_plan(dev, scale, m, sym):
+    u, v, n = graphgen.rmat(scale, 0, seed=scale + m, m=m, symmetrize=sym)
+    want = oracle.labels(u, v, n)
+    for offset in (0, 3):
+        du, dv = put(u, dev, offset), put(v, dev, offset)
+        for opt in (cc.Options(), cc.Options(path_halving="off"), cc.Options(hook="atomic", filter="giant"),
+                    cc.Options(hook="atomic", filter="giant", hot_cache="vertex"),
+                    cc.Options(symmetric=True) if sym else cc.Options(no_sync=True)):
+            print("filtered", scale, m, offset, opt, flush=True)
+            out = torch.full((n,), -7, dtype=torch.int32, device=dev)
+            cc.labels(du, dv, n, out=out, options=opt)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want), opt
+    for at in (0, m // 2, len(u) - 1):
+        keep, u[at] = u[at], n
+        with pytest.raises(cc.CCError) as ei:
+            cc.labels(put(u, dev), dv, n)
+        assert ei.value.code == cc.CC_ERR_RANGE
+        u[at] = keep
+
+
+@pytest.mark.parametrize("n", [160 * 1024 * 8 - 31, 160 * 1024 * 8, 160 * 1024 * 8 + 1])
+def test_filtered_plan_at_the_lds_bitmap_limit(dev, n):
+    """Half of the ids joined by a cycle and random chords, the rest in pairs
+    or alone: a giant component whose bitmap ends in a partial word."""
+    rng = np.random.default_rng(n)
+    ids = rng.permutation(n).astype(np.int32)
+    half, pairs = ids[: n // 2], ids[n // 2: n // 2 + 2 * (n // 8)]
+    m = 8 * n + 1
+    u = half[rng.integers(0, len(half), m)]
+    v = half[rng.integers(0, len(half), m)]
+    at = rng.choice(m, n // 8, replace=False)
+    u[at], v[at] = pairs[0::2], pairs[1::2]
+    want = oracle.labels(u, v, n)
+    lab, st = cc.labels(put(u, dev), put(v, dev), n, return_stats=True)
+    assert st["filter_used"] == 1
+    assert np.array_equal(lab.cpu().numpy(), want)
+
+
+def test_filtered_plan_without_a_giant(dev):
+    """2,000 components of 100 vertices, their entries shuffled: no component
+    holds an eighth of the samples, so nothing is filtered."""
+    rng = np.random.default_rng(5)
+    n, m = 200000, 1 << 21
+    comp = rng.integers(0, 2000, m)
+    u = (comp * 100 + rng.integers(0, 100, m)).astype(np.int32)
+    v = (comp * 100 + rng.integers(0, 100, m)).astype(np.int32)
+    lab, st = cc.labels(put(u, dev), put(v, dev), n, return_stats=True)
+    assert st["hook"] == 1 and st["filter_used"] == 0
+    assert np.array_equal(lab.cpu().numpy(), oracle.labels(u, v, n))
