@@ -57,12 +57,33 @@ static_assert(sizeof(GraphDesc) == 40, "descriptor layout");
 // are relaxed atomics of WORKGROUP scope: ordinary cached accesses on gfx950
 // that hit in L1 / the XCD's L2 and may not yet see a value another XCD wrote
 // during the same kernel.  Kernel boundaries make every earlier write
-// visible.  Stores are workgroup scope too in kernels where no thread takes
+// visible, except where several workgroups stored to one word: see settling
+// below.  Stores are workgroup scope too in kernels where no thread takes
 // a root by CAS (Multi-Jump, the atomic-free Hook).  In a kernel that hooks
 // by CAS, every write is AGENT scope: the CAS itself and the path-halving
-// store (halve_to).  COH = true makes the loads and stores agent scope as
-// well (coherent across XCDs, served beyond the per-XCD L2); it is kept for
-// measurement.
+// store (halve_to).
+//
+// Settling.  Two workgroup-scope stores to one word by workgroups on
+// different XCDs leave a different value in each XCD's L2, and the difference
+// outlives the kernel: later kernels read one value or the other by where they
+// run (uniform n = m = 2^20, a second atomic-free Hook round: about 1,200
+// words read differently by workgroups on different XCDs, after a stream
+// synchronisation and through several kernels; none with agent-scope
+// stores, none where each word has one writer).  Each value alone is a valid
+// parent, but a vertex's tree then depends on who asks, and an entry found
+// satisfied on one XCD can be unsatisfied on another: labels came out split
+// (uniform n = 2^20, m = 3 * 2^20: most solves).  So a pass of racing
+// workgroup-scope stores (the atomic-free Hook) is followed by a Multi-Jump
+// that stores every vertex's root, also where it is the parent already: each
+// word then has one writer, whose store supersedes every copy, and only
+// passes after it decide which entries are satisfied.  It may itself follow
+// different parents for different vertices of a star and so split it; the
+// entries inside are then found unsatisfied by the next pass, with one view.
+// Agent-scope stores need no settling, but where many of them meet on one
+// word (hubs) they are served one by one (R-MAT 18: 577 against 19 us).
+//
+// COH = true makes the loads and stores agent scope as well (coherent across
+// XCDs, served beyond the per-XCD L2); it is kept for measurement.
 template <bool COH>
 __device__ __forceinline__ int32_t ld_tree(const int32_t* p) {
     if (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -615,7 +615,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
                 TIMED(kPhaseHook, launch_hook_prefix(u, v, prefix, pi, n, i == 0, s));
             else
                 TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, s));
-            TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s));
+            TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s, i < kPrefixRounds));
             ++hooks;
             ++jumps;
         }
@@ -716,7 +716,7 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     const int grid_cap = device_cu_count() * 8;
     TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     // the atomic-free round, each workgroup's chunk joined in an LDS window
-    TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, s));
+    TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, (uint32_t)(m / 8), s));
     // The compaction compares parents, not roots.  An entry whose endpoints
     // have equal parents is inside one tree and is dropped; one whose parents
     // differ is kept (also when they share a root), and the Atomic-Hook climbs
@@ -728,11 +728,11 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     // hooked outside the windows (inputs without locality), the plain round's
     // chains would make most entries look active, and a Multi-Jump, gated on
     // the device by that count, makes the trees stars first.
-    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->win_far, s, (uint32_t)(m / 4)));
+    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->win_far, s, true, (uint32_t)(m / 8)));
     TIMED(kPhaseHook, launch_compact(1, u, v, m, F, F, L.cap, pi, n, ctrl, 0xffffffffu, p.block,
                                      p.ept, grid_cap, s));
     TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], L.cap, pi, p.halve, grid_cap, s));
-    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->count[1], s));
+    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->count[1], s, false));
     if (st) {
         st->hook_launches += 3;
         st->compress_launches += 2;
@@ -760,7 +760,7 @@ int32_t solve_plain(int32_t n, const int32_t* u, const int32_t* v, int64_t m, in
             if (r == 1)  // the round leaves chains
                 TIMED(kPhaseCompress, launch_mj_deep(pi, n, s));
             else
-                TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->count[(r - 1) & 1], s));
+                TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->count[(r - 1) & 1], s, true));
             TIMED(kPhaseHook, launch_compact((int)r, u, v, work, F0, F1, L.cap, pi, n, ctrl,
                                              p.tau, p.block, p.ept, grid_cap, s));
         }
@@ -824,7 +824,7 @@ int32_t solve_host_loop(int32_t n, const int32_t* u, const int32_t* v, int64_t m
         if (hctrl->status) break;
         const bool hooked = hctrl->hook_changed != 0;
         if (p.host_loop == CC_HOST_LOOP_MULTIJUMP) {
-            TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
+            TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s, true));
             ++jumps;
         } else {
             while (true) {
@@ -1220,7 +1220,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
                                              p.symmetric, s));
         TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], m, out, p.halve,
                                              device_cu_count() * 8, s));
-        TIMED(kPhaseCompress, launch_mj1(out, n, &ctrl->count[1], s));
+        TIMED(kPhaseCompress, launch_mj1(out, n, &ctrl->count[1], s, false));
         hooks = 3;
         jumps = 2;
     } else if (!filter) {

@@ -35,9 +35,10 @@ hipError_t launch_mj(int32_t* pi, int32_t n, const uint32_t* gate, bool coherent
 // vertices in LDS, then a climb across blocks (the plain Multi-Jump for
 // n < 2^22).  Postcondition as launch_mj: every tree is a star.
 hipError_t launch_mj_deep(int32_t* pi, int32_t n, hipStream_t s);
-// Multi-Jump with one vertex per thread (atomic-free path); does nothing when
-// `gate` is non-null and *gate <= limit.
-hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t s,
+// Multi-Jump with interleaved climbs (atomic-free path); does nothing when
+// `gate` is non-null and *gate <= limit.  `settle`: every vertex is stored
+// (after a pass of racing workgroup-scope stores); launch_mj_deep always does.
+hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t s, bool settle,
                       uint32_t limit = 0);
 
 // Giant-component sample: label of the component that holds the most of
@@ -71,7 +72,7 @@ hipError_t launch_hook_plain(int round, const int32_t* u, const int32_t* v, int6
 // LDS window of consecutive vertices (see kernels_batch.hip).  Range-checks
 // the entries.  Leaves pi a forest (not of stars).
 hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, hipStream_t s);
+                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s);
 // Atomic-Hook with path halving of the *count root pairs of a frontier.
 hipError_t launch_ahook_pairs(const int2* fr, const uint32_t* count, int64_t cap, int32_t* pi,
                               bool halve, int grid_cap, hipStream_t s);

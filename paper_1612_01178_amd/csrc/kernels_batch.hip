@@ -542,20 +542,19 @@ hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, co
 // chunk of a percolated 4096^2 lattice spans ~39,200 ids (within the
 // window), two workgroups fit a CU (80 KiB of LDS each), so the lattice's
 // 478 chunks run at once.
-constexpr int64_t kWinEntries = 49152;  // 1024 threads x 48 entries
-constexpr uint32_t kWinSlots = 40960;   // 16-bit local ids: 80 KiB of LDS
-constexpr int kWinSegments = 2;
 constexpr int kWinEPT = 4;  // entries per thread per step (registers: two workgroups per CU)
 
 __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict__ eu,
                                                       const int32_t* __restrict__ ev, int64_t m,
-                                                      int32_t* pi, int32_t n, Ctrl* ctrl) {
+                                                      int32_t* pi, int32_t n, Ctrl* ctrl,
+                                                      int32_t chunk, uint32_t slots,
+                                                      int32_t segments, uint32_t far_limit) {
     extern __shared__ uint16_t spi[];
-    __shared__ int32_t wave_min[16];
+    __shared__ int32_t wave_min[16], wave_max[16];
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t lane = tid & 63, wave = tid >> 6, waves = nthr >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * kWinEntries;
-    const int64_t c1 = min(m, c0 + kWinEntries);
+    const int64_t c0 = (int64_t)blockIdx.x * chunk;
+    const int64_t c1 = min(m, c0 + chunk);
     const int64_t step = (int64_t)nthr * kWinEPT;
     g_cint* gu = (g_cint*)eu;
     g_cint* gv = (g_cint*)ev;
@@ -563,27 +562,59 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     // the first segment's first entries are loaded before the LDS init, so
     // that their latency overlaps it; the window starts at the smallest
     // endpoint among the first blockDim.x of them
-    const int64_t first_end = c0 + (c1 - c0) / kWinSegments;
+    const int64_t first_end = c0 + (c1 - c0) / segments;
     edge_step_loads<kWinEPT>(gu, gv, c0, first_end, step, a, b);
     uint32_t* w32 = reinterpret_cast<uint32_t*>(spi);
-    for (uint32_t w = tid; w < kWinSlots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
-    int32_t lo = INT32_MAX;
+    for (uint32_t w = tid; w < slots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
+    int32_t lo = INT32_MAX, hi = 0;
     if (c0 + tid < first_end) {
-        if ((uint32_t)a[0] < (uint32_t)n) lo = min(lo, a[0]);
-        if ((uint32_t)b[0] < (uint32_t)n) lo = min(lo, b[0]);
+        if ((uint32_t)a[0] < (uint32_t)n) {
+            lo = min(lo, a[0]);
+            hi = max(hi, a[0]);
+        }
+        if ((uint32_t)b[0] < (uint32_t)n) {
+            lo = min(lo, b[0]);
+            hi = max(hi, b[0]);
+        }
     }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) lo = min(lo, __shfl_xor(lo, d, 64));
-    if (lane == 0) wave_min[wave] = lo;
+    for (int d = 32; d >= 1; d >>= 1) {
+        lo = min(lo, __shfl_xor(lo, d, 64));
+        hi = max(hi, __shfl_xor(hi, d, 64));
+    }
+    if (lane == 0) {
+        wave_min[wave] = lo;
+        wave_max[wave] = hi;
+    }
     __syncthreads();
-    int32_t base = wave_min[0];
-    for (uint32_t i = 1; i < waves; ++i) base = min(base, wave_min[i]);
+    int32_t base = wave_min[0], top = wave_max[0];
+    for (uint32_t i = 1; i < waves; ++i) {
+        base = min(base, wave_min[i]);
+        top = max(top, wave_max[i]);
+    }
     if (base == INT32_MAX) base = 0;
-    // window vertices: [base, base + span)
-    const uint32_t span = (uint32_t)min<int64_t>((int64_t)kWinSlots, (int64_t)n - base);
     bool bad = false;
+    // No locality: the chunk's first entries span more ids than the window
+    // holds.  The chunk is hooked in device memory; every endpoint still is
+    // its own parent or may be treated so (a stale value only loses a store).
+    if (top >= base && (uint32_t)(top - base) >= 4 * slots) {
+        for (int64_t sb = c0; sb < c1; sb += step) {
+            edge_step_loads<kWinEPT>(gu, gv, sb, c1, step, a, b);
+#pragma unroll
+            for (int j = 0; j < kWinEPT; ++j) {
+                const bool ok = max((uint32_t)a[j], (uint32_t)b[j]) < (uint32_t)n;
+                bad |= !ok;
+                if (ok && a[j] != b[j]) st_rlx(pi + max(a[j], b[j]), min(a[j], b[j]));
+            }
+        }
+        if (tid == 0) atomicMax(&ctrl->win_far, far_limit + 1);
+        if (bad) atomicOr(&ctrl->status, kStatusRange);
+        return;
+    }
+    // window vertices: [base, base + span)
+    const uint32_t span = (uint32_t)min<int64_t>((int64_t)slots, (int64_t)n - base);
     uint32_t far = 0;  // entries hooked outside the window
-    // The chunk in kWinSegments segments, each followed by a Multi-Jump over
+    // The chunk in `segments` segments, each followed by a Multi-Jump over
     // the window (the schedule of Fig. 4 inside the chunk) so that later
     // climbs start from stars.  kWinEPT entries per thread per step,
     // consecutive threads on consecutive entries (coalesced, through buffer
@@ -591,9 +622,9 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     // before this step's hooks.  An entry past the segment's end reads as
     // (0, 0); no branch surrounds the LDS hook, which is given (0, 0) -- a
     // no-op -- for every entry that is not inside the window.
-    for (int seg = 0; seg < kWinSegments; ++seg) {
-        const int64_t s0 = c0 + (c1 - c0) * seg / kWinSegments;
-        const int64_t s1 = c0 + (c1 - c0) * (seg + 1) / kWinSegments;
+    for (int seg = 0; seg < segments; ++seg) {
+        const int64_t s0 = c0 + (c1 - c0) * seg / segments;
+        const int64_t s1 = c0 + (c1 - c0) * (seg + 1) / segments;
         if (seg > 0) edge_step_loads<kWinEPT>(gu, gv, s0, s1, step, a, b);
         for (int64_t sb = s0; sb < s1; sb += step) {
             edge_step_loads<kWinEPT>(gu, gv, sb + step, s1, step, na, nb);
@@ -610,7 +641,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
                 if (in && ok && !win) {
                     ++far;
                     const int32_t pa = ld_rlx(pi + x), pb = ld_rlx(pi + y);
-                    if (pa != pb) st_rlx(pi + max(pa, pb), min(pa, pb));
+                    if (pa != pb) st_tree<true>(pi + max(pa, pb), min(pa, pb));
                 }
             }
 #pragma unroll
@@ -624,7 +655,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
         // and stores it once; after the last segment the local roots of the
         // non-roots go to pi
         // (two vertices per thread and pass, their climbs interleaved)
-        const bool last = seg + 1 == kWinSegments;
+        const bool last = seg + 1 == segments;
         for (uint32_t x = tid; x < span; x += 2 * nthr) {
             const uint32_t y = x + nthr;
             const bool has_y = y < span;
@@ -640,8 +671,8 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
                 lds_st(spi, x, p1);
                 if (has_y) lds_st(spi, y, p2);
             } else {
-                if (p1 != x) st_rlx(pi + base + (int32_t)x, base + (int32_t)p1);
-                if (has_y && p2 != y) st_rlx(pi + base + (int32_t)y, base + (int32_t)p2);
+                if (p1 != x) st_tree<true>(pi + base + (int32_t)x, base + (int32_t)p1);
+                if (has_y && p2 != y) st_tree<true>(pi + base + (int32_t)y, base + (int32_t)p2);
             }
         }
         __syncthreads();
@@ -649,21 +680,26 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     // the workgroup's count of entries hooked outside its window
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) far += __shfl_xor(far, d, 64);
-    if (lane == 0 && far) atomicAdd(&ctrl->win_far, far);
+    if (lane == 0 && far) atomicAdd(&ctrl->win_far, (far + 1) / 2);
     if (bad) atomicOr(&ctrl->status, kStatusRange);
 }
 
-hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, hipStream_t s) {
+constexpr uint32_t kWinSlotsMax = 65536;
+hipError_t launch_hook_window_p(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
+                              int32_t n, Ctrl* ctrl, int32_t chunk, uint32_t slots, int32_t segments, int block, uint32_t far_limit, hipStream_t s) {
     if (m <= 0) return hipSuccess;
     static hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hook_window),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kWinSlots * 2);
+                                                 kWinSlotsMax * 2);
     if (once != hipSuccess) return once;
-    const int64_t grid = (m + kWinEntries - 1) / kWinEntries;
+    const int64_t grid = (m + chunk - 1) / chunk;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    k_hook_window<<<(int)grid, 1024, kWinSlots * 2, s>>>(u, v, m, pi, n, ctrl);
+    k_hook_window<<<(int)grid, block, slots * 2, s>>>(u, v, m, pi, n, ctrl, chunk, slots, segments, far_limit);
     return hipGetLastError();
+}
+hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
+                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
+    return launch_hook_window_p(u, v, m, pi, n, ctrl, 49152, 40960, 2, 1024, far_limit, s);
 }
 
 hipError_t prepare_batch_lds() {

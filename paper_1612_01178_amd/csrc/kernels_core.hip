@@ -446,7 +446,11 @@ __global__ __launch_bounds__(1024, 8) void k_mj_local(int32_t* pi, int32_t n) {
 // ms; ER 2^16 rounds: 0.100 -> 0.090 ms); here a thread's V vertices climb
 // interleaved.  The Atomic-Hook path keeps k_mj, whose 16-byte loads win on
 // its shallow trees (R-MAT 24: 3.75 against 3.78 ms).
-template <int V>
+//
+// SETTLE: every vertex's root is stored, also where it is its parent already:
+// the form that must follow a pass in which several workgroups may store to
+// one slot with workgroup scope (see settling in common.hpp).
+template <int V, bool SETTLE>
 __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint32_t* gate,
                                              uint32_t limit) {
     if (gate != nullptr && *gate <= limit) return;
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
 #pragma unroll
         for (int k = 0; k < V; ++k) {
             const int64_t w = v + (int64_t)k * blockDim.x;
-            if (w < n && r[k] != q[k]) st_tree<false>(pi + w, r[k]);
+            if (w < n && (SETTLE || r[k] != q[k])) st_tree<false>(pi + w, r[k]);
         }
     }
 }
@@ -493,33 +497,34 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
 // least 8 workgroups (a 4096^2 grid's final Multi-Jump: 42 -> 35 us; eight
 // per thread no better), else two (ER 2^16: four leaves 64 workgroups).
 static hipError_t mj1_launch(int32_t* pi, int32_t n, const uint32_t* gate, uint32_t limit,
-                             bool capped, hipStream_t s) {
+                             bool settle, hipStream_t s) {
     const int64_t cus = device_cu_count();
     const int V = (int64_t)n >= 256 * 4 * 8 * cus ? 4 : 2;
     int64_t grid = ((int64_t)n + 256 * V - 1) / (256 * V);
-    if (capped) grid = std::min<int64_t>(grid, cus * 32);
-    if (V == 4)
-        k_mj1<4><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
-    else
-        k_mj1<2><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
+    // a gated launch may find nothing to do: a grid of at most 32 workgroups
+    // per CU, each thread striding over vertices, exits in a few microseconds
+    if (gate) grid = std::min<int64_t>(grid, cus * 32);
+    if (V == 4 && settle) k_mj1<4, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
+    else if (V == 4) k_mj1<4, false><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
+    else if (settle) k_mj1<2, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
+    else k_mj1<2, false><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit);
     return hipGetLastError();
 }
 
 hipError_t launch_mj_deep(int32_t* pi, int32_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     // below ~256 blocks the GPU is not filled and the plain Multi-Jump wins
-    if (n < (1 << 22)) return launch_mj1(pi, n, nullptr, s);
-    const int grid = (int)(((int64_t)n + kMjBlock - 1) / kMjBlock);
-    k_mj_local<<<grid, 1024, 0, s>>>(pi, n);
-    return mj1_launch(pi, n, nullptr, 0, false, s);
+    if (n >= (1 << 22)) {
+        const int grid = (int)(((int64_t)n + kMjBlock - 1) / kMjBlock);
+        k_mj_local<<<grid, 1024, 0, s>>>(pi, n);
+    }
+    return mj1_launch(pi, n, nullptr, 0, true, s);
 }
 
-hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t s,
+hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t s, bool settle,
                       uint32_t limit) {
     if (n <= 0) return hipSuccess;
-    // a gated launch may find nothing to do: a grid of at most 32 workgroups
-    // per CU, each thread striding over vertices, exits in a few microseconds
-    return mj1_launch(pi, n, gate, limit, gate != nullptr, s);
+    return mj1_launch(pi, n, gate, limit, settle, s);
 }
 
 hipError_t launch_mj(int32_t* pi, int32_t n, const uint32_t* gate, bool coherent, hipStream_t s) {
@@ -1229,18 +1234,17 @@ __global__ __launch_bounds__(1024) void k_hook_flag(const int32_t* __restrict__ 
     if (__ballot(changed) != 0 && (threadIdx.x & 63) == 0) ctrl->hook_changed = 1;
 }
 
-// One Jump (Fig. 2): pi(v) <- pi(pi(v)) for every vertex, raising
-// ctrl->jump_changed when any pointer moved.
+// One Jump (Fig. 2): pi(v) <- pi(pi(v)) for every vertex, stored also where it
+// does not move (settling, see common.hpp), raising ctrl->jump_changed when
+// any pointer moved.
 __global__ __launch_bounds__(256) void k_jump(int32_t* pi, int32_t n, Ctrl* ctrl) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool changed = false;
     if (x < n) {
         const int32_t p = ld_rlx(pi + x);
         const int32_t g = ld_rlx(pi + p);
-        if (g != p) {
-            st_rlx(pi + x, g);
-            changed = true;
-        }
+        st_rlx(pi + x, g);
+        changed = g != p;
     }
     if (__ballot(changed) != 0 && (threadIdx.x & 63) == 0) ctrl->jump_changed = 1;
 }

@@ -167,3 +167,35 @@ def test_filtered_plan_without_a_giant(dev):
     lab, st = cc.labels(put(u, dev), put(v, dev), n, return_stats=True)
     assert st["hook"] == 1 and st["filter_used"] == 0
     assert np.array_equal(lab.cpu().numpy(), oracle.labels(u, v, n))
+
+
+def test_racing_stores_settle(dev):
+    """Regression: in the atomic-free Hook, workgroups on different XCDs store
+    different parents to one slot; until the Multi-Jump after it stored every
+    vertex, XCDs went on reading different values and most solves of these
+    lists split a component.  Every one of many solves is compared."""
+    for name, (u, v, n) in {
+            "uniform 3n": (*graphgen.uniform_pairs(3 << 20, 1 << 20, seed=41, stream=0), 1 << 20),
+            "uniform n": (*graphgen.uniform_pairs(1 << 20, 1 << 20, seed=42, stream=0), 1 << 20),
+            "rmat20 3n": graphgen.rmat(20, 3, seed=43)}.items():
+        want = torch.from_numpy(oracle.labels(u, v, n)).to(dev)
+        du, dv = put(u, dev), put(v, dev)
+        order = np.argsort(u, kind="stable")
+        rp = torch.from_numpy(np.concatenate([[0], np.cumsum(np.bincount(u, minlength=n))])).to(dev)
+        col = put(v[order], dev)
+        out = torch.empty(n, dtype=torch.int32, device=dev)
+        calls = {"csr hybrid": lambda: cc.labels_csr(rp, col, n, out=out,
+                                                     options=cc.Options(hook="hybrid"))}
+        for opt in (cc.Options(), cc.Options(hook="plain"), cc.Options(hook="hybrid"),
+                    cc.Options(no_sync=True), cc.Options(hook="plain", host_loop="multijump"),
+                    cc.Options(hook="plain", host_loop="jump")):
+            calls[str(opt)] = lambda opt=opt: cc.labels(du, dv, n, out=out, options=opt)
+        for what, call in calls.items():
+            print("settle", name, what, flush=True)
+            bad = 0
+            for _ in range(15):
+                out.fill_(-1)
+                call()
+                torch.cuda.synchronize()
+                bad += not torch.equal(out, want)
+            assert bad == 0, (name, what, bad)
