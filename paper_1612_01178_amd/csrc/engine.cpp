@@ -87,6 +87,11 @@ constexpr int kPrefixRounds = 3;
 constexpr int64_t kPrefixStart = 2;
 constexpr int64_t kPrefixGrowth = 8;
 
+// Hybrid plan (see enqueue_hybrid).
+constexpr int kHybridRounds = 2;
+constexpr int32_t kHybridRoundsMaxN = 1 << 20;
+constexpr int64_t kHybridLong = int64_t(1) << 22;
+
 struct Plan {
     int hook = CC_HOOK_ATOMIC;  // resolved variant: CC_HOOK_ATOMIC, CC_HOOK_PLAIN or CC_HOOK_HYBRID
     int segments = 1;
@@ -173,18 +178,17 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     // orientations of every edge, half of it when each edge is listed once
     // (the library cannot tell the two apart).
     const int64_t s_paper = n > 0 ? std::min<int64_t>(int64_t(1) << 20, round_ratio(m, n)) : 1;
-    // Automatic variant (measured on gfx950): on large dense lists (average
-    // degree >= 8) the filtered Atomic-Hook wins (one pass over the entries,
-    // most of them reduced to two bitmap tests; R-MAT 24 3.8 ms against 38 ms
-    // for the atomic-free rounds); on large sparse lists the hybrid plan (the
-    // window round, then Atomic-Hook over the compacted pairs; percolated
-    // 4096^2 grid 0.38 ms against 1.07 Atomic-Hook and 0.99 atomic-free
-    // rounds).  On small lists (< 2^22 entries) the per-kernel cost dominates
-    // and the atomic-free rounds win (ER 2^16: 0.10 ms against 0.26 hybrid and
-    // 0.14-0.28 Atomic-Hook); a no-sync call needs a fixed launch
-    // sequence and takes the hybrid plan there.  CSR input has no atomic-free
-    // rounds: its large sparse inputs take the hybrid plan (grid as CSR 0.73
-    // ms against 1.47 Atomic-Hook), the rest the Atomic-Hook.
+    // Automatic variant (measured on gfx950): on dense lists (average degree
+    // >= 8, m >= 2^21) the filtered Atomic-Hook wins (one pass over the entries,
+    // most of them reduced to two bitmap tests; R-MAT 24 3.2 ms against 38 ms
+    // for the atomic-free rounds; R-MAT 18, m = 2.6 M 98 us against 113 for the
+    // hybrid plan, R-MAT 17, m = 2^20 83 against 75); on all other lists the
+    // hybrid plan (percolated 4096^2 grid 0.32 ms against 1.07 Atomic-Hook and
+    // 0.99 atomic-free rounds; 1237 x 1001 grid 83 us against 186 atomic-free
+    // rounds; R-MAT 20, m = 2^22 262 us; uniform n = 65,536, m = 524,672 60
+    // against 85), unless the call sets an option of the rounds.  CSR input
+    // has no atomic-free rounds: its large sparse inputs take the CSR hybrid
+    // (grid as CSR 0.73 ms against 1.47 Atomic-Hook), the rest the Atomic-Hook.
     const bool large = m >= (int64_t(1) << 22);
     const bool dense_large = m >= int64_t(1) << (input == kInputCsr ? 22 : 21) &&
                              n > 0 && m >= 8 * (int64_t)n;
@@ -195,7 +199,8 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
             auto_filtered = dense_large && op.filter != CC_FILTER_OFF;
         } else if (!allow_plain) {
             p.hook = large ? CC_HOOK_HYBRID : CC_HOOK_ATOMIC;
-        } else if (large || op.no_sync == 1) {
+        } else if (large || op.no_sync == 1 ||
+                   (op.max_rounds == 0 && op.rounds_per_check == 0 && op.compact_threshold == 0)) {
             p.hook = CC_HOOK_HYBRID;
         } else {
             p.hook = CC_HOOK_PLAIN;
@@ -203,6 +208,7 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
         // an explicit round cap is a question about the rounds: they run
         p.lds_single = allow_plain && op.symmetric == 0 && op.max_rounds == 0 &&
                        fits_lds_single(n, m);
+        if (p.lds_single) p.hook = op.no_sync == 1 ? CC_HOOK_HYBRID : CC_HOOK_PLAIN;
     } else {
         p.hook = op.hook;
     }
@@ -321,7 +327,7 @@ Layout layout(int32_t n, int64_t m, const Plan& p) {
         L.f1 = off;
         off += align256((size_t)m * 8);
     }
-    if (p.hook == CC_HOOK_HYBRID) {  // one frontier: round 1 writes it, nothing rewrites it
+    if (p.hook == CC_HOOK_HYBRID && m >= kHybridLong) {  // one frontier, written once
         L.cap = m;
         L.f0 = L.f1 = off;
         off += align256((size_t)m * 8);
@@ -411,6 +417,7 @@ int32_t ensure_dev(PoolEntry* e, size_t bytes) {
 
 int32_t ensure_host(PoolEntry* e, int64_t count = 1) {
     if (e->host_ctrl && e->host_ctrl_count >= count) return CC_OK;
+    drop_graphs(e);  // captured launches post to the old blocks
     if (e->host_ctrl) {
         HIPCHK(hipHostFree(e->host_ctrl));
         e->host_ctrl = nullptr;
@@ -526,8 +533,10 @@ int32_t run_graph(PoolEntry* pe, uint64_t key, hipStream_t s, F&& enqueue) {
 }
 
 // ---------------------------------------------------------------------- single solve
-int32_t finish(hipStream_t s, Ctrl* dctrl, Ctrl* hctrl, cc_stats* st) {
-    HIPCHK(hipMemcpyAsync(hctrl, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+// Waits for the call's work.  The control block reaches hctrl by a copy unless
+// the last launch has posted it there.
+int32_t finish(hipStream_t s, const Ctrl* dctrl, Ctrl* hctrl, cc_stats* st, bool posted = false) {
+    if (!posted) HIPCHK(hipMemcpyAsync(hctrl, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (st) st->host_syncs += 1;
     return CC_OK;
@@ -545,8 +554,6 @@ int32_t post_async(PoolEntry* e, hipStream_t s, const Ctrl* dctrl) {
 }
 
 
-// Enqueues the Atomic-Hook solve (Fig. 4) of one graph on s; no synchronisation.
-// `ctrl` is the graph's control block, `bits` its giant bitmap (filter plans).
 // Giant-filter buffers of one solve (null when the plan does not use them).
 struct FilterBufs {
     uint32_t* bits = nullptr;
@@ -583,9 +590,12 @@ constexpr int64_t kSuperGrowth = 4;
 // for 8; the same graph as CSR 4.74 against 4.76 ms for 1.
 constexpr int64_t kSuperStart = 2;
 
+// Enqueues the Atomic-Hook solve (Fig. 4) of one graph on s; no
+// synchronisation.  `ctrl` is the graph's control block, posted to `host`
+// (nullable) by the last launch.
 int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                        const Plan& p, Ctrl* ctrl, const FilterBufs& fb, hipStream_t s, Timer& tm,
-                       cc_stats* st) {
+                       cc_stats* st, Ctrl* host) {
     uint32_t* bits = fb.bits;
     const bool hot = p.hot && fb.hot_tags != nullptr;
     const bool vhot = p.hot && fb.vtab != nullptr;
@@ -596,13 +606,14 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
         return segment_start(m, i, S);
     };
     int hooks = 0, jumps = 0;
+    const Post post = {ctrl, host};
     TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     if (p.filter != CC_FILTER_GIANT) {
         // Fig. 4: for each segment, Atomic-Hook the segment, then Multi-Jump all of V.
         for (int i = 0; i < S; ++i) {
             TIMED(kPhaseHook, launch_ahook(u, v, bound(i), bound(i + 1), pi, n, ctrl, nullptr,
                                            p.block, p.ept, p.coherent, p.halve, p.symmetric, s));
-            TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
+            TIMED(kPhaseCompress, launch_mj(pi, n, p.coherent, s, i + 1 == S ? post : Post{}));
             ++hooks;
             ++jumps;
         }
@@ -614,7 +625,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
             if (i < kPrefixRounds)
                 TIMED(kPhaseHook, launch_hook_prefix(u, v, prefix, pi, n, i == 0, s));
             else
-                TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, s));
+                TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, p.halve, s));
             TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s, i < kPrefixRounds));
             ++hooks;
             ++jumps;
@@ -626,7 +637,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
             else
                 TIMED(kPhaseHook, launch_ahook(u, v, bound(i), bound(i + 1), pi, n, ctrl, nullptr,
                                                p.block, p.ept, p.coherent, p.halve, p.symmetric, s));
-            TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
+            TIMED(kPhaseCompress, launch_mj(pi, n, p.coherent, s));
             ++hooks;
             ++jumps;
         }
@@ -680,7 +691,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
                 TIMED(kPhaseCompress, launch_mj_bitmap(pi, n, ctrl, bits, hot ? fb.hot_tags : nullptr,
                                                        fb.hot_vals, p.hot_slots, fb.vtab, s));
             } else {
-                TIMED(kPhaseCompress, launch_mj(pi, n, nullptr, p.coherent, s));
+                TIMED(kPhaseCompress, launch_mj(pi, n, p.coherent, s, to < m ? Post{} : post));
                 if (to < m) TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
             }
             ++hooks;
@@ -695,51 +706,60 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     return CC_OK;
 }
 
-// The atomic-free Hook in blocks of K = rounds_per_check rounds, the host
-// reading the control block after each block.  With `graph`, each block's
-// launches (block b: rounds bK+1 .. bK+K; block 0 also the init) are
-// captured once per (arrays, sizes, plan, b) and replayed.
 // Hybrid plan: one atomic-free Hook round (Fig. 2) over all entries, in
 // which each workgroup first joins its chunk of entries in an LDS window
-// (launch_hook_window), and the compaction of the entries whose endpoints
-// still have different parents into parent pairs; then one Atomic-Hook pass
-// with path halving (Fig. 3) over those pairs and a final Multi-Jump (skipped
-// on the device when no pair was active).  Trees only merge, so an entry
-// dropped by the compaction stays satisfied; the pairs are vertices of the
-// endpoints' trees, valid starting parents for the climb.  A fixed launch
-// sequence: no host read until the end.
+// (launch_hook_window), then a pass over all entries that hooks the ones
+// still active for good (Fig. 3), and a final Multi-Jump.  A fixed launch
+// sequence without a host read; what depends on the input is decided on the
+// device by win_far, which exceeds far_limit when more than a quarter of the
+// entries (or a whole chunk) were hooked outside the windows.
+//
+// Short lists: Multi-Jump, and where there is no locality kHybridRounds more
+// atomic-free rounds (each round leaves about a sixteenth of the roots, so
+// that the last pass joins few; up to kHybridRoundsMaxN vertices, above which
+// a round's gathers cost more than the compare-and-swaps it saves), then the
+// contracting hook over all entries.  Long lists with locality instead
+// compact the entries whose parents differ into pairs and hook those: an
+// entry with equal parents is inside one tree, a kept pair is a valid climb
+// start, and few entries are left, so no Multi-Jump runs first (4096^2 grid:
+// 318 us against 352 with the contracting hook).
 int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                        const Plan& p, char* ws, const Layout& L, hipStream_t s, Timer& tm,
-                       cc_stats* st) {
+                       cc_stats* st, Ctrl* host) {
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
-    int2* F = reinterpret_cast<int2*>(ws + L.f0);
     const int grid_cap = device_cu_count() * 8;
+    const uint32_t far_limit = (uint32_t)(m / 8);  // win_far counts pairs of entries
+    const uint32_t* far = &ctrl->win_far;
+    const bool longer = m >= kHybridLong;
+    // uniform lists of fewer entries than vertices have no large component
+    const int rounds = n <= kHybridRoundsMaxN && 10 * m >= 11 * (int64_t)n ? kHybridRounds : 0;
     TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
-    // the atomic-free round, each workgroup's chunk joined in an LDS window
-    TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, (uint32_t)(m / 8), s));
-    // The compaction compares parents, not roots.  An entry whose endpoints
-    // have equal parents is inside one tree and is dropped; one whose parents
-    // differ is kept (also when they share a root), and the Atomic-Hook climbs
-    // from that pair to the roots (every parent is a vertex of its endpoint's
-    // tree, a valid start).  When the windows held most entries, nearly every
-    // vertex already points at its chunk's local root and the extra pairs
-    // are few, so no Multi-Jump runs first (4096^2 grid: it cost 58 us, the
-    // pairs it saved far less); when more than a quarter of the entries were
-    // hooked outside the windows (inputs without locality), the plain round's
-    // chains would make most entries look active, and a Multi-Jump, gated on
-    // the device by that count, makes the trees stars first.
-    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->win_far, s, true, (uint32_t)(m / 8)));
-    TIMED(kPhaseHook, launch_compact(1, u, v, m, F, F, L.cap, pi, n, ctrl, 0xffffffffu, p.block,
-                                     p.ept, grid_cap, s));
-    TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], L.cap, pi, p.halve, grid_cap, s));
-    TIMED(kPhaseCompress, launch_mj1(pi, n, &ctrl->count[1], s, false));
+    TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, far_limit, s));
+    TIMED(kPhaseCompress, launch_mj1(pi, n, longer ? far : nullptr, s, true, far_limit));
+    for (int r = 0; r < rounds; ++r) {
+        TIMED(kPhaseHook, launch_hook_prefix(u, v, m, pi, n, false, s, far, far_limit));
+        TIMED(kPhaseCompress, launch_mj1(pi, n, far, s, true, far_limit));
+    }
+    if (longer) {
+        int2* F = reinterpret_cast<int2*>(ws + L.f0);
+        TIMED(kPhaseHook, launch_compact(1, u, v, m, F, F, L.cap, pi, n, ctrl, 0xffffffffu, p.block,
+                                         p.ept, grid_cap, s, far, far_limit));
+        TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], L.cap, pi, p.halve, grid_cap, s));
+    }
+    TIMED(kPhaseHook, launch_hook_contract(u, v, 0, m, pi, n, ctrl, p.halve, s,
+                                           longer ? far : nullptr, far_limit));
+    TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s, false, 0, Post{ctrl, host}));
     if (st) {
-        st->hook_launches += 3;
-        st->compress_launches += 2;
+        st->hook_launches += 2 + rounds + (longer ? 2 : 0);
+        st->compress_launches += 2 + rounds;
     }
     return CC_OK;
 }
 
+// The atomic-free Hook in blocks of K = rounds_per_check rounds, the host
+// reading the control block after each block.  With `graph`, each block's
+// launches (block b: rounds bK+1 .. bK+K; block 0 also the init) are
+// captured once per (arrays, sizes, plan, b) and replayed.
 int32_t solve_plain(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                     const Plan& p, char* ws, const Layout& L, hipStream_t s, PoolEntry* pe,
                     Ctrl* hctrl, bool use_graph, Timer& tm, cc_stats* st, int64_t* rounds_run) {
@@ -903,15 +923,17 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
     }
     if (p.hook == CC_HOOK_ATOMIC || p.hook == CC_HOOK_HYBRID) {
         // fixed launch sequences: no host read until the end
+        // (the pool's control blocks are pinned: the last launch posts there)
+        Ctrl* host = pe && !p.no_sync ? hctrl : nullptr;
         auto enqueue = [&](cc_stats* sx) {
             if (p.hook == CC_HOOK_HYBRID)
-                return enqueue_hybrid(n, u, v, m, out, p, ws, L, s, tm, sx);
+                return enqueue_hybrid(n, u, v, m, out, p, ws, L, s, tm, sx, host);
             return enqueue_atomic(n, u, v, m, out, p, reinterpret_cast<Ctrl*>(ws),
-                                  filter_bufs(ws, L), s, tm, sx);
+                                  filter_bufs(ws, L), s, tm, sx, host);
         };
         if (use_graph) {
             KeyHash k;
-            k.add(n).add(m).add(u).add(v).add(out).add(ws).add(s).add(p.hook).add(p.segments)
+            k.add(n).add(m).add(u).add(v).add(out).add(ws).add(s).add(host).add(p.hook).add(p.segments)
                 .add(p.filter).add(p.filter_after).add(p.block).add(p.ept).add(p.coherent)
                 .add(p.hot).add(p.hot_slots).add(p.lds_bits).add(p.auto_filter).add(p.prefix).add(p.halve)
                 .add(p.symmetric);
@@ -924,7 +946,7 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
             if (st) st->giant_label = -1;  // not known without a synchronisation
             return rc;
         }
-        if (rc == CC_OK) rc = finish(s, reinterpret_cast<Ctrl*>(ws), hctrl, st);
+        if (rc == CC_OK) rc = finish(s, reinterpret_cast<Ctrl*>(ws), hctrl, st, host != nullptr);
     } else if (p.host_loop != CC_HOST_LOOP_OFF) {
         rc = solve_host_loop(n, u, v, m, out, p, ws, s, hctrl, tm, st);
     } else {
@@ -1137,7 +1159,7 @@ int32_t stream_impl(int32_t n, const int32_t* hu, const int32_t* hv, int64_t m, 
         const bool filtered = filter && i > 0;
         HIPCHK(launch_ahook(su[b], sv[b], 0, len, out, n, ctrl, filtered ? bits : nullptr, p.block,
                             p.ept, p.coherent, p.halve, p.symmetric, s));
-        HIPCHK(launch_mj(out, n, nullptr, p.coherent, s));
+        HIPCHK(launch_mj(out, n, p.coherent, s));
         ++hooks;
         ++jumps;
         if (filter && i == 0) HIPCHK(launch_sample_giant(su[b], len, out, n, ctrl, s));
@@ -1207,6 +1229,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
     Timer tm;
     tm.on = p.profile;
     tm.s = s;
+    const Post post = {ctrl, p.no_sync ? nullptr : pe->host_ctrl};
     int hooks = 0, jumps = 0;
     TIMED(kPhaseOther, launch_init(out, n, ctrl, s));
     TIMED(kPhaseOther, launch_csr_check(row_ptr, n, m, ctrl, s));
@@ -1220,14 +1243,14 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
                                              p.symmetric, s));
         TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], m, out, p.halve,
                                              device_cu_count() * 8, s));
-        TIMED(kPhaseCompress, launch_mj1(out, n, &ctrl->count[1], s, false));
+        TIMED(kPhaseCompress, launch_mj1(out, n, &ctrl->count[1], s, false, 0, post));
         hooks = 3;
         jumps = 2;
     } else if (!filter) {
         for (int i = 0; i < S; ++i) {
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(i), bound(i + 1), out, ctrl,
                                                nullptr, p.symmetric, p.halve, false, s));
-            TIMED(kPhaseCompress, launch_mj(out, n, nullptr, false, s));
+            TIMED(kPhaseCompress, launch_mj(out, n, false, s, i + 1 == S ? post : Post{}));
             ++hooks;
             ++jumps;
         }
@@ -1236,7 +1259,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
         for (int i = 0; i < fa; ++i) {
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(i), bound(i + 1), out, ctrl,
                                                nullptr, p.symmetric, p.halve, false, s));
-            TIMED(kPhaseCompress, launch_mj(out, n, nullptr, false, s));
+            TIMED(kPhaseCompress, launch_mj(out, n, false, s));
             ++hooks;
             ++jumps;
         }
@@ -1248,7 +1271,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
             const int64_t h = std::min<int64_t>(S, g + step);
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(g), bound(h), out, ctrl, bits,
                                                p.symmetric, p.halve, false, s));
-            TIMED(kPhaseCompress, launch_mj(out, n, nullptr, false, s));
+            TIMED(kPhaseCompress, launch_mj(out, n, false, s, h < S ? Post{} : post));
             ++hooks;
             ++jumps;
             if (h < S) TIMED(kPhaseOther, launch_bitmap(out, n, ctrl, bits, s));
@@ -1263,7 +1286,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
         }
         return post_async(pe, s, ctrl);
     }
-    rc = finish(s, ctrl, pe->host_ctrl, st);
+    rc = finish(s, ctrl, pe->host_ctrl, st, true);
     if (rc != CC_OK) return rc;
     tm.collect(st);
     if (st) {
@@ -1306,7 +1329,7 @@ int32_t lds_segments(int64_t m, int64_t n, int32_t cap) {
 // every larger graph gets the device-memory Atomic-Hook solve with its own
 // control block.  Everything is enqueued on `s`; the call ends with one
 // synchronisation, after which the LDS launch's pinned status word and the
-// large graphs' control blocks (copied back) are read.
+// large graphs' control blocks (posted by their last launches) are read.
 template <class GraphAt>
 int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hipStream_t s,
                   cc_stats* st, void* workspace, size_t ws_bytes, size_t* ws_needed) {
@@ -1453,7 +1476,7 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
             const cc_graph G = graph_at(large[i]);
             int32_t r2 = enqueue_atomic(G.n, G.edges_u, G.edges_v, G.m, G.out_label, plans[i],
                                         &lctrls[i], filter_bufs(ws + region_off[i], layouts[i]),
-                                        s, tm, nullptr);
+                                        s, tm, nullptr, &pe->host_ctrl[i]);
             if (r2 != CC_OK) return r2;
         }
         return CC_OK;
@@ -1465,7 +1488,7 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
         // copy node re-reads the pinned staging buffer, rewritten above, at
         // every replay.  Only what the capture bakes in is: sizes, pointers,
         // the LDS launch shape, and each large graph's arrays and plan.
-        k.add(count).add(ws).add(s).add(pe->host_stage).add(seg_cap).add(lds_halve)
+        k.add(count).add(ws).add(s).add(pe->host_stage).add(pe->host_ctrl).add(seg_cap).add(lds_halve)
             .add(maxn_small).add(ns).add(nl).add(lds_block);
         for (int32_t i = 0; i < nl; ++i) {
             const cc_graph G = graph_at(large[i]);
@@ -1477,8 +1500,6 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
     }
     if (rc != CC_OK) return rc;
     if (st) st->hook_launches += (ns > 0 ? 1 : 0);
-    if (nl > 0)
-        HIPCHK(hipMemcpyAsync(pe->host_ctrl, lctrls, sizeof(Ctrl) * nl, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (st) st->host_syncs += 1;
     bool bad = (*(volatile int32_t*)pe->batch_status & kStatusRange) != 0;

@@ -22,14 +22,22 @@ hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin,
                               int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, bool sym,
                               hipStream_t s);
 // One atomic-free Hook (Fig. 2) pass over entries [0, m), which are hooked
-// again later; `first`: pi is the identity.  No range check.
+// again later; `first`: pi is the identity.  No range check.  Does nothing
+// when `gate` is non-null and *gate <= limit.
 hipError_t launch_hook_prefix(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi, int32_t n,
-                              bool first, hipStream_t s);
+                              bool first, hipStream_t s, const uint32_t* gate = nullptr,
+                              uint32_t limit = 0);
 
-// Multi-Jump (Fig. 3) over all n vertices.  When `gate` is non-null the
-// kernel does nothing if *gate == 0.  `coherent` selects agent-scope tree
-// loads and stores (see common.hpp).
-hipError_t launch_mj(int32_t* pi, int32_t n, const uint32_t* gate, bool coherent, hipStream_t s);
+// Where a call's last launch copies the control block for the host (pinned
+// memory); nothing is copied when host is null.
+struct Post {
+    const Ctrl* ctrl = nullptr;
+    Ctrl* host = nullptr;
+};
+
+// Multi-Jump (Fig. 3) over all n vertices.  `coherent` selects agent-scope
+// tree loads and stores (see common.hpp).
+hipError_t launch_mj(int32_t* pi, int32_t n, bool coherent, hipStream_t s, Post post = {});
 
 // Multi-Jump for deep trees: pointer jumping within blocks of consecutive
 // vertices in LDS, then a climb across blocks (the plain Multi-Jump for
@@ -39,7 +47,7 @@ hipError_t launch_mj_deep(int32_t* pi, int32_t n, hipStream_t s);
 // `gate` is non-null and *gate <= limit.  `settle`: every vertex is stored
 // (after a pass of racing workgroup-scope stores); launch_mj_deep always does.
 hipError_t launch_mj1(int32_t* pi, int32_t n, const uint32_t* gate, hipStream_t s, bool settle,
-                      uint32_t limit = 0);
+                      uint32_t limit = 0, Post post = {});
 
 // Giant-component sample: label of the component that holds the most of
 // 1,024 edge endpoints drawn across entries [0, m); sets ctrl->giant and
@@ -78,14 +86,17 @@ hipError_t launch_ahook_pairs(const int2* fr, const uint32_t* count, int64_t cap
                               bool halve, int grid_cap, hipStream_t s);
 
 // Atomic-Hook of entries [begin, end) with each workgroup's active roots joined
-// in LDS first; pi a forest of stars with few roots left.
+// in LDS first; pi a forest of stars with few roots left.  Gate as above.
 hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
-                                int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s);
+                                int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
+                                const uint32_t* gate = nullptr, uint32_t limit = 0);
 
 // tau: frontier rewrite threshold in thousandths (0xffffffff = every round).
+// Does nothing when `skip` is non-null and *skip > limit.
 hipError_t launch_compact(int round, const int32_t* u, const int32_t* v, int64_t m, int2* f0,
                           int2* f1, int64_t cap, const int32_t* pi, int32_t n, Ctrl* ctrl,
-                          uint32_t tau, int block, int ept, int grid_cap, hipStream_t s);
+                          uint32_t tau, int block, int ept, int grid_cap, hipStream_t s,
+                          const uint32_t* skip = nullptr, uint32_t limit = 0);
 
 // Fig. 1 as a host loop: a Hook pass over all m entries that sets
 // ctrl->hook_changed when an entry's parents differ, and one level of Jump

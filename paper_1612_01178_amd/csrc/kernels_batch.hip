@@ -518,30 +518,37 @@ hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, co
 
 // Window round of the hybrid plan (an atomic-free Hook round, Fig. 2, with
 // the Hook of each workgroup's chunk done in LDS; beyond the paper).
-// Workgroup w takes entries [w * kWinEntries, (w + 1) * kWinEntries) and a
-// window of kWinSlots consecutive vertices starting at the smallest endpoint
-// among the chunk's first blockDim.x entries.  Entries with both endpoints in
-// the window are joined completely in LDS (Atomic-Hook with path halving on
-// 16-bit local ids, then a Multi-Jump over the window); every other entry
-// gets the device-memory atomic-free Hook (plain store pi[max] = min of the
-// endpoints' current parents).  Then each window vertex that is not its
-// local root is pointed at it with a plain store.  The number of entries
-// hooked outside the windows is added to ctrl->win_far.
+// Workgroup w takes entries [w * chunk, (w + 1) * chunk) and a window of
+// `slots` consecutive vertices starting at the smallest endpoint among the
+// chunk's first blockDim.x entries.  Entries with both endpoints in the window
+// are joined completely in LDS (Atomic-Hook with path halving on 16-bit local
+// ids, then a Multi-Jump over the window); every other entry gets the
+// device-memory atomic-free Hook (pi[max] = min of the endpoints' current
+// parents).  Then each window vertex that is not its local root is pointed at
+// it.  The number of entries hooked outside the windows is added to
+// ctrl->win_far, in pairs.
+//
+// A chunk of whose first entries fewer than three eighths lie in its window
+// has no locality; it is hooked without a window, each entry pointing its
+// larger endpoint at the smaller one (their own parents at the init; nothing
+// is loaded), and raises ctrl->win_far above far_limit, so that the caller
+// treats the list as one without locality.
 //
 // Every value written to pi names a vertex of the slot's own component below
-// the slot (a local root, or the smaller of two parents joined by an entry),
+// the slot (a local root, or the smaller of two vertices joined by an entry),
 // so pi stays a forest of subsets of components with pi[x] <= x.  Stores of
 // different workgroups to one slot overwrite each other, which can split a
-// chunk's local component into several trees; then some entry of that chunk
-// joins two of them, and the compaction that follows the Multi-Jump keeps it
-// for the Atomic-Hook pass.  No thread of this kernel takes a root by CAS in
-// device memory, so its stores are of workgroup scope.  On inputs whose
-// consecutive entries touch nearby ids (a row-major lattice) nearly every
-// entry is joined in LDS and few survive the round; elsewhere the chunks'
-// windows hold few entries and the round is the plain one.  The sizes: a
-// chunk of a percolated 4096^2 lattice spans ~39,200 ids (within the
-// window), two workgroups fit a CU (80 KiB of LDS each), so the lattice's
-// 478 chunks run at once.
+// chunk's local component into several trees; the pass that follows over all
+// entries joins them.  The window stores are of agent scope (see settling in
+// common.hpp; the slots are hardly contended, the cost is nil); those of
+// chunks without locality are not, and a settling Multi-Jump follows them.
+// On inputs whose consecutive entries touch nearby ids (a row-major lattice)
+// nearly every entry is joined in LDS and few survive the round.
+//
+// Sizes by list length (window_shape below): a chunk of a percolated lattice
+// spans ~0.8 ids per entry plus a row; long lists take the largest chunks of
+// which two workgroups fit a CU (80 KiB of LDS), shorter ones smaller chunks,
+// so that every CU has one.
 constexpr int kWinEPT = 4;  // entries per thread per step (registers: two workgroups per CU)
 
 __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict__ eu,
@@ -550,7 +557,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
                                                       int32_t chunk, uint32_t slots,
                                                       int32_t segments, uint32_t far_limit) {
     extern __shared__ uint16_t spi[];
-    __shared__ int32_t wave_min[16], wave_max[16];
+    __shared__ int32_t wave_min[16];
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t lane = tid & 63, wave = tid >> 6, waves = nthr >> 6;
     const int64_t c0 = (int64_t)blockIdx.x * chunk;
@@ -559,47 +566,26 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     g_cint* gu = (g_cint*)eu;
     g_cint* gv = (g_cint*)ev;
     int32_t a[kWinEPT], b[kWinEPT], na[kWinEPT], nb[kWinEPT];
-    // the first segment's first entries are loaded before the LDS init, so
-    // that their latency overlaps it; the window starts at the smallest
-    // endpoint among the first blockDim.x of them
+    // the window starts at the smallest endpoint among the first blockDim.x
+    // entries
     const int64_t first_end = c0 + (c1 - c0) / segments;
     edge_step_loads<kWinEPT>(gu, gv, c0, first_end, step, a, b);
-    uint32_t* w32 = reinterpret_cast<uint32_t*>(spi);
-    for (uint32_t w = tid; w < slots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
-    int32_t lo = INT32_MAX, hi = 0;
-    if (c0 + tid < first_end) {
-        if ((uint32_t)a[0] < (uint32_t)n) {
-            lo = min(lo, a[0]);
-            hi = max(hi, a[0]);
-        }
-        if ((uint32_t)b[0] < (uint32_t)n) {
-            lo = min(lo, b[0]);
-            hi = max(hi, b[0]);
-        }
-    }
+    const bool first = c0 + tid < first_end && max((uint32_t)a[0], (uint32_t)b[0]) < (uint32_t)n;
+    int32_t lo = first ? min(a[0], b[0]) : INT32_MAX;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        lo = min(lo, __shfl_xor(lo, d, 64));
-        hi = max(hi, __shfl_xor(hi, d, 64));
-    }
-    if (lane == 0) {
-        wave_min[wave] = lo;
-        wave_max[wave] = hi;
-    }
+    for (int d = 32; d >= 1; d >>= 1) lo = min(lo, __shfl_xor(lo, d, 64));
+    if (lane == 0) wave_min[wave] = lo;
     __syncthreads();
-    int32_t base = wave_min[0], top = wave_max[0];
-    for (uint32_t i = 1; i < waves; ++i) {
-        base = min(base, wave_min[i]);
-        top = max(top, wave_max[i]);
-    }
+    int32_t base = wave_min[0];
+    for (uint32_t i = 1; i < waves; ++i) base = min(base, wave_min[i]);
     if (base == INT32_MAX) base = 0;
+    // window vertices: [base, base + span)
+    const uint32_t span = (uint32_t)min<int64_t>((int64_t)slots, (int64_t)n - base);
     bool bad = false;
-    // No locality: the chunk's first entries span more ids than the window
-    // holds.  The chunk is hooked in device memory; every endpoint still is
-    // its own parent or may be treated so (a stale value only loses a store).
-    if (top >= base && (uint32_t)(top - base) >= 4 * slots) {
+    const int near = __syncthreads_count(first && (uint32_t)max(a[0], b[0]) - (uint32_t)base < span);
+    if (8 * near < 3 * (int)min<int64_t>(first_end - c0, nthr)) {
         for (int64_t sb = c0; sb < c1; sb += step) {
-            edge_step_loads<kWinEPT>(gu, gv, sb, c1, step, a, b);
+            if (sb > c0 || segments > 1) edge_step_loads<kWinEPT>(gu, gv, sb, c1, step, a, b);
 #pragma unroll
             for (int j = 0; j < kWinEPT; ++j) {
                 const bool ok = max((uint32_t)a[j], (uint32_t)b[j]) < (uint32_t)n;
@@ -607,12 +593,15 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
                 if (ok && a[j] != b[j]) st_rlx(pi + max(a[j], b[j]), min(a[j], b[j]));
             }
         }
-        if (tid == 0) atomicMax(&ctrl->win_far, far_limit + 1);
+        // a plain store: additions by other workgroups only raise it
+        if (tid == 0)
+            __hip_atomic_store(&ctrl->win_far, far_limit + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (bad) atomicOr(&ctrl->status, kStatusRange);
         return;
     }
-    // window vertices: [base, base + span)
-    const uint32_t span = (uint32_t)min<int64_t>((int64_t)slots, (int64_t)n - base);
+    uint32_t* w32 = reinterpret_cast<uint32_t*>(spi);
+    for (uint32_t w = tid; w < slots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
+    __syncthreads();
     uint32_t far = 0;  // entries hooked outside the window
     // The chunk in `segments` segments, each followed by a Multi-Jump over
     // the window (the schedule of Fig. 4 inside the chunk) so that later
@@ -653,8 +642,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
         __syncthreads();
         // Multi-Jump over the window: each vertex climbs to its local root
         // and stores it once; after the last segment the local roots of the
-        // non-roots go to pi
-        // (two vertices per thread and pass, their climbs interleaved)
+        // non-roots go to pi (two vertices per thread and pass, their climbs interleaved)
         const bool last = seg + 1 == segments;
         for (uint32_t x = tid; x < span; x += 2 * nthr) {
             const uint32_t y = x + nthr;
@@ -684,22 +672,34 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     if (bad) atomicOr(&ctrl->status, kStatusRange);
 }
 
-constexpr uint32_t kWinSlotsMax = 65536;
-hipError_t launch_hook_window_p(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, int32_t chunk, uint32_t slots, int32_t segments, int block, uint32_t far_limit, hipStream_t s) {
+// Chunk and window sizes for m entries (whole solve, us; percolated lattices):
+// 4096^2, 23 M entries 318 (49,152-entry chunks) and 328 (24,576); 2048^2,
+// 5.9 M 170 and 131; 1237 x 1001, 1.7 M 96 (24,576) and 83 (8,192); 300^2,
+// 126,000 41 (4,096).
+struct WindowShape {
+    int32_t chunk, segments;
+    uint32_t slots;
+};
+static WindowShape window_shape(int64_t m) {
+    if (m >= 8 << 20) return {49152, 2, 40960};
+    if (m >= 3 << 20) return {24576, 2, 24576};
+    if (m >= 1 << 20) return {8192, 2, 12288};
+    return {4096, 1, 8192};
+}
+
+hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
+                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
     if (m <= 0) return hipSuccess;
     static hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hook_window),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kWinSlotsMax * 2);
+                                                 40960 * 2);
     if (once != hipSuccess) return once;
-    const int64_t grid = (m + chunk - 1) / chunk;
+    const WindowShape w = window_shape(m);
+    const int64_t grid = (m + w.chunk - 1) / w.chunk;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    k_hook_window<<<(int)grid, block, slots * 2, s>>>(u, v, m, pi, n, ctrl, chunk, slots, segments, far_limit);
+    k_hook_window<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots,
+                                                       w.segments, far_limit);
     return hipGetLastError();
-}
-hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
-    return launch_hook_window_p(u, v, m, pi, n, ctrl, 49152, 40960, 2, 1024, far_limit, s);
 }
 
 hipError_t prepare_batch_lds() {

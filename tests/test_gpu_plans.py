@@ -199,3 +199,38 @@ def test_racing_stores_settle(dev):
                 torch.cuda.synchronize()
                 bad += not torch.equal(out, want)
             assert bad == 0, (name, what, bad)
+
+
+# (n, entries per vertex): the hybrid plan's rules on one side and the other:
+# no further rounds (sparse; more than 2^20 vertices), two further rounds, the
+# last short list, lists with one chunk that has locality and one that has not
+@pytest.mark.parametrize("n,m", [(40000, 30000), (40000, 44000), (1 << 20, 1 << 21),
+                                 ((1 << 20) + 1, 1 << 21), (1 << 20, (1 << 22) - 1),
+                                 (1 << 20, 1 << 22), (3000, 500000)])
+def test_hybrid_plan(dev, n, m):
+    u, v = graphgen.uniform_pairs(m, n, seed=n + m, stream=0)
+    path = np.arange(n - 1, dtype=np.int32)
+    lists = {"uniform": (u, v), "half a path": (np.concatenate([path, u[: m // 2]]),
+                                                np.concatenate([path + 1, v[: m // 2]]))}
+    hub = u.copy()
+    hub[: m // 2] = n - 1  # half of the entries share an endpoint, the largest id
+    lists["hub"] = (hub, v)
+    for name, (a, b) in lists.items():
+        want = oracle.labels(a, b, n)
+        for offset in (0, 2):
+            da, db = put(a, dev, offset), put(b, dev, offset)
+            for opt in (cc.Options(), cc.Options(hook="hybrid", path_halving="off"),
+                        cc.Options(no_sync=True)):
+                print("hybrid", n, m, name, offset, opt.no_sync, flush=True)
+                out = torch.full((n,), -7, dtype=torch.int32, device=dev)
+                cc.labels(da, db, n, out=out, options=opt)
+                torch.cuda.synchronize()
+                assert np.array_equal(out.cpu().numpy(), want), (name, opt)
+        if m < 1 << 22:
+            out.fill_(-7)
+            cc.labels_noalloc(da, db, n, out=out)
+            assert np.array_equal(out.cpu().numpy(), want), name
+    u[m - 1] = n
+    with pytest.raises(cc.CCError) as ei:
+        cc.labels(put(u, dev), put(v, dev), n)
+    assert ei.value.code == cc.CC_ERR_RANGE
