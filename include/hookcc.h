@@ -62,10 +62,10 @@ extern "C" {
 /* ---------------------------------------------------------------- options */
 #define CC_HOOK_AUTO 0   /* library choice (the default): the Atomic-Hook with the
                             giant filter for lists of m >= 2^21 entries (CSR: 2^22) with
-                            m / n >= 8, the hybrid plan below for the other lists of
-                            m >= 2^22 entries; the
-                            atomic-free Hook for smaller lists (the hybrid plan for a
-                            no-sync call); the Atomic-Hook with the symmetric flag.
+                            m / n >= 8, the hybrid plan below for the other lists (the
+                            atomic-free Hook when max_rounds, rounds_per_check or
+                            compact_threshold is set and m < 2^22); the Atomic-Hook with
+                            the symmetric flag.
                             The smallest lists (n <= 32,768, 2 n + m <= 131,072, no
                             max_rounds) are solved by one workgroup in LDS, in one
                             launch, and counted as one round of the atomic-free Hook  */
@@ -73,10 +73,11 @@ extern "C" {
 #define CC_HOOK_PLAIN 2  /* atomic-free Hook (Fig. 2) rounds until no change (Fig. 1),
                             convergence test and active-edge frontier on the device   */
 #define CC_HOOK_HYBRID 3 /* one atomic-free Hook round (Fig. 2) over all entries with its
-                            Multi-Jump and frontier compaction, then Atomic-Hook (Fig. 3,
-                            path halving) over the still-active root pairs and a final
-                            Multi-Jump: a fixed launch sequence, no host read (the same
-                            for CSR input)                                          */
+                            Multi-Jump (and up to two more on short lists without
+                            locality), then the Atomic-Hook (Fig. 3, path halving) of the
+                            entries still active and a final Multi-Jump: a fixed launch
+                            sequence, no host read (CSR: one round, the active entries
+                            compacted to root pairs)                                */
 
 #define CC_FILTER_OFF 0  /* Atomic-Hook only: hook every edge entry                   */
 #define CC_FILTER_GIANT 1 /* Atomic-Hook only: after the first segment(s), sample the
