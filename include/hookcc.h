@@ -61,7 +61,7 @@ extern "C" {
 
 /* ---------------------------------------------------------------- options */
 #define CC_HOOK_AUTO 0   /* library choice (the default): the Atomic-Hook with the
-                            giant filter for lists of m >= 2^21 entries (CSR: 2^22) with
+                            giant filter for lists of m >= 2^21 entries (CSR: 2^20) with
                             m / n >= 8, the hybrid plan below for the other lists (the
                             atomic-free Hook when max_rounds, rounds_per_check or
                             compact_threshold is set and m < 2^22); the Atomic-Hook with
@@ -76,8 +76,7 @@ extern "C" {
                             Multi-Jump (and up to two more on short lists without
                             locality), then the Atomic-Hook (Fig. 3, path halving) of the
                             entries still active and a final Multi-Jump: a fixed launch
-                            sequence, no host read (CSR: one round, the active entries
-                            compacted to root pairs)                                */
+                            sequence, no host read                                    */
 
 #define CC_FILTER_OFF 0  /* Atomic-Hook only: hook every edge entry                   */
 #define CC_FILTER_GIANT 1 /* Atomic-Hook only: after the first segment(s), sample the
@@ -367,17 +366,19 @@ int32_t cc_labels_host(int32_t n, const int32_t* host_u, const int32_t* host_v, 
 
 /* CSR adjacency input: entry i of row r is the pair (r, col[i]).  The
  * Atomic-Hook works on any subsets of E (Fig. 4), so the solve is the same as
- * for a pair list of m entries; the row of an entry is found on the fly (an
- * LDS window of row_ptr per tile), and with the giant filter the row's bit is
- * tested once per group of four consecutive entries.
+ * for a pair list of m entries.  The hybrid plan writes each entry's row first
+ * (4 bytes of scratch per entry); the automatic filtered plan starts from two
+ * neighbours per row and passes over the entries once; both give way to the
+ * unfiltered Atomic-Hook where their scratch cannot be had (no memory, or
+ * inside a stream capture).
  *   row_ptr    [device] int64[n+1]: row_ptr[0] == 0, non-decreasing, row_ptr[n] == m
  *   col        [device] int32[m], ids in [0, n)
  *   out_label  [device] int32[n]
  *   opts       as cc_labels_ex; hook CC_HOOK_AUTO, CC_HOOK_ATOMIC or CC_HOOK_HYBRID
- *              (AUTO: the hybrid plan for m >= 2^22 entries with m / n < 8, else
- *              the Atomic-Hook, filtered when m >= 2^22 and m / n >= 8);
+ *              (AUTO: the filtered Atomic-Hook for m >= 2^20 entries with m / n >= 8,
+ *              else the hybrid plan);
  *              opts->symmetric = 1 promises a symmetric adjacency (every pair in
- *              both rows) and hooks only the entries with col > row
+ *              both rows): the Atomic-Hook then skips entries with col < row
  * Synchronous on `stream` (NULL = null stream) unless opts->no_sync = 1 (as
  * for cc_labels_ex).  A malformed row_ptr or a column id outside [0, n)
  * returns CC_ERR_RANGE (checked on the device). */

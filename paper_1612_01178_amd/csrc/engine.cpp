@@ -187,10 +187,12 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     // 0.99 atomic-free rounds; 1237 x 1001 grid 83 us against 186 atomic-free
     // rounds; R-MAT 20, m = 2^22 262 us; uniform n = 65,536, m = 524,672 60
     // against 85), unless the call sets an option of the rounds.  CSR input
-    // has no atomic-free rounds: its large sparse inputs take the CSR hybrid
-    // (grid as CSR 0.73 ms against 1.47 Atomic-Hook), the rest the Atomic-Hook.
+    // likewise, without rounds; its filtered plan finds the giant with two
+    // neighbours per row and wins from 2^20 entries (R-MAT 16, m = 1.4 M: 71 us
+    // against 112 hybrid; R-MAT 15, m = 0.8 M: 86 against 88; R-MAT 13,
+    // m = 0.6 M: 97 against 85).
     const bool large = m >= (int64_t(1) << 22);
-    const bool dense_large = m >= int64_t(1) << (input == kInputCsr ? 22 : 21) &&
+    const bool dense_large = m >= int64_t(1) << (input == kInputCsr ? 20 : 21) &&
                              n > 0 && m >= 8 * (int64_t)n;
     bool auto_filtered = false;
     if (op.hook == CC_HOOK_AUTO) {
@@ -198,7 +200,7 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
             p.hook = CC_HOOK_ATOMIC;
             auto_filtered = dense_large && op.filter != CC_FILTER_OFF;
         } else if (!allow_plain) {
-            p.hook = large ? CC_HOOK_HYBRID : CC_HOOK_ATOMIC;
+            p.hook = CC_HOOK_HYBRID;
         } else if (large || op.no_sync == 1 ||
                    (op.max_rounds == 0 && op.rounds_per_check == 0 && op.compact_threshold == 0)) {
             p.hook = CC_HOOK_HYBRID;
@@ -725,7 +727,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
 // 318 us against 352 with the contracting hook).
 int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                        const Plan& p, char* ws, const Layout& L, hipStream_t s, Timer& tm,
-                       cc_stats* st, Ctrl* host) {
+                       cc_stats* st, Ctrl* host, bool init = true) {
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
     const int grid_cap = device_cu_count() * 8;
     const uint32_t far_limit = (uint32_t)(m / 8);  // win_far counts pairs of entries
@@ -733,7 +735,7 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     const bool longer = m >= kHybridLong;
     // uniform lists of fewer entries than vertices have no large component
     const int rounds = n <= kHybridRoundsMaxN && 10 * m >= 11 * (int64_t)n ? kHybridRounds : 0;
-    TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
+    if (init) TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, far_limit, s));
     TIMED(kPhaseCompress, launch_mj1(pi, n, longer ? far : nullptr, s, true, far_limit));
     for (int r = 0; r < rounds; ++r) {
@@ -1180,15 +1182,23 @@ int32_t stream_impl(int32_t n, const int32_t* hu, const int32_t* hv, int64_t m, 
 }
 
 // ---------------------------------------------------------------------- CSR input
-// Same plan as a pair list of m entries (segments of the col[] array, each
-// followed by a Multi-Jump; with the giant filter the growing super-segments
-// of enqueue_atomic); the first endpoint of an entry is its row.  The hybrid
-// plan is the pair-list one: an atomic-free Hook pass over all entries, a
-// Multi-Jump, the still-active entries compacted to root pairs, then the
-// Atomic-Hook (with path halving) over those pairs and a Multi-Jump; the
-// first pass joins nearly everything with plain stores, and the Atomic-Hook
-// restores the links it overwrote (grid as CSR 0.73 ms; 0.77 ms with an
-// Atomic-Hook pass over all entries instead of the compaction).
+// The first endpoint of an entry is its row.  The hybrid plan writes the row
+// of every entry once (4 bytes per entry written and read) and is then the
+// pair-list plan; a second set of kernels that find rows on the fly was slower
+// (2048^2 grid: 346 us, 200 now) and only went beyond 2^22 entries (50 x 4,000
+// grid: 354, 75 now).
+//
+// The automatic filtered plan hooks two neighbours of every row first: the
+// first one in the initial tree, the last one by an atomic-free round and a
+// contracting hook.  That finds the giant whatever the order of the rows (of
+// R-MAT 20's 646,362 vertices with an edge all but 200 or so are in it), so
+// one filtered pass over all entries follows: R-MAT 20, 2^25 entries 147 us
+// against 466 for growing segments of rows, whose first ones contend for the
+// hubs; a split pass with a bitmap refresh in between 193.
+//
+// With options of its own (segments, filter_after, ...) the Atomic-Hook runs
+// segments of the col[] array, each followed by a Multi-Jump; with the giant
+// filter the growing super-segments of enqueue_atomic.
 int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t m, int32_t* out,
                  const cc_options* opts, hipStream_t s, cc_stats* st) {
     if (n < 0 || m < 0) return fail(CC_ERR_ARG, "n < 0 or m < 0");
@@ -1203,27 +1213,53 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
     if (st) {
         std::memset(st, 0, sizeof *st);
         st->hook = p.hook;
-        st->segments = p.hook == CC_HOOK_ATOMIC ? p.segments : 0;
         st->giant_label = -1;
     }
     if (n == 0) {
         if (m > 0) return fail(CC_ERR_RANGE, "entries in a graph with no vertices");
         return CC_OK;
     }
-    const bool filter = p.filter == CC_FILTER_GIANT;
-    const size_t bits_bytes = filter ? align256(((size_t)n + 31) / 32 * 4) : 0;
     PoolEntry* pe = pool_entry(s);
     std::lock_guard<std::mutex> lk(pe->mu);
     rc = ensure_host(pe);
     if (rc != CC_OK) return rc;
-    // the hybrid plan's frontier of root pairs (8 B x m)
-    const size_t frontier_bytes = p.hook == CC_HOOK_HYBRID ? align256((size_t)m * 8) : 0;
-    rc = ensure_dev(pe, 256 + bits_bytes + frontier_bytes);
+    bool tiled = p.hook == CC_HOOK_HYBRID || p.auto_filter;
+    // Workspace: [control block, bitmap or hybrid frontier][first row of each
+    // tile][row of each entry (hybrid) or the sampled pairs (filtered plan)]
+    const Layout L = layout(n, m, p);
+    const size_t bits_bytes = align256(((size_t)n + 31) / 32 * 4);
+    const size_t base = p.hook == CC_HOOK_HYBRID ? L.total : 256 + bits_bytes;
+    const size_t tile_bytes = align256(((size_t)m / kCsrTile + 2) * 4);
+    const size_t row_bytes = align256((p.hook == CC_HOOK_HYBRID ? (size_t)m : (size_t)n) * 4);
+    if (tiled) {
+        const size_t need = base + tile_bytes + (p.auto_filter ? 2 : 1) * row_bytes;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (pe->bytes < need && hipStreamIsCapturing(s, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusNone;
+        }
+        if (cap != hipStreamCaptureStatusNone || ensure_dev(pe, need) != CC_OK) {
+            // No memory for it, or none to be had inside a capture: the
+            // unfiltered Atomic-Hook needs the control block only.
+            (void)hipGetLastError();
+            tiled = p.auto_filter = false;
+            p.hook = CC_HOOK_ATOMIC;
+            p.filter = CC_FILTER_OFF;
+            p.segments = (int)std::min<int64_t>(std::min<int64_t>(1 << 20, round_ratio(m, n)), m / 4 + 1);
+        }
+    }
+    const bool filter = p.filter == CC_FILTER_GIANT;
+    rc = ensure_dev(pe, 256 + (filter ? bits_bytes : 0));
     if (rc != CC_OK) return rc;
+    if (st) {
+        st->hook = p.hook;
+        st->segments = p.hook == CC_HOOK_ATOMIC ? p.segments : 0;
+    }
     char* ws = static_cast<char*>(pe->dev);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
     uint32_t* bits = filter ? reinterpret_cast<uint32_t*>(ws + 256) : nullptr;
-    int2* F = frontier_bytes ? reinterpret_cast<int2*>(ws + 256 + bits_bytes) : nullptr;
+    int32_t* tile_row = tiled ? reinterpret_cast<int32_t*>(ws + base) : nullptr;
+    int32_t* rows = tiled ? reinterpret_cast<int32_t*>(ws + base + tile_bytes) : nullptr;
     const int S = p.segments;
     auto bound = [&](int64_t i) -> int64_t { return i >= S ? m : segment_start(m, i, S); };
     Timer tm;
@@ -1231,25 +1267,39 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
     tm.s = s;
     const Post post = {ctrl, p.no_sync ? nullptr : pe->host_ctrl};
     int hooks = 0, jumps = 0;
-    TIMED(kPhaseOther, launch_init(out, n, ctrl, s));
-    TIMED(kPhaseOther, launch_csr_check(row_ptr, n, m, ctrl, s));
+    if (tiled) {
+        TIMED(kPhaseOther, launch_init(out, 1, ctrl, s));
+    } else {
+        TIMED(kPhaseOther, launch_init(out, n, ctrl, s));
+        TIMED(kPhaseOther, launch_csr_check(row_ptr, n, m, ctrl, s));
+    }
     if (p.hook == CC_HOOK_HYBRID) {
-        TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, 0, m, out, ctrl, nullptr, p.symmetric,
-                                           false, /*plain=*/true, s));
-        TIMED(kPhaseCompress, launch_mj_deep(out, n, s));  // the pass leaves chains
-        // the entries still active, as root pairs, then the Atomic-Hook over
-        // those pairs (as the pair-list hybrid plan)
-        TIMED(kPhaseHook, launch_compact_csr(row_ptr, col, n, m, out, F, &ctrl->count[1],
-                                             p.symmetric, s));
-        TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], m, out, p.halve,
-                                             device_cu_count() * 8, s));
-        TIMED(kPhaseCompress, launch_mj1(out, n, &ctrl->count[1], s, false, 0, post));
+        TIMED(kPhaseOther, launch_csr_prep(row_ptr, col, n, m, ctrl, out, tile_row, nullptr, nullptr, s));
+        TIMED(kPhaseOther, launch_csr_expand(row_ptr, tile_row, n, m, rows, s));
+        cc_stats counts = {};
+        rc = enqueue_hybrid(n, rows, col, m, out, p, ws, L, s, tm, &counts, post.host, /*init=*/false);
+        if (rc != CC_OK) return rc;
+        hooks = counts.hook_launches;
+        jumps = counts.compress_launches;
+    } else if (p.auto_filter) {
+        int32_t* sv = rows + row_bytes / 4;
+        TIMED(kPhaseOther, launch_csr_prep(row_ptr, col, n, m, ctrl, out, tile_row, rows, sv, s));
+        TIMED(kPhaseCompress, launch_mj_deep(out, n, s));
+        TIMED(kPhaseHook, launch_hook_prefix(rows, sv, n, out, n, false, s));
+        TIMED(kPhaseCompress, launch_mj1(out, n, nullptr, s, true));
+        TIMED(kPhaseHook, launch_hook_contract(rows, sv, 0, n, out, n, ctrl, p.halve, s));
+        TIMED(kPhaseCompress, launch_mj1(out, n, nullptr, s, false));
+        TIMED(kPhaseOther, launch_sample_giant(col, m, out, n, ctrl, s));
+        TIMED(kPhaseOther, launch_bitmap(out, n, ctrl, bits, s));
+        TIMED(kPhaseHook, launch_csr_filter(row_ptr, col, n, m, tile_row, out, ctrl, bits, p.halve,
+                                            p.symmetric, s));
+        TIMED(kPhaseCompress, launch_mj(out, n, false, s, post));
         hooks = 3;
-        jumps = 2;
+        jumps = 4;
     } else if (!filter) {
         for (int i = 0; i < S; ++i) {
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(i), bound(i + 1), out, ctrl,
-                                               nullptr, p.symmetric, p.halve, false, s));
+                                               nullptr, p.symmetric, p.halve, s));
             TIMED(kPhaseCompress, launch_mj(out, n, false, s, i + 1 == S ? post : Post{}));
             ++hooks;
             ++jumps;
@@ -1258,7 +1308,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
         const int fa = p.filter_after;
         for (int i = 0; i < fa; ++i) {
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(i), bound(i + 1), out, ctrl,
-                                               nullptr, p.symmetric, p.halve, false, s));
+                                               nullptr, p.symmetric, p.halve, s));
             TIMED(kPhaseCompress, launch_mj(out, n, false, s));
             ++hooks;
             ++jumps;
@@ -1270,7 +1320,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
         while (g < S) {
             const int64_t h = std::min<int64_t>(S, g + step);
             TIMED(kPhaseHook, launch_ahook_csr(row_ptr, col, n, bound(g), bound(h), out, ctrl, bits,
-                                               p.symmetric, p.halve, false, s));
+                                               p.symmetric, p.halve, s));
             TIMED(kPhaseCompress, launch_mj(out, n, false, s, h < S ? Post{} : post));
             ++hooks;
             ++jumps;

@@ -160,16 +160,25 @@ hipError_t launch_ahook_hot(const int32_t* u, const int32_t* v, int64_t begin, i
 
 // CSR adjacency (kernels_csr.hip): Atomic-Hook of entries [begin, end) of
 // col[], the first endpoint of entry i being its row; `bits` non-null applies
-// the giant filter; `sym` hooks only col > row; `plain` runs the atomic-free
-// Hook (Fig. 2) instead (no filter, no halving).
+// the giant filter; `sym` hooks only col > row.
 hipError_t launch_ahook_csr(const int64_t* row_ptr, const int32_t* col, int32_t n, int64_t begin,
                             int64_t end, int32_t* pi, Ctrl* ctrl, const uint32_t* bits, bool sym,
-                            bool halve, bool plain, hipStream_t s);
-// CSR hybrid: the entries whose endpoints' roots differ (pi a forest of stars)
-// as root pairs in fr[0 .. *count) (capacity m; *count accumulated).
-hipError_t launch_compact_csr(const int64_t* row_ptr, const int32_t* col, int32_t n, int64_t m,
-                              const int32_t* pi, int2* fr, uint32_t* count, bool sym,
-                              hipStream_t s);
+                            bool halve, hipStream_t s);
+// CSR by tiles of kCsrTile entries: the check of row_ptr, the initial tree,
+// the row of each tile's first entry (tile_row: tiles + 1 words) and, with su
+// non-null, one pair (su[r], sv[r]) per row (see k_csr_prep).
+constexpr int kCsrTile = 1024;
+constexpr int32_t kCsrLdsBitsMaxN = (kLdsBytes - kCsrTile * 2 * 16) * 8;
+hipError_t launch_csr_prep(const int64_t* row_ptr, const int32_t* col, int32_t n, int64_t m,
+                           Ctrl* ctrl, int32_t* pi, int32_t* tile_row, int32_t* su, int32_t* sv,
+                           hipStream_t s);
+// eu[i] = row of entry i.
+hipError_t launch_csr_expand(const int64_t* row_ptr, const int32_t* tile_row, int32_t n, int64_t m,
+                             int32_t* eu, hipStream_t s);
+// Filtered Atomic-Hook of all entries (unfiltered when ctrl->filter_on is 0).
+hipError_t launch_csr_filter(const int64_t* row_ptr, const int32_t* col, int32_t n, int64_t m,
+                             const int32_t* tile_row, int32_t* pi, Ctrl* ctrl,
+                             const uint32_t* bits, bool halve, bool sym, hipStream_t s);
 // Sets the range bit unless row_ptr[0] == 0, row_ptr[n] == m and row_ptr is
 // non-decreasing.
 hipError_t launch_csr_check(const int64_t* row_ptr, int32_t n, int64_t m, Ctrl* ctrl,

@@ -583,7 +583,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     const uint32_t span = (uint32_t)min<int64_t>((int64_t)slots, (int64_t)n - base);
     bool bad = false;
     const int near = __syncthreads_count(first && (uint32_t)max(a[0], b[0]) - (uint32_t)base < span);
-    if (8 * near < 3 * (int)min<int64_t>(first_end - c0, nthr)) {
+    if (8 * near < 3 * (int)min(first_end - c0, (int64_t)nthr)) {
         for (int64_t sb = c0; sb < c1; sb += step) {
             if (sb > c0 || segments > 1) edge_step_loads<kWinEPT>(gu, gv, sb, c1, step, a, b);
 #pragma unroll
@@ -617,7 +617,7 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
         if (seg > 0) edge_step_loads<kWinEPT>(gu, gv, s0, s1, step, a, b);
         for (int64_t sb = s0; sb < s1; sb += step) {
             edge_step_loads<kWinEPT>(gu, gv, sb + step, s1, step, na, nb);
-            const uint32_t rem = (uint32_t)min<int64_t>(s1 - sb, step);
+            const uint32_t rem = (uint32_t)min(s1 - sb, (int64_t)step);
 #pragma unroll
             for (int j = 0; j < kWinEPT; ++j) {
                 const bool in = tid + j * nthr < rem;

@@ -408,7 +408,7 @@ __global__ __launch_bounds__(1024, 8) void k_mj_local(int32_t* pi, int32_t n) {
     __shared__ int32_t lp[kMjBlock];
     constexpr int kPer = kMjBlock / 1024;
     const int64_t base = (int64_t)blockIdx.x * kMjBlock;
-    const int cnt = (int)min<int64_t>(kMjBlock, (int64_t)n - base);
+    const int cnt = (int)min((int64_t)kMjBlock, (int64_t)n - base);
     auto lds_ld = [&](int i) { return __hip_atomic_load(lp + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
     auto lds_st = [&](int i, int32_t x) { __hip_atomic_store(lp + i, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
 #pragma unroll

@@ -234,3 +234,79 @@ def test_hybrid_plan(dev, n, m):
     with pytest.raises(cc.CCError) as ei:
         cc.labels(put(u, dev), put(v, dev), n)
     assert ei.value.code == cc.CC_ERR_RANGE
+
+
+def to_csr(u, v, n):
+    order = np.argsort(u, kind="stable")
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(u, minlength=n), out=rp[1:])
+    return rp, v[order].astype(np.int32)
+
+
+# The CSR plans' sizes on one side and the other: part of a tile of 1,024
+# entries, one tile, the last hybrid and the first filtered list, the last
+# bitmap in LDS and the first one outside; a ragged end throughout
+@pytest.mark.parametrize("n,m", [(1, 0), (70, 5), (100, 1023), (100, 1024), (5000, 40001),
+                                 (100000, (1 << 20) - 1), (100000, (1 << 20) + 2),
+                                 (1 << 20, (1 << 23) + 3), ((1 << 20) + 1, (1 << 23) + 9)])
+def test_csr_plans(dev, n, m):
+    u, v = graphgen.uniform_pairs(m, n, seed=n + m, stream=0)
+    half = m // 2
+    u2, v2 = np.concatenate([u[:half], v[:half]]), np.concatenate([v[:half], u[:half]])
+    far = n - 1 - n // 4  # rows n // 4 .. are empty but the last: tiles of empty rows
+    lists = {"uniform": (u, v, False), "both orientations": (u2, v2, True),
+             "empty rows": (np.where(u < n // 4, u, n - 1), np.where(v < n // 4, v, far), False),
+             # parts of 8 vertices: no giant, the filter stays off
+             "small parts": (u, (u & ~7) + (v & 7).clip(max=(n - 1) & 7), False)}
+    for name, (a, b, sym) in lists.items():
+        b = np.minimum(b, n - 1).astype(np.int32)
+        want = oracle.labels(a, b, n)
+        rp, col = to_csr(a, b, n)
+        drp = torch.from_numpy(rp).to(dev)
+        for offset in (0, 1):
+            dcol = put(col, dev, offset)
+            for opt in (cc.Options(), cc.Options(path_halving="off"), cc.Options(no_sync=True),
+                        cc.Options(symmetric=sym)):
+                print("csr", n, m, name, offset, opt.no_sync, opt.symmetric, flush=True)
+                out = torch.full((n,), -7, dtype=torch.int32, device=dev)
+                cc.labels_csr(drp, dcol, n, out=out, options=opt)
+                torch.cuda.synchronize()
+                assert np.array_equal(out.cpu().numpy(), want), (name, opt)
+    if m:
+        for at, value in ((0, n), (m // 2, -1), (m - 1, n)):
+            wrong = col.copy()
+            wrong[at] = value
+            with pytest.raises(cc.CCError) as ei:
+                cc.labels_csr(drp, put(wrong, dev), n)
+            assert ei.value.code == cc.CC_ERR_RANGE
+        for at, value in ((0, 1), (n, m - 1), (n // 2, m + 5), (n // 2, -3)):
+            wrong = rp.copy()
+            wrong[at] = value
+            with pytest.raises(cc.CCError) as ei:
+                cc.labels_csr(torch.from_numpy(wrong).to(dev), put(col, dev), n)
+            assert ei.value.code == cc.CC_ERR_RANGE
+
+
+def test_csr_capture_needs_no_memory(dev):
+    """Inside a capture the plans that need more scratch than is there give way
+    to the one that needs none; every replay is right."""
+    n, m = 1 << 19, 3 << 19
+    u, v = graphgen.uniform_pairs(m, n, seed=5, stream=0)
+    want = torch.from_numpy(np.asarray(oracle.labels(u, v, n), dtype=np.int32)).to(dev)
+    rp, col = to_csr(u, v, n)
+    drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+    out = torch.empty(n, dtype=torch.int32, device=dev)
+    stream = torch.cuda.Stream()
+    opt = cc.Options(no_sync=True)
+    with torch.cuda.stream(stream):  # a small call: the stream's smallest scratch
+        cc.labels_csr(torch.zeros(2, dtype=torch.int64, device=dev), dcol[:0], 1, options=opt, stream=stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        cc.labels_csr(drp, dcol, n, out=out, options=opt, stream=stream)
+    for _ in range(3):
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
