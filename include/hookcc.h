@@ -399,8 +399,9 @@ typedef struct cc_graph {
  * descriptors holding device pointers); synchronous on `stream` (NULL = null
  * stream).  Same solvers as cc_labels_batch: graphs of at most
  * CC_BATCH_LDS_MAX_N vertices share one persistent LDS launch, larger ones
- * are each solved in device memory on the same stream, and the call ends
- * with a single synchronisation.  Descriptors may point anywhere (the
+ * (and up to 16 of those with 786,432 entries or more, where they alone would
+ * prolong the LDS launch) are each solved in device memory on the same stream,
+ * and the call ends with a single synchronisation.  Descriptors may point anywhere (the
  * graphs need not be packed).  `opts` as for cc_labels_batch_ex (nullable).
  * Returns CC_OK, CC_ERR_ARG, CC_ERR_RANGE, CC_ERR_NOMEM or CC_ERR_HIP. */
 int32_t cc_labels_list(int32_t count, const cc_graph* graphs, const cc_options* opts, void* stream,
@@ -412,18 +413,18 @@ int32_t cc_labels_list(int32_t count, const cc_graph* graphs, const cc_options* 
  * admitted in arrival order while their HBM footprints fit a budget of
  * cfg->device_bytes.  A request's footprint is 8m bytes of edges, 4n bytes of
  * labels and the device workspace of its solve (256-byte granules), charged
- * whether its arrays are in host or device memory: a request of more than
- * CC_BATCH_LDS_MAX_N vertices brings its own Atomic-Hook workspace (bitmap
- * and vertex table of the giant filter), small requests share a fixed block
- * per worker, charged once at creation.  The server allocates one device
+ * whether its arrays are in host or device memory: a large request, of
+ * more than CC_BATCH_LDS_MAX_N vertices or 786,432 entries, brings its own
+ * workspace (bitmap and vertex table of the giant filter), small requests
+ * share a fixed block per worker, charged once at creation (a request of few
+ * vertices that fits the budget only without a workspace is a small one).  The server allocates one device
  * arena of cfg->device_bytes and carves from it everything it puts on the
  * device: copies of host edges and labels, and the workspaces, so the solves
  * of admitted requests never allocate.  Each of
  * cfg->workers host threads owns one HIP stream and, whenever it is free,
  * solves a wave taken from the head of the queue in arrival order (the
- * cc_labels_list solvers): the longest run of admitted small requests (at
- * most CC_BATCH_LDS_MAX_N vertices, one persistent LDS launch), or a single
- * large request on its own, so small requests never wait for a large one in
+ * cc_labels_list solvers): the longest run of admitted small requests (one
+ * persistent LDS launch), or a single large request on its own, so small requests never wait for a large one in
  * their wave.  Requests that arrive while other waves run join the next
  * wave, and waves overlap on the device.  Times are seconds on the clock of
  * cc_server_clock(). */

@@ -115,6 +115,7 @@ struct Plan {
     bool lds_bits = false;       // hot: the whole giant bitmap in LDS
     bool auto_filter = false;    // the filtered schedule of the automatic choice
     bool prefix = false;         // auto_filter: atomic-free rounds over a prefix come first
+    bool frontier = false;       // hybrid: the entries left are compacted into pairs
 };
 
 // Small lists that the automatic choice gives to one LDS workgroup.  The
@@ -128,10 +129,10 @@ bool fits_lds_single(int64_t n, int64_t m) {
     return n > 0 && n <= 32768 && 2 * n + m <= 131072;
 }
 
-// Hook variants an input form supports: pair lists all of them; CSR input the
-// Atomic-Hook and the hybrid plan (its atomic-free pass needs no frontier);
-// the graph-list path the Atomic-Hook only.
-enum PlanInput { kInputPairs, kInputCsr, kInputAtomicOnly };
+// Hook variants an input form supports: pair lists all of them; CSR input and
+// the large graphs of a list the Atomic-Hook and the hybrid plan; edges that
+// are uploaded in chunks the Atomic-Hook only.
+enum PlanInput { kInputPairs, kInputCsr, kInputGraphList, kInputAtomicOnly };
 
 int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
                   PlanInput input = kInputPairs) {
@@ -196,7 +197,8 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
                              n > 0 && m >= 8 * (int64_t)n;
     bool auto_filtered = false;
     if (op.hook == CC_HOOK_AUTO) {
-        if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large) {
+        if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large ||
+            (input == kInputGraphList && m >= (int64_t(1) << 32))) {
             p.hook = CC_HOOK_ATOMIC;
             auto_filtered = dense_large && op.filter != CC_FILTER_OFF;
         } else if (!allow_plain) {
@@ -214,6 +216,8 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     } else {
         p.hook = op.hook;
     }
+    // the scratch of a graph in a list does not grow with its entries
+    p.frontier = p.hook == CC_HOOK_HYBRID && m >= kHybridLong && input != kInputGraphList;
     if ((!allow_plain && p.hook == CC_HOOK_PLAIN) || (!allow_hybrid && p.hook == CC_HOOK_HYBRID))
         return fail(CC_ERR_ARG, "the atomic-free Hook is not available here");
     int64_t s = op.segments;
@@ -329,7 +333,7 @@ Layout layout(int32_t n, int64_t m, const Plan& p) {
         L.f1 = off;
         off += align256((size_t)m * 8);
     }
-    if (p.hook == CC_HOOK_HYBRID && m >= kHybridLong) {  // one frontier, written once
+    if (p.frontier) {  // written once
         L.cap = m;
         L.f0 = L.f1 = off;
         off += align256((size_t)m * 8);
@@ -732,7 +736,7 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     const int grid_cap = device_cu_count() * 8;
     const uint32_t far_limit = (uint32_t)(m / 8);  // win_far counts pairs of entries
     const uint32_t* far = &ctrl->win_far;
-    const bool longer = m >= kHybridLong;
+    const bool longer = p.frontier;
     // uniform lists of fewer entries than vertices have no large component
     const int rounds = n <= kHybridRoundsMaxN && 10 * m >= 11 * (int64_t)n ? kHybridRounds : 0;
     if (init) TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
@@ -1372,12 +1376,42 @@ int32_t lds_segments(int64_t m, int64_t n, int32_t cap) {
     return cap > 0 ? std::min(r, cap) : r;
 }
 
+// How many of the LDS graphs, largest first, a list's solve gives to the
+// device-memory path instead.  One workgroup takes ~0.28 us per 1,000 entries
+// (n = 65,536, m = 1.3 M: 384 us), and a few graphs with many entries keep the
+// launch from ending while the other CUs idle; the device-memory path takes
+// them one after the other, ~80 us each.  The count with the least sum of both
+// (at most 16 graphs of kListAloneM entries and more).
+template <class GraphAt>
+int32_t alone_count(const std::vector<int32_t>& small, GraphAt&& graph_at) {
+    constexpr double kUsPerEntry = 2.8e-4, kDeviceUs = 80.0;
+    if (small.empty() || graph_at(small[0]).m < kListAloneM) return 0;
+    double rest = 0;
+    for (int32_t g : small) rest += kUsPerEntry / 256 * (double)graph_at(g).m;
+    int32_t best = 0;
+    double least = 1e30, device = 0;
+    for (int32_t k = 0; k <= 16; ++k) {
+        const double next = k < (int32_t)small.size() ? kUsPerEntry * (double)graph_at(small[k]).m : 0;
+        const double cost = device + std::max(next, rest);
+        if (cost < least) {
+            least = cost;
+            best = k;
+        }
+        if (k == (int32_t)small.size() || graph_at(small[k]).m < kListAloneM) break;
+        device += kDeviceUs;
+        rest -= next / 256;
+    }
+    return best;
+}
+
 // The graph-list solve over any graph accessor: graph_at(g) returns graph g
 // as a cc_graph (the caller's array, or one computed from batch offsets, so a
 // batch never materialises a list).  Small graphs (n <= CC_BATCH_LDS_MAX_N)
 // go to one persistent LDS launch whose workgroups take them largest first;
-// every larger graph gets the device-memory Atomic-Hook solve with its own
-// control block.  Everything is enqueued on `s`; the call ends with one
+// every larger graph, and the few that alone would prolong that launch
+// (alone_count), get a device-memory solve with its own control block: the
+// filtered plan where dense, else the hybrid plan without its frontier (R-MAT
+// 17, m = 1.05 M: 8 Atomic-Hook segments before).  Everything is enqueued on `s`; the call ends with one
 // synchronisation, after which the LDS launch's pinned status word and the
 // large graphs' control blocks (posted by their last launches) are read.
 template <class GraphAt>
@@ -1447,27 +1481,48 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
         for (size_t i = 0; i < k; ++i) sorted[start[cls[i]]++] = small[i];
         small.swap(sorted);
     }
-    const int32_t ns = (int32_t)small.size();
-    if (lds_block == 0) lds_block = batch_block(ns, (int32_t)maxn_small);
-    const int32_t nl = (int32_t)large.size();
-    std::vector<Plan> plans(nl);
-    std::vector<size_t> region_off(nl, 0);
-    std::vector<Layout> layouts(nl);
-    // Workspace: the LDS launch's queue counters, its descriptors right after
-    // (one copy from the staging buffer uploads both and clears the counters),
-    // then the large graphs' control blocks and their regions.
+    // The workspace of a solve that gives the first `moved` of the small graphs
+    // to the device-memory path: the LDS launch's queue counters, its
+    // descriptors right after (one copy from the staging buffer uploads both
+    // and clears the counters), then the large graphs' control blocks and
+    // their regions.
+    const int32_t nl0 = (int32_t)large.size();
+    const bool by_rule = ph == CC_HALVE_AUTO && lds_block == 0 && (!opts || opts->segments == 0);
+    int32_t moved = by_rule ? alone_count(small, graph_at) : 0;
+    int32_t ns, nl;
+    std::vector<Plan> plans;
+    std::vector<size_t> region_off;
+    std::vector<Layout> layouts;
     const size_t desc_off = kQueueBytes;
-    const size_t desc_bytes = align256((size_t)ns * sizeof(GraphDesc));
-    const size_t lctrl_off = desc_off + desc_bytes;
-    size_t off = lctrl_off + align256((size_t)nl * sizeof(Ctrl));
-    for (int32_t i = 0; i < nl; ++i) {
-        const cc_graph G = graph_at(large[i]);
-        int32_t rc = make_plan(G.n, G.m, nullptr, plans[i], kInputAtomicOnly);
-        if (rc != CC_OK) return rc;
-        layouts[i] = layout(G.n, G.m, plans[i]);  // its control block is lctrls[i] instead
-        region_off[i] = off;
-        off += align256(layouts[i].total);
+    size_t desc_bytes, lctrl_off, off;
+    while (true) {
+        ns = (int32_t)small.size() - moved;
+        nl = nl0 + moved;
+        large.insert(large.end(), small.begin(), small.begin() + moved);
+        plans.assign(nl, Plan());
+        region_off.assign(nl, 0);
+        layouts.assign(nl, Layout());
+        desc_bytes = align256((size_t)ns * sizeof(GraphDesc));
+        lctrl_off = desc_off + desc_bytes;
+        off = lctrl_off + align256((size_t)nl * sizeof(Ctrl));
+        for (int32_t i = 0; i < nl; ++i) {
+            const cc_graph G = graph_at(large[i]);
+            int32_t rc = make_plan(G.n, G.m, nullptr, plans[i], kInputGraphList);
+            if (rc != CC_OK) return rc;
+            layouts[i] = layout(G.n, G.m, plans[i]);  // its control block is lctrls[i] instead
+            region_off[i] = off;
+            off += align256(layouts[i].total);
+        }
+        if (moved == 0 || !workspace || ws_bytes >= off) break;
+        large.resize(nl0);  // a workspace sized for the LDS launch alone
+        moved = 0;
     }
+    if (moved) {
+        small.erase(small.begin(), small.begin() + moved);
+        maxn_small = 0;
+        for (int32_t g : small) maxn_small = std::max<int64_t>(maxn_small, graph_at(g).n);
+    }
+    if (lds_block == 0) lds_block = batch_block(ns, (int32_t)maxn_small);
     if (ws_needed) {  // size query only
         *ws_needed = off;
         return CC_OK;
@@ -1524,9 +1579,13 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
         }
         for (int32_t i = 0; i < nl; ++i) {
             const cc_graph G = graph_at(large[i]);
-            int32_t r2 = enqueue_atomic(G.n, G.edges_u, G.edges_v, G.m, G.out_label, plans[i],
-                                        &lctrls[i], filter_bufs(ws + region_off[i], layouts[i]),
-                                        s, tm, nullptr, &pe->host_ctrl[i]);
+            int32_t r2 = plans[i].hook == CC_HOOK_HYBRID
+                             ? enqueue_hybrid(G.n, G.edges_u, G.edges_v, G.m, G.out_label, plans[i],
+                                              reinterpret_cast<char*>(&lctrls[i]), layouts[i], s, tm,
+                                              nullptr, &pe->host_ctrl[i])
+                             : enqueue_atomic(G.n, G.edges_u, G.edges_v, G.m, G.out_label, plans[i],
+                                              &lctrls[i], filter_bufs(ws + region_off[i], layouts[i]),
+                                              s, tm, nullptr, &pe->host_ctrl[i]);
             if (r2 != CC_OK) return r2;
         }
         return CC_OK;

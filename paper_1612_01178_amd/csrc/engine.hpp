@@ -23,6 +23,13 @@ size_t workspace_bytes_impl(int32_t n, int64_t m, const cc_options* opts);
 int32_t labels_noalloc_impl(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
                             int32_t* out, const cc_options* opts, hipStream_t s, cc_stats* st);
 
+// Fewest entries with which a graph of at most CC_BATCH_LDS_MAX_N vertices may
+// leave the LDS launch for the device-memory path (bursts of 24 graphs of 2^10
+// to 2^16 vertices through the server: 566 us against 718 from 2^19 and 827
+// without, another 653, 680 and 747; 32 graphs of up to 2^14 vertices and 2^19
+// entries 455, 465 and 476).
+constexpr int64_t kListAloneM = int64_t(3) << 18;
+
 // Independent graphs given by descriptors (device arrays); synchronous on s.
 // opts (nullable): `segments` (per-graph segment cap of the LDS solver),
 // `path_halving` (in the LDS climb) and `graph` are used.  `workspace`

@@ -1,9 +1,9 @@
 // Continuous-batching request server for connected-components queries.
 //
 // Admission by HBM footprint.  Every request is charged 8m bytes of edges,
-// 4n bytes of labels and the device workspace its solve takes (a request
-// above CC_BATCH_LDS_MAX_N vertices: its own Atomic-Hook workspace, sized by
-// the graph-list solver; small requests: nothing beyond a fixed block per
+// 4n bytes of labels and the device workspace its solve takes (a large request,
+// above CC_BATCH_LDS_MAX_N vertices or kListAloneM entries: its own workspace,
+// sized by the graph-list solver; small requests: nothing beyond a fixed block per
 // worker, set aside at creation) against a budget of `device_bytes`, whether
 // its arrays live in host or device memory.  A request is admitted, in
 // arrival order, only while the charges of all admitted requests fit the
@@ -205,7 +205,7 @@ void worker_main(cc_server* S, int32_t index) {
                 int64_t edges = 0;
                 while (!S->pending.empty() && (int32_t)wave.size() < S->cfg.max_batch) {
                     Request* r = S->pending.front();
-                    const bool large = r->n > CC_BATCH_LDS_MAX_N;
+                    const bool large = r->ws_bytes > 0;
                     if (!wave.empty() && (large || edges + r->m > S->cfg.max_batch_edges)) break;
                     if (r->charge > S->budget - S->small_ws * S->cfg.workers) {
                         // can never fit, even with nothing else admitted
@@ -350,7 +350,7 @@ int32_t cc_server_submit_on(cc_server* S, int32_t n, const int32_t* edges_u,
     r->v = edges_v;
     r->out = out_label;
     r->flags = flags;
-    if (n > CC_BATCH_LDS_MAX_N) {
+    if (n > CC_BATCH_LDS_MAX_N || (n > 0 && m >= kListAloneM)) {
         // the workspace the graph-list solver takes for this graph alone
         cc_graph G;
         std::memset(&G, 0, sizeof G);
@@ -363,6 +363,11 @@ int32_t cc_server_submit_on(cc_server* S, int32_t n, const int32_t* edges_u,
         if (rc != CC_OK) return rc;
     }
     r->charge = edge_bytes(*r) + label_bytes(*r) + r->ws_bytes;
+    if (n <= CC_BATCH_LDS_MAX_N && r->charge > S->budget - S->small_ws * S->cfg.workers) {
+        // fits the budget, if at all, without a workspace: one of the small
+        r->charge -= r->ws_bytes;
+        r->ws_bytes = 0;
+    }
     const bool device_arrays = (m > 0 && !(flags & CC_REQ_HOST_EDGES)) ||
                                (n > 0 && !(flags & CC_REQ_HOST_LABELS));
     if (device_arrays) {

@@ -310,3 +310,45 @@ def test_csr_capture_needs_no_memory(dev):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+# Graphs of a list that leave the LDS launch: none, one, two among small ones,
+# and the sparse and dense graphs above the LDS's vertices
+@pytest.mark.parametrize("sizes", [[(65536, 786431), (300, 900)],
+                                   [(65536, 786432), (300, 900), (40, 0)],
+                                   [(1, 800000), (2000, 1 << 20), (5000, 700000), (65536, 65536)],
+                                   [(65536, 1 << 21), (65537, 65537), (65537, (1 << 21) + 1),
+                                    (1 << 20, 1 << 22), (70000, 0), (0, 0)]])
+def test_list_routes(dev, sizes):
+    lists = [graphgen.uniform_pairs(m, max(n, 1), seed=n + m, stream=0) for n, m in sizes]
+    want = [oracle.labels(u, v, n) for (u, v), (n, m) in zip(lists, sizes)]
+    graphs = [(put(u, dev), put(v, dev), n) for (u, v), (n, m) in zip(lists, sizes)]
+    for opt in (cc.Options(), cc.Options(segments=1), cc.Options(block=512), cc.Options(path_halving="off")):
+        print("list", sizes, opt.segments, opt.block, flush=True)
+        for got, lab in zip(cc.labels_list(graphs, options=opt), want):
+            assert np.array_equal(got.cpu().numpy(), lab), opt
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    for rep in range(3):
+        got = cc.labels_list(graphs, options=cc.Options(graph=True), stream=stream)
+        for g, lab in zip(got, want):
+            assert np.array_equal(g.cpu().numpy(), lab), rep
+    # room for every request's edges and labels and little more: workspaces
+    # are waited for or done without
+    need = max(8 * m + 4 * n for n, m in sizes)
+    for extra in (200 << 10, 64 << 20):
+        with cc.Server(device_bytes=need + extra, workers=2, max_batch=8) as srv:
+            tickets = [srv.submit(u, v, n) for u, v, n in graphs if n <= 65536 or extra > 1 << 20]
+            kept = [lab for lab, (u, v, n) in zip(want, graphs) if n <= 65536 or extra > 1 << 20]
+            for t, lab in zip(tickets, kept):
+                got, info = srv.wait(t)
+                assert np.array_equal(got.cpu().numpy(), lab)
+    for i, (n, m) in enumerate(sizes):
+        if m:
+            bad = lists[i][1].copy()
+            bad[m - 1] = n
+            wrong = list(graphs)
+            wrong[i] = (graphs[i][0], put(bad, dev), n)
+            with pytest.raises(cc.CCError) as ei:
+                cc.labels_list(wrong)
+            assert ei.value.code == cc.CC_ERR_RANGE
