@@ -156,13 +156,17 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     p.symmetric = op.symmetric == 1;
     if (op.hot_cache < CC_HOT_AUTO || op.hot_cache > CC_HOT_VERTEX)
         return fail(CC_ERR_ARG, "unknown cc_options.hot_cache");
-    // Hot cache: the whole bitmap where it fits the LDS (n <= 1,310,720),
-    // then the vertex table where every id fits its tags (n <= 255 *
+    // Hot cache: the whole bitmap where it fits the LDS (n <= 1,310,720), its
+    // first 1,310,720 vertices where that is half of them at least (R-MAT 21,
+    // m = 50 M: 495 us against 526 with the vertex table; uniform n = 2^21,
+    // m = 33 M: 766 and 854; but R-MAT 22: 742 and 633, and above, where few
+    // vertices are in the first part, R-MAT 23: 1,511 and 1,119), then the
+    // vertex table where every id fits its tags (n <= 255 *
     // 81,920; R-MAT 24: 3.9 ms against 4.52 with 32,768 word slots), else the
     // word table.
     const bool vert = op.hot_cache == CC_HOT_VERTEX ||
                       (op.hot_cache == CC_HOT_AUTO && n <= (int64_t)kVertTagNone * kVertSets);
-    p.lds_bits = op.hot_cache == CC_HOT_AUTO && n <= kLdsBitsMaxN;
+    p.lds_bits = op.hot_cache == CC_HOT_AUTO && n <= kLdsPartMaxN;
     p.hot_slots = op.hot_cache == CC_HOT_ON ? 16384 : vert ? kVertSlots : 32768;
     if (op.path_halving < CC_HALVE_AUTO || op.path_halving > CC_HALVE_OFF)
         return fail(CC_ERR_ARG, "unknown cc_options.path_halving");

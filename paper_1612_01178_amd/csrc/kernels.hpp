@@ -135,9 +135,11 @@ constexpr int64_t kVertScratchWords = (int64_t)kVPartsMax * kVPartCap + 2LL * kV
 hipError_t launch_hot_vprepare(const int32_t* u, const int32_t* v, int64_t m, int32_t n,
                                uint32_t* scratch, uint8_t* table, hipStream_t s);
 // Filtered Atomic-Hook of entries [begin, end), membership tests answered in
-// LDS from the whole bitmap (n <= kLdsBitsMaxN) or from the vertex table.
+// LDS from the bitmap (n <= kLdsPartMaxN; all of it up to kLdsBitsMaxN, then
+// its first kLdsBitsMaxN vertices) or from the vertex table.
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int32_t kLdsBitsMaxN = kLdsBytes * 8;  // 1,310,720
+constexpr int32_t kLdsPartMaxN = 2 * kLdsBitsMaxN;
 hipError_t launch_filter_bits(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
                               int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, bool halve,
                               bool sym, hipStream_t s);

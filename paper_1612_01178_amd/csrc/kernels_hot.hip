@@ -457,10 +457,16 @@ __device__ __forceinline__ void load_step(const int32_t* __restrict__ p, int64_t
 //   kFilterVertex  the vertex table (a slot's tag kept only while its member
 //                  flag is set): 1 when set x mod kVertSets holds the tag
 //                  x / kVertSets, else the bitmap in device memory decides.
-//                  Bound by the L2 rate of those tests (R-MAT 24 3.46 ms with
-//                  the kept entries hooked in place, 3.16 with the queue;
-//                  R-MAT 21 616 and 544 us).
-enum { kFilterBits = 0, kFilterVertex = 1 };
+//                  Bound by the address and L2 rate of those tests (R-MAT 24
+//                  3.46 ms with the kept entries hooked in place, 3.24 with
+//                  the queue, 3.12 with the queue passed by where all entries
+//                  of a wave's step are inside the giant);
+//   kFilterPart    the bitmap of the first kLdsBitsMaxN vertices; the others'
+//                  tests go to device memory (R-MAT 21, 50 M entries: 526 us
+//                  with the vertex table, 481).
+// Only lanes whose test is not answered in LDS load: a load of a fixed word by
+// the other lanes costs more than the branch (R-MAT 24 3.50 ms).
+enum { kFilterBits = 0, kFilterVertex = 1, kFilterPart = 2 };
 
 template <int EPT, int MODE>
 __global__ __launch_bounds__(1024) void k_filter(const int32_t* __restrict__ eu,
@@ -473,8 +479,8 @@ __global__ __launch_bounds__(1024) void k_filter(const int32_t* __restrict__ eu,
     const bool filter = ctrl->filter_on != 0;
     const int32_t g = ctrl->giant;
     if (filter) {
-        if (MODE == kFilterBits) {
-            const uint32_t words = ((uint32_t)n + 31) / 32;
+        if (MODE != kFilterVertex) {
+            const uint32_t words = ((uint32_t)min(n, kLdsBitsMaxN) + 31) / 32;
             for (uint32_t i = threadIdx.x * 4; i < words; i += blockDim.x * 4) {
                 if (i + 3 < words) {
                     *reinterpret_cast<v4i*>(lds + i) = *reinterpret_cast<const v4i*>(bits + i);
@@ -502,40 +508,64 @@ __global__ __launch_bounds__(1024) void k_filter(const int32_t* __restrict__ eu,
     }
     const uint16_t* lset = reinterpret_cast<const uint16_t*>(lds);
     const int64_t tile = (int64_t)blockDim.x * EPT;
-    bool bad = false;
+    uint32_t top = 0;  // largest endpoint seen
     PairQueue q;
     for (int64_t t0 = begin + (int64_t)blockIdx.x * tile; t0 < end; t0 += (int64_t)gridDim.x * tile) {
         int32_t a[EPT], b[EPT];
         load_step<EPT>(eu, t0, end, vec, a);
         load_step<EPT>(ev, t0, end, vec, b);
+        // bit j of ma, mb: entry j's first, second endpoint is in the giant.
+        // An endpoint out of range is tested as n - 1; `top` reports it.
+        uint32_t ma = 0, mb = 0;
+        if (filter) {
+            uint32_t wa[EPT], wb[EPT];
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) {
+                const uint32_t xa = min((uint32_t)a[j], (uint32_t)n - 1), xb = min((uint32_t)b[j], (uint32_t)n - 1);
+                if (MODE == kFilterBits) {
+                    wa[j] = lds[xa >> 5] >> (xa & 31);
+                    wb[j] = lds[xb >> 5] >> (xb & 31);
+                } else if (MODE == kFilterPart) {
+                    const bool hita = xa < (uint32_t)kLdsBitsMaxN, hitb = xb < (uint32_t)kLdsBitsMaxN;
+                    wa[j] = lds[hita ? xa >> 5 : 0u];
+                    wb[j] = lds[hitb ? xb >> 5 : 0u];
+                    if (!hita) wa[j] = bits[xa >> 5];
+                    if (!hitb) wb[j] = bits[xb >> 5];
+                    wa[j] >>= xa & 31;
+                    wb[j] >>= xb & 31;
+                } else {
+                    // a tag of kVertTagNone (the empty marker) or more never hits
+                    const uint32_t sa = lset[xa % kVertSets], sb = lset[xb % kVertSets];
+                    const uint32_t ka = xa / kVertSets, kb = xb / kVertSets;
+                    const bool hita = ka < kVertTagNone && ((sa & 0xffu) == ka || (sa >> 8) == ka);
+                    const bool hitb = kb < kVertTagNone && ((sb & 0xffu) == kb || (sb >> 8) == kb);
+                    wa[j] = wb[j] = 1;
+                    if (!hita) wa[j] = bits[xa >> 5] >> (xa & 31);
+                    if (!hitb) wb[j] = bits[xb >> 5] >> (xb & 31);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) {
+                ma |= (wa[j] & 1) << j;
+                mb |= (wb[j] & 1) << j;
+            }
+        }
+        // Nearly every step is inside the giant altogether.
+        constexpr uint32_t kAll = (1u << EPT) - 1;
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) top = max(top, max((uint32_t)a[j], (uint32_t)b[j]));
+        if (!__any((ma & mb) != kAll)) continue;
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
-            const uint32_t xa = (uint32_t)a[j], xb = (uint32_t)b[j];
-            const bool in = max(xa, xb) < (uint32_t)n;
-            bad |= !in;
-            uint32_t ba = 0, bb = 0;
-            if (filter && MODE == kFilterBits) {
-                ba = lds[in ? xa >> 5 : 0u] >> (xa & 31) & 1;
-                bb = lds[in ? xb >> 5 : 0u] >> (xb & 31) & 1;
-            } else if (filter && in) {
-                // a tag of kVertTagNone (the empty marker) or more never hits
-                const uint32_t sa = lset[xa % kVertSets], sb = lset[xb % kVertSets];
-                const uint32_t ka = xa / kVertSets, kb = xb / kVertSets;
-                const bool hita = ka < kVertTagNone && ((sa & 0xffu) == ka || (sa >> 8) == ka);
-                const bool hitb = kb < kVertTagNone && ((sb & 0xffu) == kb || (sb >> 8) == kb);
-                uint32_t worda = 1, wordb = 1;
-                if (!hita) worda = __hip_atomic_load(bits + (xa >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> (xa & 31);
-                if (!hitb) wordb = __hip_atomic_load(bits + (xb >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> (xb & 31);
-                ba = worda & 1;
-                bb = wordb & 1;
-            }
-            const bool keep = in && xa != xb && !(ba & bb) && !(sym && a[j] > b[j]);
+            const uint32_t ba = ma >> j & 1, bb = mb >> j & 1;
+            const bool in = max((uint32_t)a[j], (uint32_t)b[j]) < (uint32_t)n;
+            const bool keep = in && a[j] != b[j] && !(ba & bb) && !(sym && a[j] > b[j]);
             // an endpoint in the giant starts its climb at the giant's root
             q.push(keep, ba ? g : a[j], bb ? g : b[j], pi, halve);
         }
     }
     q.flush(pi, halve);
-    if (bad) atomicOr(&ctrl->status, kStatusRange);
+    if (top >= (uint32_t)n) atomicOr(&ctrl->status, kStatusRange);
 }
 
 hipError_t launch_hot_vprepare(const int32_t* u, const int32_t* v, int64_t m, int32_t n,
@@ -578,7 +608,7 @@ static hipError_t filter_dispatch(const int32_t* u, const int32_t* v, int64_t be
     }();
     if (once != hipSuccess) return once;
     const int block = 1024;
-    const size_t lds = MODE == kFilterBits ? ((size_t)n + 127) / 128 * 16 : (size_t)kVertSlots;
+    const size_t lds = MODE == kFilterBits ? ((size_t)n + 127) / 128 * 16 : MODE == kFilterPart ? (size_t)kLdsBytes : (size_t)kVertSlots;
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
     // workgroups that are resident at once: two per CU where the LDS allows
     const int64_t cap = (int64_t)device_cu_count() * (2 * lds <= (size_t)kLdsBytes ? 2 : 1);
@@ -605,6 +635,8 @@ static hipError_t filter_dispatch(const int32_t* u, const int32_t* v, int64_t be
 hipError_t launch_filter_bits(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
                               int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, bool halve,
                               bool sym, hipStream_t s) {
+    if (n > kLdsBitsMaxN)
+        return filter_dispatch<kFilterPart>(u, v, begin, end, pi, n, ctrl, bits, nullptr, halve, sym, s);
     return filter_dispatch<kFilterBits>(u, v, begin, end, pi, n, ctrl, bits, nullptr, halve, sym, s);
 }
 

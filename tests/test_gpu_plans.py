@@ -138,7 +138,8 @@ def test_filtered_plan(dev, scale, m, sym):
         u[at] = keep
 
 
-@pytest.mark.parametrize("n", [160 * 1024 * 8 - 31, 160 * 1024 * 8, 160 * 1024 * 8 + 1])
+@pytest.mark.parametrize("n", [160 * 1024 * 8 - 31, 160 * 1024 * 8, 160 * 1024 * 8 + 1,
+                               320 * 1024 * 8, 320 * 1024 * 8 + 1])
 def test_filtered_plan_at_the_lds_bitmap_limit(dev, n):
     """Half of the ids joined by a cycle and random chords, the rest in pairs
     or alone: a giant component whose bitmap ends in a partial word."""
