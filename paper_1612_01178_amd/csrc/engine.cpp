@@ -741,8 +741,14 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     const uint32_t far_limit = (uint32_t)(m / 8);  // win_far counts pairs of entries
     const uint32_t* far = &ctrl->win_far;
     const bool longer = p.frontier;
-    // uniform lists of fewer entries than vertices have no large component
-    const int rounds = n <= kHybridRoundsMaxN && 10 * m >= 11 * (int64_t)n ? kHybridRounds : 0;
+    // Uniform lists of fewer entries than vertices have no large component; on
+    // denser lists one round more leaves few enough roots (uniform n = 65,536,
+    // m = 1.5 M: 92 us with one, 122 with two; R-MAT 17, m = 1.8 M: 121 and 134;
+    // R-MAT 19, m = 3.5 M: 185 and 221; but uniform n = 300,000, m = 2 M: 166 and
+    // 155, n = 65,536, m = 150,000: 92 and 75).
+    const int rounds = n > kHybridRoundsMaxN || 10 * m < 11 * (int64_t)n ? 0
+                       : m >= 6 * (int64_t)n                             ? 1
+                                                                         : kHybridRounds;
     if (init) TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, far_limit, s));
     TIMED(kPhaseCompress, launch_mj1(pi, n, longer ? far : nullptr, s, true, far_limit));

@@ -300,8 +300,12 @@ __global__ __launch_bounds__(256) void k_hook_prefix(const int32_t* __restrict__
             }
         }
 #pragma unroll
-        for (int j = 0; j < kPrefixEPT; ++j)
-            if (a[j] != b[j]) st_rlx(pi + max(a[j], b[j]), min(a[j], b[j]));
+        for (int j = 0; j < kPrefixEPT; ++j) {
+            if (a[j] == b[j]) continue;
+            // many entries meet on a hub's root; most find a smaller id there
+            const int32_t H = max(a[j], b[j]), L = min(a[j], b[j]);
+            if (FIRST || ld_rlx(pi + H) > L) st_rlx(pi + H, L);
+        }
     }
 }
 
