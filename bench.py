@@ -186,7 +186,7 @@ def main():
     traffic = None
     if st.get("hook") == 1:
         alg_bytes = 8.0 * m  # each int32 (u, v) entry read once across the Atomic-Hook launches
-        kernel = "k_ahook_short + k_filter (all Atomic-Hook launches of one solve)"
+        kernel = "k_ahook + k_filter (all Atomic-Hook launches of one solve)"
         if args.hook == "auto" and args.filter == "auto" and args.hot == "auto" and not (
                 args.segments or args.ept or args.block or args.coherent or args.symmetric):
             traffic = measured_traffic(args.workload, "atomic")
@@ -544,6 +544,7 @@ def serving(cc, torch, dev, requests=2000, loads=(0.5, 0.7, 0.9), host_mode=Fals
 # code (comments and blank lines aside) hashes to the value stored in it.
 COUNTER_SOURCES = ("paper_1612_01178_amd/csrc/kernels_core.hip",
                    "paper_1612_01178_amd/csrc/kernels_hot.hip",
+                   "paper_1612_01178_amd/csrc/pair_queue.hpp",
                    "paper_1612_01178_amd/csrc/common.hpp",
                    "paper_1612_01178_amd/csrc/kernels.hpp",
                    "paper_1612_01178_amd/csrc/engine.cpp")

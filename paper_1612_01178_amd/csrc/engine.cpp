@@ -112,7 +112,8 @@ struct Plan {
     bool no_sync = false;    // enqueue only; status read later by cc_stream_status
     uint32_t tau = 0xffffffffu;  // atomic-free Hook: frontier rewrite threshold (1/1000)
     bool lds_single = false;     // one workgroup solves the whole graph in LDS
-    bool lds_bits = false;       // hot: the whole giant bitmap in LDS
+    bool lds_bits = false;       // hot: the giant bitmap in LDS
+    bool table_room = false;     // the workspace has the vertex table's room all the same
     bool auto_filter = false;    // the filtered schedule of the automatic choice
     bool prefix = false;         // auto_filter: atomic-free rounds over a prefix come first
     bool frontier = false;       // hybrid: the entries left are compacted into pairs
@@ -126,7 +127,7 @@ struct Plan {
 // 68 us; n = 8,192, m = 65,536 34 against 80; n = 32,768, m = 65,536 50
 // against 85; n = 65,536, m = 131,072 111 against 76).
 bool fits_lds_single(int64_t n, int64_t m) {
-    return n > 0 && n <= 32768 && 2 * n + m <= 131072;
+    return n > 0 && n <= 32768 && m <= 131072 - 2 * n;
 }
 
 // Hook variants an input form supports: pair lists all of them; CSR input and
@@ -167,6 +168,8 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     const bool vert = op.hot_cache == CC_HOT_VERTEX ||
                       (op.hot_cache == CC_HOT_AUTO && n <= (int64_t)kVertTagNone * kVertSets);
     p.lds_bits = op.hot_cache == CC_HOT_AUTO && n <= kLdsPartMaxN;
+    // a call that asks for the filter itself has been told the table's size
+    p.table_room = op.filter == CC_FILTER_GIANT;
     p.hot_slots = op.hot_cache == CC_HOT_ON ? 16384 : vert ? kVertSlots : 32768;
     if (op.path_halving < CC_HALVE_AUTO || op.path_halving > CC_HALVE_OFF)
         return fail(CC_ERR_ARG, "unknown cc_options.path_halving");
@@ -315,7 +318,7 @@ Layout layout(int32_t n, int64_t m, const Plan& p) {
     if (p.hook == CC_HOOK_ATOMIC && p.filter == CC_FILTER_GIANT) {
         L.bits = off;
         off += align256(((size_t)n + 31) / 32 * 4);
-        if (p.hot && p.lds_bits) {  // nothing but the bitmap
+        if (p.hot && p.lds_bits && !p.table_room) {  // nothing but the bitmap
         } else if (p.hot && p.hot_slots == kVertSlots) {  // selection scratch, byte table
             L.hot_counts = off;
             off += align256((size_t)kVertScratchWords * 4);
@@ -608,8 +611,8 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
                        cc_stats* st, Ctrl* host) {
     uint32_t* bits = fb.bits;
     const bool hot = p.hot && fb.hot_tags != nullptr;
-    const bool vhot = p.hot && fb.vtab != nullptr;
     const bool lds_bits = p.hot && p.lds_bits;
+    const bool vhot = p.hot && !lds_bits && fb.vtab != nullptr;
     const int S = p.segments;
     auto bound = [&](int64_t i) -> int64_t {
         if (i >= S) return m;
@@ -699,7 +702,8 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
             if (to < m && !p.coherent) {
                 // Compress, bitmap refresh and hot-word refresh in one pass
                 TIMED(kPhaseCompress, launch_mj_bitmap(pi, n, ctrl, bits, hot ? fb.hot_tags : nullptr,
-                                                       fb.hot_vals, p.hot_slots, fb.vtab, s));
+                                                       fb.hot_vals, p.hot_slots,
+                                                       vhot ? fb.vtab : nullptr, s));
             } else {
                 TIMED(kPhaseCompress, launch_mj(pi, n, p.coherent, s, to < m ? Post{} : post));
                 if (to < m) TIMED(kPhaseOther, launch_bitmap(pi, n, ctrl, bits, s));
