@@ -333,12 +333,14 @@ hipError_t launch_csr_expand(const int64_t* row_ptr, const int32_t* tile_row, in
 //      in the giant.  What is not inside the giant goes to the wave's queue.
 // Without a giant (filter off) every row counts as outside it.  A tile that
 // spans more than kCsrMaxSpan rows searches row_ptr per entry instead.
-// Persistent; with LDS_BITS (n <= kCsrLdsBitsMaxN) the whole bitmap is in LDS
-// and the pass streams 4 bytes per entry and 8 per row, bound by instruction
-// issue (R-MAT 20, 2^25 entries: 36.5 us, 3.7 TB/s; with tiles of 4,096 entries
-// per workgroup and two barriers each 68; the growing segments with a row
-// search per tile took 387).  Else the tests go to the L2, whose request rate
-// bounds it (R-MAT 22, 10^8 entries: 395 us).
+// Persistent.  ALL (n <= kCsrLdsBitsMaxN): the whole bitmap is in LDS and the
+// pass streams 4 bytes per entry and 8 per row, bound by instruction issue
+// (R-MAT 20, 2^25 entries: 36.5 us, 3.7 TB/s; with tiles of 4,096 entries per
+// workgroup and two barriers each 68; the growing segments with a row search
+// per tile took 387).  Else the first kCsrLdsBitsMaxN vertices' bits are, and
+// the other tests go to the L2, whose request rate bounds them (solves, without
+// any bits in LDS and now: R-MAT 21, 6 * 10^7 entries 374 and 285 us; R-MAT 22,
+// 10^8 entries 790 and 715; R-MAT 24, 3.2 * 10^8 entries 2,033 and 1,957).
 constexpr int kCsrShortRow = 32;
 constexpr int kCsrFilterThreads = 1024;
 constexpr int kCsrEPT = kCsrTile / 64;
@@ -347,7 +349,7 @@ static_assert(kCsrMaxSpan < 65535, "rows of a tile are numbered in 16 bits");
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
-template <bool LDS_BITS, bool VEC>
+template <bool ALL, bool VEC>
 __global__ __launch_bounds__(kCsrFilterThreads) void k_csr_filter(
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t n, int64_t m,
     const int32_t* __restrict__ tile_row, int32_t* pi, Ctrl* ctrl,
@@ -356,22 +358,28 @@ __global__ __launch_bounds__(kCsrFilterThreads) void k_csr_filter(
     const int tid = threadIdx.x, lane = tid & 63;
     // per entry of the wave's tile: 1 + its row's number in the tile, 0 = a row of the giant
     uint16_t* owner = reinterpret_cast<uint16_t*>(lds) + (tid >> 6) * kCsrTile;
-    uint32_t* lbits = lds + kCsrTile / 2 * (kCsrFilterThreads / 64);  // the bitmap (LDS_BITS)
+    uint32_t* lbits = lds + kCsrTile / 2 * (kCsrFilterThreads / 64);  // the bitmap's first part
     const uint32_t on_mask = ctrl->filter_on != 0 ? ~0u : 0u;
     const int32_t g = ctrl->giant;
 #pragma unroll
     for (int k = 0; k < kCsrEPT / 4; ++k) *reinterpret_cast<v2u*>(owner + 256 * k + 4 * lane) = v2u{0, 0};
-    if (LDS_BITS && on_mask) {
-        const uint32_t words = ((uint32_t)n + 31) / 32;
+    if (on_mask) {
+        const uint32_t words = ((uint32_t)min(n, kCsrLdsBitsMaxN) + 31) / 32;
 #pragma unroll 4
         for (uint32_t i = tid * 4; i + 3 < words; i += kCsrFilterThreads * 4)
             *reinterpret_cast<v4i*>(lbits + i) = *reinterpret_cast<const v4i*>(bits + i);
         if (tid < (int)(words & 3)) lbits[(words & ~3u) + tid] = bits[(words & ~3u) + tid];
     }
     __syncthreads();
+    auto word_of = [&](uint32_t x) -> uint32_t {
+        if (ALL) return lbits[x >> 5];
+        const bool near = x < (uint32_t)kCsrLdsBitsMaxN;
+        uint32_t w = lbits[near ? x >> 5 : 0u];
+        if (!near) w = bits[x >> 5];
+        return w;
+    };
     auto in_giant = [&](uint32_t x) -> bool {  // x < n
-        const uint32_t w = LDS_BITS ? lbits[(x >> 5) & on_mask] : bits[(x >> 5) & on_mask];
-        return (w & on_mask) >> (x & 31) & 1;
+        return (word_of(x & on_mask) & on_mask) >> (x & 31) & 1;
     };
     const int64_t tiles = (m + kCsrTile - 1) / kCsrTile;
     bool bad = false;
@@ -482,7 +490,7 @@ __global__ __launch_bounds__(kCsrFilterThreads) void k_csr_filter(
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t y = min((uint32_t)x.c[4 * k + j], (uint32_t)n - 1);
                     top = max(top, (uint32_t)x.c[4 * k + j]);
-                    inside &= (LDS_BITS ? lbits[y >> 5] : bits[y >> 5]) >> (y & 31);
+                    inside &= word_of(y) >> (y & 31);
                 }
                 if (!__any(inside == 0)) continue;
             }
@@ -540,19 +548,21 @@ hipError_t launch_csr_filter(const int64_t* row_ptr, const int32_t* col, int32_t
     auto allow = [](const void* f) {
         return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     };
-    static const hipError_t once[2] = {allow(reinterpret_cast<const void*>(&k_csr_filter<true, false>)),
-                                       allow(reinterpret_cast<const void*>(&k_csr_filter<true, true>))};
-    if (once[0] != hipSuccess) return once[0];
-    if (once[1] != hipSuccess) return once[1];
+    static const hipError_t once[4] = {allow(reinterpret_cast<const void*>(&k_csr_filter<true, false>)),
+                                       allow(reinterpret_cast<const void*>(&k_csr_filter<true, true>)),
+                                       allow(reinterpret_cast<const void*>(&k_csr_filter<false, false>)),
+                                       allow(reinterpret_cast<const void*>(&k_csr_filter<false, true>))};
+    for (hipError_t e : once)
+        if (e != hipSuccess) return e;
     constexpr int kWaves = kCsrFilterThreads / 64;
-    const bool in_lds = n <= kCsrLdsBitsMaxN;
-    const size_t lds = kCsrTile * 2 * kWaves + (in_lds ? ((size_t)n + 127) / 128 * 16 : 0);
+    const bool all = n <= kCsrLdsBitsMaxN;
+    const size_t lds = kCsrTile * 2 * kWaves + ((size_t)std::min(n, kCsrLdsBitsMaxN) + 127) / 128 * 16;
     const int64_t tiles = (m + kCsrTile - 1) / kCsrTile;
     const int64_t cap = (int64_t)device_cu_count() * (2 * lds <= (size_t)kLdsBytes ? 2 : 1);
     const int grid = (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, cap);
     const bool vec = ((uintptr_t)col & 15) == 0 && m >= 4;
-    const auto kernel = in_lds ? (vec ? &k_csr_filter<true, true> : &k_csr_filter<true, false>)
-                               : (vec ? &k_csr_filter<false, true> : &k_csr_filter<false, false>);
+    const auto kernel = all ? (vec ? &k_csr_filter<true, true> : &k_csr_filter<true, false>)
+                            : (vec ? &k_csr_filter<false, true> : &k_csr_filter<false, false>);
     kernel<<<grid, kCsrFilterThreads, lds, s>>>(row_ptr, col, n, m, tile_row, pi, ctrl, bits, halve, sym);
     return hipGetLastError();
 }
