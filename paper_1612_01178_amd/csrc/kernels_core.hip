@@ -1239,12 +1239,15 @@ hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begi
                                 int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
                                 const uint32_t* gate, uint32_t limit) {
     if (end <= begin) return hipSuccess;
-    // Two workgroups per CU; fewer for short lists, where few roots are left
-    // and the workgroups' tables meet on them (uniform n = 150,000, m = 300,000
-    // after one round: 107 us on 64 workgroups, 128 on all).
+    // At most two workgroups per CU, with equal shares of two tiles or more: on
+    // short lists few roots are left and the workgroups' tables meet on them
+    // (uniform n = 150,000, m = 300,000 after one round: 107 us on 64
+    // workgroups, 128 on one per tile; n = 300,000, m = 2 M: 160 us for the
+    // solve with four tiles each, 140 with two; n = 65,536, m = 524,672: 81 and 69).
     const int64_t tiles = (end - begin + kContractTile - 1) / kContractTile;
-    const int64_t most = std::max<int64_t>(64, std::min<int64_t>(tiles / 4, 2 * device_cu_count()));
-    const int64_t grid64 = std::min<int64_t>(tiles, most);
+    const int64_t cap = 2 * (int64_t)device_cu_count();
+    const int64_t share = std::max<int64_t>(2, (tiles + cap - 1) / cap);
+    const int64_t grid64 = std::min<int64_t>(tiles, std::max<int64_t>(64, (tiles + share - 1) / share));
     if (halve)
         k_hook_contract<true><<<(int)grid64, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl, gate, limit);
     else
