@@ -78,6 +78,13 @@ __device__ __forceinline__ uint32_t lds_cas(uint16_t* spi, uint32_t idx, uint32_
     return lds_cas16(spi, idx, expected, desired);
 }
 
+// A Multi-Jump climb of more steps than this stores where it has got to at
+// every further step, so that the vertices of a chain shorten it for each
+// other (a path of 2^15 vertices, whose climbs otherwise walk up to 2^15 levels
+// in each of 16 passes: 17.8 -> 0.12 ms; from the 9th step on, trees of a few
+// dozen levels lost up to 15 %).
+constexpr int kDeepLdsSteps = 64;
+
 // Atomic-Hook in LDS (Fig. 3, top), same steps as the device-memory kernel;
 // with `halve`, a passed non-root H whose grandparent differs from its
 // parent is re-pointed at the grandparent (path halving).  The re-point of a
@@ -187,7 +194,7 @@ __device__ __forceinline__ void solve_graph(T* spi, const GraphDesc& d, bool hal
         }
         __syncthreads();
         // Multi-Jump (Fig. 3, bottom) over the graph's vertices, low ids first.
-        // Each vertex climbs to its root and stores it once (a root stores
+        // Each vertex climbs to its root and stores it (a root stores
         // itself); no hook runs in this phase, so only the stores of other
         // climbers race with it, and each stores an ancestor.  After the last
         // segment the root is the label: it goes to global memory only.
@@ -199,9 +206,14 @@ __device__ __forceinline__ void solve_graph(T* spi, const GraphDesc& d, bool hal
             const bool has_y = y < n;
             uint32_t p1 = lds_ld(spi, x), p2 = lds_ld(spi, has_y ? y : x);
             uint32_t g1 = lds_ld(spi, p1), g2 = lds_ld(spi, p2);
+            int k = 0;
             while (g1 != p1 || g2 != p2) {
                 p1 = g1;
                 p2 = g2;
+                if (++k > kDeepLdsSteps) {
+                    lds_st(spi, x, p1);
+                    lds_st(spi, has_y ? y : x, p2);
+                }
                 g1 = lds_ld(spi, p1);
                 g2 = lds_ld(spi, p2);
             }
@@ -649,9 +661,14 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
             const bool has_y = y < span;
             uint32_t p1 = lds_ld(spi, x), p2 = lds_ld(spi, has_y ? y : x);
             uint32_t g1 = lds_ld(spi, p1), g2 = lds_ld(spi, p2);
+            int k = 0;
             while (g1 != p1 || g2 != p2) {
                 p1 = g1;
                 p2 = g2;
+                if (++k > kDeepLdsSteps) {
+                    lds_st(spi, x, p1);
+                    lds_st(spi, has_y ? y : x, p2);
+                }
                 g1 = lds_ld(spi, p1);
                 g2 = lds_ld(spi, p2);
             }

@@ -1,6 +1,8 @@
 """The automatic plan's paths at the sizes where its rules change and its
 kernels have edges, against the CPU oracle (integer labels with one correct
 answer: every comparison is bit-exact)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -353,3 +355,72 @@ def test_list_routes(dev, sizes):
             with pytest.raises(cc.CCError) as ei:
                 cc.labels_list(wrong)
             assert ei.value.code == cc.CC_ERR_RANGE
+
+
+def band(n, b):
+    """Every vertex and the b ids on either side of it, in the order of the rows."""
+    d = np.array([k for k in range(-b, b + 1) if k], dtype=np.int64)
+    u = np.repeat(np.arange(n), 2 * b)
+    v = u + np.tile(d, n)
+    keep = (v >= 0) & (v < n)
+    return u[keep].astype(np.int32), v[keep].astype(np.int32)
+
+
+def median_us(call, passes=7):
+    call()
+    times = []
+    for _ in range(passes):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        times.append((time.perf_counter() - t) * 1e6)
+    return sorted(times)[passes // 2]
+
+
+# Paths in rising and random order, which leave chains of up to n levels, at
+# the sizes of the LDS solver (32- and 16-bit slots in batches) and of the
+# window rounds.  Regression: the Multi-Jump in LDS walked a chain one load at
+# a time (5 to 340 times as long as the same graph takes with its ids
+# permuted).  4 times is allowed; an exact pass each.
+@pytest.mark.parametrize("what", ["path 1000", "path 32768", "path 50000", "path %d" % (1 << 20),
+                                  "shuffled path 32768", "batch 32768", "batch 60000"])
+def test_chains(dev, what):
+    kind, n = what.rsplit(" ", 1)
+    n = int(n)
+    rng = np.random.default_rng(n)
+    if "band5" in kind:
+        u, v = band(n, 5)
+    else:
+        u, v = np.arange(n - 1, dtype=np.int32), np.arange(1, n, dtype=np.int32)
+    if kind == "falling path":
+        u, v = u[::-1], v[::-1]
+    if kind == "shuffled path":
+        order = rng.permutation(len(u))
+        u, v = u[order], v[order]
+    perm = rng.permutation(n).astype(np.int32)
+    times = []
+    for a, b in ((u, v), (perm[u], perm[v])):
+        if kind.startswith("csr"):
+            rp, col = to_csr(a, b, n)
+            drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+            out = torch.empty(n, dtype=torch.int32, device=dev)
+            call = lambda: cc.labels_csr(drp, dcol, n, out=out)  # noqa: E731
+        elif kind == "batch":
+            count = 5
+            du, dv = put(np.tile(a, count), dev), put(np.tile(b, count), dev)
+            vo, eo = np.arange(count + 1) * n, np.arange(count + 1) * len(a)
+            out = torch.empty(count * n, dtype=torch.int32, device=dev)
+            call = lambda: cc.labels_batch(du, dv, vo, eo, out=out)  # noqa: E731
+        else:
+            du, dv = put(a, dev), put(b, dev)
+            out = torch.empty(n, dtype=torch.int32, device=dev)
+            call = lambda: cc.labels(du, dv, n, out=out)  # noqa: E731
+        for _ in range(5):
+            out.fill_(-1)
+            call()
+            torch.cuda.synchronize()
+            assert int(torch.count_nonzero(out)) == 0, what  # one component each
+        times.append(median_us(call))
+    print("chains", what, times, flush=True)
+    assert times[0] <= 4 * times[1], (what, times)
