@@ -113,6 +113,19 @@ __device__ __forceinline__ int32_t cas_root(int32_t* p, int32_t expected, int32_
 __device__ __forceinline__ void halve_to(int32_t* p, int32_t a) {
     __hip_atomic_store(p, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A Multi-Jump may meet chains (a round over a path or a band in the order of
+// its ids leaves one of up to n levels), which a climb would walk one dependent
+// load at a time, most of it through vertices of other XCDs, whose parents it
+// would see as they were when first loaded.  So on every kDeepSteps-th step a
+// climb stores where it has got to and loads with agent scope: the vertices of
+// a chain shorten it for each other across XCDs, and the distance they cover
+// doubles with every such step (a path of 2^20 vertices, entries shuffled:
+// 5.4 -> 0.13 ms; one of 2^22 in falling order: 26.5 -> 0.31 ms).  Doing so on
+// every step past the 16th costs more than it saves where trees have 20 to 200
+// levels, all climbs meeting near the roots (50^3 lattice, entries shuffled:
+// 104 us, 84 on every 16th).  A vertex is stored by its own thread only.
+constexpr int kDeepSteps = 16;
+
 // A climb re-points on one of every kHalveEvery* of its steps that can
 // re-point (steps 1, 1 + k, 1 + 2k, ...): an agent-scope store goes past
 // the L2, so fewer of them is faster until the trees grow deep enough to

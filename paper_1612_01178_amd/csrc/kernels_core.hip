@@ -387,9 +387,15 @@ __global__ __launch_bounds__(256) void k_mj(int32_t* pi, int32_t n, Post post) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             int32_t q = p[c][j], g = gp[c][j];
+            int steps = 0;
             while (g != q) {
-                st_tree<COH>(pi + base[c] + j, g);
                 q = g;
+                if (++steps % kDeepSteps == 0) {
+                    st_tree<true>(pi + base[c] + j, q);
+                    g = ld_tree<true>(pi + q);
+                    continue;
+                }
+                st_tree<COH>(pi + base[c] + j, q);
                 g = ld_tree<COH>(pi + q);
             }
         }
@@ -479,7 +485,7 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
     // V vertices per thread and pass (v, v + blockDim.x, ...: every load
     // coalesced), their climbs interleaved so that each thread keeps V
     // dependent loads in flight; a finished climb stays on its root, whose
-    // parent is itself.  Each vertex's root is stored once, if it is not
+    // parent is itself.  Each vertex's root is stored at the end, if it is not
     // already its parent.
     const int64_t step = (int64_t)gridDim.x * blockDim.x * V;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x * V + threadIdx.x; v < n; v += step) {
@@ -498,8 +504,21 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
         bool more = false;
 #pragma unroll
         for (int k = 0; k < V; ++k) more |= g[k] != r[k];
+        int steps = 0;
         while (more) {
             more = false;
+            if (++steps % kDeepSteps == 0) {
+#pragma unroll
+                for (int k = 0; k < V; ++k)  // a climb under way: its vertex is below n
+                    if (g[k] != r[k]) st_tree<true>(pi + v + (int64_t)k * blockDim.x, g[k]);
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    r[k] = g[k];
+                    g[k] = ld_tree<true>(pi + r[k]);
+                    more |= g[k] != r[k];
+                }
+                continue;
+            }
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 r[k] = g[k];
@@ -566,11 +585,14 @@ hipError_t launch_mj(int32_t* pi, int32_t n, bool coherent, hipStream_t s, Post 
 // (evenly spread over the list), climbs to the root of its first endpoint, and
 // counts roots in an LDS hash table (open addressing, 2 * S slots).  The most
 // frequent root is the giant label; the filter is switched on when it holds
-// at least 1/8 of the samples.  `again`: nothing to do when it is on already.  Each
-// wave adds up its lanes with the first lane's root before it touches the
-// table (most samples have one root, and a wave's atomics on one slot are
-// served one by one).
+// at least 1/8 of the samples.  `again`: nothing to do when it is on already;
+// no Multi-Jump has run since the last hooks then, and a climb of more than
+// kSampleSteps steps (a chain: up to 1.1 ms on a band of 2^19 vertices) is
+// given up and counts for no component.  Each wave adds up its lanes with the
+// first lane's root before it touches the table (most samples have one root,
+// and a wave's atomics on one slot are served one by one).
 constexpr int kSamples = 1024;
+constexpr int kSampleSteps = 64;
 
 __global__ __launch_bounds__(kSamples) void k_sample(const int32_t* __restrict__ eu, int64_t m,
                                                      double step, const int32_t* pi, int32_t n,
@@ -587,11 +609,18 @@ __global__ __launch_bounds__(kSamples) void k_sample(const int32_t* __restrict__
     keys[tid] = keys[tid + kSamples] = -1;
     cnts[tid] = cnts[tid + kSamples] = 0;
     int32_t r = -1;
-    if ((uint32_t)x < (uint32_t)n)
-        for (int32_t up = x; up != r;) {
+    if ((uint32_t)x < (uint32_t)n) {
+        int32_t up = x;
+        int steps = 0;
+        while (up != r) {
             r = up;
+            if (++steps > kSampleSteps) {
+                r = -1;
+                break;
+            }
             up = ld_rlx(pi + r);
         }
+    }
     __syncthreads();
     const int32_t first = __builtin_amdgcn_readfirstlane(r);
     const uint64_t same = __ballot(r == first);
@@ -758,9 +787,15 @@ __global__ __launch_bounds__(256) void k_mj_bitmap(int32_t* pi, int32_t n, Ctrl*
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             int32_t q = p[c][j], g = gp[c][j];
+            int steps = 0;
             while (g != q) {
-                st_tree<false>(pi + base[c] + j, g);
                 q = g;
+                if (++steps % kDeepSteps == 0) {
+                    st_tree<true>(pi + base[c] + j, q);
+                    g = ld_tree<true>(pi + q);
+                    continue;
+                }
+                st_tree<false>(pi + base[c] + j, q);
                 g = ld_tree<false>(pi + q);
             }
             p[c][j] = q;  // the root

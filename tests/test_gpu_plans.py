@@ -378,13 +378,18 @@ def median_us(call, passes=7):
     return sorted(times)[passes // 2]
 
 
-# Paths in rising and random order, which leave chains of up to n levels, at
-# the sizes of the LDS solver (32- and 16-bit slots in batches) and of the
-# window rounds.  Regression: the Multi-Jump in LDS walked a chain one load at
-# a time (5 to 340 times as long as the same graph takes with its ids
+# Lists that leave chains of up to n levels: paths in rising, falling and
+# random order at the sizes of the LDS solver (32- and 16-bit slots in batches),
+# the window rounds and the Multi-Jump with two and four vertices per thread;
+# bands in the order of their rows for the filtered plans with and without
+# prefix rounds and the CSR plan.  Regression: the Multi-Jumps walked a chain one
+# load at a time (5 to 340 times as long as the same graph takes with its ids
 # permuted).  4 times is allowed; an exact pass each.
 @pytest.mark.parametrize("what", ["path 1000", "path 32768", "path 50000", "path %d" % (1 << 20),
-                                  "shuffled path 32768", "batch 32768", "batch 60000"])
+                                  "falling path %d" % (1 << 22), "shuffled path 32768",
+                                  "shuffled path %d" % (1 << 21), "band5 %d" % (1 << 18),
+                                  "band5 %d" % (1 << 19), "band5 %d" % (1 << 21),
+                                  "csr band5 %d" % (1 << 21), "batch 32768", "batch 60000"])
 def test_chains(dev, what):
     kind, n = what.rsplit(" ", 1)
     n = int(n)
