@@ -62,13 +62,13 @@ extern "C" {
 /* ---------------------------------------------------------------- options */
 #define CC_HOOK_AUTO 0   /* library choice (the default): the Atomic-Hook with the
                             giant filter for lists of m >= 2^21 entries (CSR: 2^20) with
-                            m / n >= 8, the hybrid plan below for the other lists (the
+                            m / n >= 8, the hybrid plan below for the other lists; the
                             atomic-free Hook when max_rounds, rounds_per_check or
-                            compact_threshold is set and m < 2^22); the Atomic-Hook with
-                            the symmetric flag.
-                            The smallest lists (n <= 32,768, 2 n + m <= 131,072, no
-                            max_rounds) are solved by one workgroup in LDS, in one
-                            launch, and counted as one round of the atomic-free Hook  */
+                            compact_threshold is set and m < 2^22 (not for CSR or no_sync);
+                            the Atomic-Hook with the symmetric flag.
+                            The smallest lists (n <= 32,768, 2 n + m <= 131,072, none of
+                            the three options set) are solved by one workgroup in LDS, in
+                            one launch, and counted as one round of the atomic-free Hook  */
 #define CC_HOOK_ATOMIC 1 /* Atomic-Hook (Fig. 3, CAS on roots) + segmentation (Fig. 4) */
 #define CC_HOOK_PLAIN 2  /* atomic-free Hook (Fig. 2) rounds until no change (Fig. 1),
                             convergence test and active-edge frontier on the device   */

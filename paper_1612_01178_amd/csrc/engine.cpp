@@ -202,23 +202,20 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
     const bool large = m >= (int64_t(1) << 22);
     const bool dense_large = m >= int64_t(1) << (input == kInputCsr ? 20 : 21) &&
                              n > 0 && m >= 8 * (int64_t)n;
+    // A call that sets an option of the rounds gets them where it always did.
+    const bool rounds_asked = op.max_rounds != 0 || op.rounds_per_check != 0 || op.compact_threshold != 0;
     bool auto_filtered = false;
     if (op.hook == CC_HOOK_AUTO) {
-        if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large ||
-            (input == kInputGraphList && m >= (int64_t(1) << 32))) {
+        if (allow_plain && op.symmetric == 0 && rounds_asked && !large && op.no_sync == 0) {
+            p.hook = CC_HOOK_PLAIN;
+        } else if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large ||
+                   (input == kInputGraphList && m >= (int64_t(1) << 32))) {
             p.hook = CC_HOOK_ATOMIC;
             auto_filtered = dense_large && op.filter != CC_FILTER_OFF;
-        } else if (!allow_plain) {
-            p.hook = CC_HOOK_HYBRID;
-        } else if (large || op.no_sync == 1 ||
-                   (op.max_rounds == 0 && op.rounds_per_check == 0 && op.compact_threshold == 0)) {
-            p.hook = CC_HOOK_HYBRID;
         } else {
-            p.hook = CC_HOOK_PLAIN;
+            p.hook = CC_HOOK_HYBRID;
         }
-        // an explicit round cap is a question about the rounds: they run
-        p.lds_single = allow_plain && op.symmetric == 0 && op.max_rounds == 0 &&
-                       fits_lds_single(n, m);
+        p.lds_single = allow_plain && op.symmetric == 0 && !rounds_asked && fits_lds_single(n, m);
         if (p.lds_single) p.hook = op.no_sync == 1 ? CC_HOOK_HYBRID : CC_HOOK_PLAIN;
     } else {
         p.hook = op.hook;

@@ -172,6 +172,22 @@ def test_workspace_sizes(lib):
     assert cc.workspace_bytes(-1, 5) == 0
 
 
+# Regression: the automatic choice took lists of the last size solved in LDS
+# and dense lists of 2^21 entries and more past an option of the atomic-free
+# rounds (a round cap was no cap, CC_ERR_NOCONVERGE never came).
+@pytest.mark.parametrize("option", ["max_rounds", "rounds_per_check", "compact_threshold"])
+@pytest.mark.parametrize("n,m", [(1000, 4000), (32768, 65536), (1 << 17, 1 << 21),
+                                 (1000, (1 << 22) - 1), (1 << 20, 1 << 20)])
+def test_round_options_get_the_rounds(lib, n, m, option):
+    rounds = cc.workspace_bytes(n, m, cc.Options(hook="plain"))
+    assert cc.workspace_bytes(n, m, cc.Options(**{option: 2})) == rounds
+    assert cc.workspace_bytes(n, m) < rounds
+    # not where the rounds cannot run, or above 2^22 entries
+    for other in (dict(no_sync=True), dict(symmetric=True)):
+        assert cc.workspace_bytes(n, m, cc.Options(**{option: 2}, **other)) < rounds
+    assert cc.workspace_bytes(n, 1 << 22, cc.Options(**{option: 2})) == cc.workspace_bytes(n, 1 << 22)
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(cc, "_lib", None)
     monkeypatch.setattr(cc, "LIB_PATH", str(tmp_path / "missing.so"))
