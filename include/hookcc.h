@@ -376,7 +376,8 @@ int32_t cc_labels_host(int32_t n, const int32_t* host_u, const int32_t* host_v, 
  *   out_label  [device] int32[n]
  *   opts       as cc_labels_ex; hook CC_HOOK_AUTO, CC_HOOK_ATOMIC or CC_HOOK_HYBRID
  *              (AUTO: the filtered Atomic-Hook for m >= 2^20 entries with m / n >= 8,
- *              else the hybrid plan);
+ *              else the hybrid plan, or the Atomic-Hook where segments, filter or
+ *              filter_after is set and m < 2^22);
  *              opts->symmetric = 1 promises a symmetric adjacency (every pair in
  *              both rows): the Atomic-Hook then skips entries with col < row
  * Synchronous on `stream` (NULL = null stream) unless opts->no_sync = 1 (as

@@ -204,11 +204,14 @@ int32_t make_plan(int32_t n, int64_t m, const cc_options* o, Plan& p,
                              n > 0 && m >= 8 * (int64_t)n;
     // A call that sets an option of the rounds gets them where it always did.
     const bool rounds_asked = op.max_rounds != 0 || op.rounds_per_check != 0 || op.compact_threshold != 0;
+    // So does a CSR call that sets an option of the segments.
+    const bool segments_asked = op.segments != 0 || op.filter_after != 0 || op.filter != CC_FILTER_AUTO;
     bool auto_filtered = false;
     if (op.hook == CC_HOOK_AUTO) {
         if (allow_plain && op.symmetric == 0 && rounds_asked && !large && op.no_sync == 0) {
             p.hook = CC_HOOK_PLAIN;
         } else if (!allow_hybrid || (allow_plain && op.symmetric == 1) || dense_large ||
+                   (input == kInputCsr && segments_asked && !large) ||
                    (input == kInputGraphList && m >= (int64_t(1) << 32))) {
             p.hook = CC_HOOK_ATOMIC;
             auto_filtered = dense_large && op.filter != CC_FILTER_OFF;

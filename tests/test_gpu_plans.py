@@ -290,6 +290,30 @@ def test_csr_plans(dev, n, m):
             assert ei.value.code == cc.CC_ERR_RANGE
 
 
+# Regression: lists with fewer than 8 entries per vertex or 2^20 entries took
+# the hybrid plan past these options.  Rows of every kind: even ones, long
+# empty ranges (a tile's row window is more than the LDS holds), hubs.
+def test_csr_segment_options_get_segments(dev):
+    rng = np.random.default_rng(11)
+    hub = np.concatenate([np.full(30000, 17, np.int32), np.arange(9000, dtype=np.int32)])
+    lists = {"uniform": (*graphgen.uniform_pairs(300000, 100000, seed=6, stream=0), 100000),
+             "empty rows": (*graphgen.uniform_pairs(30000, 400000, seed=7, stream=0), 400000),
+             "hub": (hub, rng.integers(0, 9000, len(hub)).astype(np.int32), 9000)}
+    for name, (u, v, n) in lists.items():
+        want = oracle.labels(u, v, n)
+        rp, col = to_csr(u, v, n)
+        drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev, 1)
+        for opt, segments in ((cc.Options(segments=3), 3), (cc.Options(filter="giant", segments=8), 8),
+                              (cc.Options(filter="giant", segments=12, filter_after=2,
+                                          path_halving="off"), 12),
+                              (cc.Options(filter="off"), max(1, int(len(u) / n + 0.5)))):
+            print("csr segments", name, opt, flush=True)
+            lab, st = cc.labels_csr(drp, dcol, n, options=opt, return_stats=True)
+            assert np.array_equal(lab.cpu().numpy(), want), (name, opt)
+            assert (st["hook"], st["segments"]) == (1, segments), (name, opt)
+        assert cc.labels_csr(drp, dcol, n, return_stats=True)[1]["hook"] == 3
+
+
 def test_csr_capture_needs_no_memory(dev):
     """Inside a capture the plans that need more scratch than is there give way
     to the one that needs none; every replay is right."""
