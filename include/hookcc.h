@@ -367,10 +367,12 @@ int32_t cc_labels_host(int32_t n, const int32_t* host_u, const int32_t* host_v, 
 /* CSR adjacency input: entry i of row r is the pair (r, col[i]).  The
  * Atomic-Hook works on any subsets of E (Fig. 4), so the solve is the same as
  * for a pair list of m entries.  The hybrid plan writes each entry's row first
- * (4 bytes of scratch per entry); the automatic filtered plan starts from two
- * neighbours per row and passes over the entries once; both give way to the
- * unfiltered Atomic-Hook where their scratch cannot be had (no memory, or
- * inside a stream capture).
+ * (4 bytes of scratch per entry, and 8 more from 2^22 entries on); the automatic
+ * filtered plan starts from two neighbours per row (8 bytes per row) and passes
+ * over the entries once.  Where the automatic plan's scratch cannot be had (no
+ * memory, or inside a stream capture), the filtered one gives way to the
+ * Atomic-Hook by filtered segments (n / 8 bytes), the hybrid one, or that one
+ * again, to unfiltered segments; an explicit CC_HOOK_HYBRID is CC_ERR_NOMEM.
  *   row_ptr    [device] int64[n+1]: row_ptr[0] == 0, non-decreasing, row_ptr[n] == m
  *   col        [device] int32[m], ids in [0, n)
  *   out_label  [device] int32[n]

@@ -1256,14 +1256,27 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
             (void)hipGetLastError();
             cap = hipStreamCaptureStatusNone;
         }
-        if (cap != hipStreamCaptureStatusNone || ensure_dev(pe, need) != CC_OK) {
-            // No memory for it, or none to be had inside a capture: the
-            // unfiltered Atomic-Hook needs the control block only.
+        const bool capturing = cap != hipStreamCaptureStatusNone;
+        rc = capturing ? fail(CC_ERR_NOMEM, "no memory for the plan inside a stream capture")
+                       : ensure_dev(pe, need);
+        if (rc != CC_OK) {
+            // No memory for it, or none to be had inside a capture: an explicit
+            // plan is refused; the automatic one falls back to the filtered
+            // segments, which need the bitmap, or to unfiltered ones, which
+            // need the control block only (R-MAT 20, 2^25 entries, inside a
+            // capture: 457 us, 969 unfiltered).
             (void)hipGetLastError();
-            tiled = p.auto_filter = false;
+            if (opts && opts->hook != CC_HOOK_AUTO) return rc;
+            tiled = false;
+            const bool fits = capturing ? pe->bytes >= 256 + bits_bytes
+                                        : ensure_dev(pe, 256 + bits_bytes) == CC_OK;
+            (void)hipGetLastError();
+            if (!p.auto_filter || !fits) {
+                p.filter = CC_FILTER_OFF;
+                p.segments = (int)std::min<int64_t>(std::min<int64_t>(1 << 20, round_ratio(m, n)), m / 4 + 1);
+            }
+            p.auto_filter = false;
             p.hook = CC_HOOK_ATOMIC;
-            p.filter = CC_FILTER_OFF;
-            p.segments = (int)std::min<int64_t>(std::min<int64_t>(1 << 20, round_ratio(m, n)), m / 4 + 1);
         }
     }
     const bool filter = p.filter == CC_FILTER_GIANT;

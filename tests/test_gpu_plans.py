@@ -339,6 +339,37 @@ def test_csr_capture_needs_no_memory(dev):
         assert torch.equal(out, want)
 
 
+def test_csr_capture_keeps_the_filter(dev):
+    """Regression: inside a capture with too little scratch for the automatic
+    filtered plan but room for the bitmap, a dense adjacency ran unfiltered; an
+    explicit hybrid plan ran as another one instead of being refused."""
+    u, v, n = graphgen.rmat(18, 8, seed=18, symmetrize=True)
+    want = torch.from_numpy(np.asarray(oracle.labels(u, v, n), dtype=np.int32)).to(dev)
+    rp, col = to_csr(u, v, n)
+    drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+    out = torch.empty(n, dtype=torch.int32, device=dev)
+    stream = torch.cuda.Stream()
+    opt = cc.Options(no_sync=True)
+    with torch.cuda.stream(stream):  # a small call: the stream's smallest scratch
+        cc.labels_csr(torch.zeros(2, dtype=torch.int64, device=dev), dcol[:0], 1, options=opt, stream=stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        _, st = cc.labels_csr(drp, dcol, n, out=out, options=opt, stream=stream, return_stats=True)
+        with pytest.raises(cc.CCError) as ei:
+            cc.labels_csr(drp, dcol, n, out=out, options=cc.Options(no_sync=True, hook="hybrid"),
+                          stream=stream)
+    assert ei.value.code == cc.CC_ERR_NOMEM
+    # segments of n / 16 entries, launched by growing numbers of them
+    assert st["hook"] == 1 and st["segments"] == 16 * 16 and st["hook_launches"] < 16
+    for _ in range(3):
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+
+
 # Graphs of a list that leave the LDS launch: none, one, two among small ones,
 # and the sparse and dense graphs above the LDS's vertices
 @pytest.mark.parametrize("sizes", [[(65536, 786431), (300, 900)],
