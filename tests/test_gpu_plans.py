@@ -484,3 +484,22 @@ def test_chains(dev, what):
         times.append(median_us(call))
     print("chains", what, times, flush=True)
     assert times[0] <= 4 * times[1], (what, times)
+
+
+def test_contracting_hook_spreads_over_the_roots(dev):
+    """Regression: the workgroups of the contracting hook met on each root's
+    word at the same time (0.86 times the time of the Atomic-Hook by segments
+    on these adjacencies, 0.54 to 0.60 since; half-way is allowed)."""
+    n, m = 200000, 600000
+    times = np.zeros(2)
+    for seed in (1, 2, 3):
+        u, v = graphgen.uniform_pairs(m, n, seed=seed, stream=0)
+        rp, col = to_csr(np.concatenate([u, v]), np.concatenate([v, u]), n)
+        drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+        out = torch.empty(n, dtype=torch.int32, device=dev)
+        want = oracle.labels(u, v, n)
+        for k, opt in enumerate((cc.Options(), cc.Options(hook="atomic"))):
+            times[k] += median_us(lambda: cc.labels_csr(drp, dcol, n, out=out, options=opt), passes=15)
+            assert np.array_equal(out.cpu().numpy(), want)
+    print("contract", times, flush=True)
+    assert times[0] <= 0.72 * times[1], times
