@@ -1167,11 +1167,13 @@ constexpr int kContractEPT = 2;
 constexpr int kContractTile = kContractThreads * kContractEPT;
 constexpr int kContractSlots = 8192;
 constexpr int kContractMaxKeys = kContractSlots / 4;  // before a tile, which adds up to 2 * kContractTile
-// A root has the same slot in every workgroup's table, so each workgroup sweeps
-// its table from another slot on (one of 128, an odd multiple of a wave's 64):
-// from the same one they met on each root's word at the same time (uniform
-// n = 200,000, m = 1.2 M: 150 us, 124 now; as a CSR adjacency, m = 1.2 M: 243 and
-// 165; n = 2 M, m = 28 M: 490 and 323).
+// A root has the same slot in every workgroup's table, so where roots are few
+// each workgroup sweeps its table from another slot on (one of 128, an odd
+// multiple of a wave's 64): from the same one they met on each root's word at
+// the same time (uniform n = 200,000, m = 1.2 M: 150 us, 124 now; as a CSR
+// adjacency, m = 1.2 M: 243 and 165; n = 2 M, m = 28 M: 490 and 323).  With many
+// roots they hardly meet, and sweeping in one order shares the lines of pi (CSR,
+// uniform n = 2 M, m = 12 M: 631 us, 711 from other slots).
 constexpr int kContractStagger = 41 * 64;
 constexpr int kContractDirect = 128;  // active entries of a tile that are hooked directly
 
@@ -1203,7 +1205,7 @@ __global__ __launch_bounds__(kContractThreads) void k_hook_contract(
     bool bad = false;
     int used = -1;  // keys in the table as of the last barrier; -1: not set up
     auto hook_table = [&]() {
-        const int start = (int)blockIdx.x * kContractStagger + tid;
+        const int start = (used <= kContractMaxKeys ? (int)blockIdx.x * kContractStagger : 0) + tid;
         for (int k = 0; k < kContractSlots; k += kContractThreads) {
             const int i = (start + k) & (kContractSlots - 1);
             uint32_t r = par[i];
