@@ -561,8 +561,13 @@ hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, co
 // spans ~0.8 ids per entry plus a row; long lists take the largest chunks of
 // which two workgroups fit a CU (80 KiB of LDS), shorter ones smaller chunks,
 // so that every CU has one.
+//
+// DEEP: climbs in the window shorten chains (see kDeepLdsSteps).  Counting the
+// steps costs the launch 2 % (4096^2 grid: 150 us, 155 counted by one, 153 by
+// two), so the largest chunks do without (path of 2^24 vertices: 13 ms, 1.4 with).
 constexpr int kWinEPT = 4;  // entries per thread per step (registers: two workgroups per CU)
 
+template <bool DEEP>
 __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict__ eu,
                                                       const int32_t* __restrict__ ev, int64_t m,
                                                       int32_t* pi, int32_t n, Ctrl* ctrl,
@@ -665,12 +670,18 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
             while (g1 != p1 || g2 != p2) {
                 p1 = g1;
                 p2 = g2;
-                if (++k > kDeepLdsSteps) {
-                    lds_st(spi, x, p1);
-                    lds_st(spi, has_y ? y : x, p2);
-                }
                 g1 = lds_ld(spi, p1);
                 g2 = lds_ld(spi, p2);
+                if (DEEP && (g1 != p1 || g2 != p2)) {  // counted by two
+                    p1 = g1;
+                    p2 = g2;
+                    if (++k > kDeepLdsSteps / 2) {
+                        lds_st(spi, x, p1);
+                        lds_st(spi, has_y ? y : x, p2);
+                    }
+                    g1 = lds_ld(spi, p1);
+                    g2 = lds_ld(spi, p2);
+                }
             }
             if (!last) {
                 lds_st(spi, x, p1);
@@ -707,15 +718,22 @@ static WindowShape window_shape(int64_t m) {
 hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                               int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
     if (m <= 0) return hipSuccess;
-    static hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hook_window),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 40960 * 2);
+    static hipError_t once = [] {
+        for (const void* f : {reinterpret_cast<const void*>(&k_hook_window<true>),
+                              reinterpret_cast<const void*>(&k_hook_window<false>)}) {
+            const hipError_t e =
+                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 40960 * 2);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
     if (once != hipSuccess) return once;
     const WindowShape w = window_shape(m);
     const int64_t grid = (m + w.chunk - 1) / w.chunk;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    k_hook_window<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots,
-                                                       w.segments, far_limit);
+    const auto kernel = w.chunk < 49152 ? &k_hook_window<true> : &k_hook_window<false>;
+    kernel<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots, w.segments,
+                                                far_limit);
     return hipGetLastError();
 }
 

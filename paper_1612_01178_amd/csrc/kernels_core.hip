@@ -476,7 +476,10 @@ __global__ __launch_bounds__(1024, 8) void k_mj_local(int32_t* pi, int32_t n) {
 //
 // SETTLE: every vertex's root is stored, also where it is its parent already:
 // the form that must follow a pass in which several workgroups may store to
-// one slot with workgroup scope (see settling in common.hpp).
+// one slot with workgroup scope (see settling in common.hpp).  Such passes leave
+// the chains that climbs shorten (kDeepSteps); the other form, after the
+// Atomic-Hook's path halving, does so on every fourth such step only (4096^2
+// grid: 26 us, 30 with each of them; path of 2^24 vertices 48 -> 13 ms).
 template <int V, bool SETTLE>
 __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint32_t* gate,
                                              uint32_t limit, Post post) {
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
         int steps = 0;
         while (more) {
             more = false;
-            if (++steps % kDeepSteps == 0) {
+            if (++steps % (SETTLE ? kDeepSteps : 4 * kDeepSteps) == 0) {
 #pragma unroll
                 for (int k = 0; k < V; ++k)  // a climb under way: its vertex is below n
                     if (g[k] != r[k]) st_tree<true>(pi + v + (int64_t)k * blockDim.x, g[k]);
@@ -542,9 +545,13 @@ static hipError_t mj1_launch(int32_t* pi, int32_t n, const uint32_t* gate, uint3
     const int64_t cus = device_cu_count();
     const int V = (int64_t)n >= 256 * 4 * 8 * cus ? 4 : 2;
     int64_t grid = ((int64_t)n + 256 * V - 1) / (256 * V);
-    // a gated launch may find nothing to do: a grid of at most 32 workgroups
-    // per CU, each thread striding over vertices, exits in a few microseconds
-    if (gate) grid = std::min<int64_t>(grid, cus * 32);
+    // A gated launch may find nothing to do: a large grid then costs more than
+    // it has to.  Above 32 workgroups per CU the 8 that are resident stride over
+    // the vertices, all of them through the same range of ids at a time: with
+    // workgroups that start only when others have passed over all ranges, the
+    // ranges they skip stay chains (path of 2^24 vertices, entries shuffled: 8.4 s
+    // at 32 per CU, 26 ms).
+    if (gate && grid > cus * 32) grid = cus * 8;
     if (V == 4 && settle) k_mj1<4, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
     else if (V == 4) k_mj1<4, false><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
     else if (settle) k_mj1<2, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
