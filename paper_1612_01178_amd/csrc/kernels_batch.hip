@@ -78,13 +78,6 @@ __device__ __forceinline__ uint32_t lds_cas(uint16_t* spi, uint32_t idx, uint32_
     return lds_cas16(spi, idx, expected, desired);
 }
 
-// A Multi-Jump climb of more steps than this stores where it has got to at
-// every further step, so that the vertices of a chain shorten it for each
-// other (a path of 2^15 vertices, whose climbs otherwise walk up to 2^15 levels
-// in each of 16 passes: 17.8 -> 0.12 ms; from the 9th step on, trees of a few
-// dozen levels lost up to 15 %).
-constexpr int kDeepLdsSteps = 64;
-
 // Atomic-Hook in LDS (Fig. 3, top), same steps as the device-memory kernel;
 // with `halve`, a passed non-root H whose grandparent differs from its
 // parent is re-pointed at the grandparent (path halving).  The re-point of a
@@ -114,6 +107,46 @@ __device__ __forceinline__ void lds_atomic_hook(T* spi, uint32_t pu, uint32_t pv
         const bool hooked = found == H;
         pu = hooked ? L : gu;
         pv = hooked ? L : gv;
+    }
+}
+
+// The roots p1, p2 of vertices x and y (a root is its own), their climbs
+// interleaved; a finished climb stays on its root, whose parent is itself.
+// A climb of more than kDeepLdsSteps steps stores where it has got to at
+// every further step, so that the vertices of a chain shorten it for each
+// other (a path of 2^15 vertices, whose climbs otherwise walk up to 2^15 levels
+// in each of 16 passes: 17.8 -> 0.12 ms; from the 9th step on, trees of a few
+// dozen levels lost up to 15 %).  The first three steps are not counted: most
+// climbs end there (10,000 graphs: 873 us, 883 counting from the first; 4096^2
+// grid 327 and 335).
+constexpr int kDeepLdsSteps = 64;
+
+template <typename T>
+__device__ __forceinline__ void lds_climb(T* spi, uint32_t x, uint32_t y, uint32_t& p1,
+                                          uint32_t& p2) {
+    p1 = lds_ld(spi, x);
+    p2 = lds_ld(spi, y);
+    uint32_t g1 = lds_ld(spi, p1), g2 = lds_ld(spi, p2);
+    auto under_way = [&] { return g1 != p1 || g2 != p2; };
+    auto step = [&] {
+        p1 = g1;
+        p2 = g2;
+        g1 = lds_ld(spi, p1);
+        g2 = lds_ld(spi, p2);
+    };
+    if (!under_way()) return;
+    step();
+    if (!under_way()) return;
+    step();
+    if (!under_way()) return;
+    step();
+    int k = 3;
+    while (under_way()) {
+        if (++k > kDeepLdsSteps) {
+            lds_st(spi, x, g1);
+            lds_st(spi, y, g2);
+        }
+        step();
     }
 }
 
@@ -198,25 +231,13 @@ __device__ __forceinline__ void solve_graph(T* spi, const GraphDesc& d, bool hal
         // itself); no hook runs in this phase, so only the stores of other
         // climbers race with it, and each stores an ancestor.  After the last
         // segment the root is the label: it goes to global memory only.
-        // Two vertices per thread and pass, their climbs interleaved (a
-        // finished climb stays on its root, whose parent is itself).
+        // Two vertices per thread and pass.
         const bool last = seg + 1 == s;
         for (uint32_t x = tid; x < n; x += 2 * nthr) {
             const uint32_t y = x + nthr;
             const bool has_y = y < n;
-            uint32_t p1 = lds_ld(spi, x), p2 = lds_ld(spi, has_y ? y : x);
-            uint32_t g1 = lds_ld(spi, p1), g2 = lds_ld(spi, p2);
-            int k = 0;
-            while (g1 != p1 || g2 != p2) {
-                p1 = g1;
-                p2 = g2;
-                if (++k > kDeepLdsSteps) {
-                    lds_st(spi, x, p1);
-                    lds_st(spi, has_y ? y : x, p2);
-                }
-                g1 = lds_ld(spi, p1);
-                g2 = lds_ld(spi, p2);
-            }
+            uint32_t p1, p2;
+            lds_climb(spi, x, has_y ? y : x, p1, p2);
             if (last) {
                 dout[x] = (int32_t)p1;
                 if (has_y) dout[y] = (int32_t)p2;
@@ -561,13 +582,8 @@ hipError_t launch_batch_prep(const int64_t* vo, const int64_t* eo, int32_t B, co
 // spans ~0.8 ids per entry plus a row; long lists take the largest chunks of
 // which two workgroups fit a CU (80 KiB of LDS), shorter ones smaller chunks,
 // so that every CU has one.
-//
-// DEEP: climbs in the window shorten chains (see kDeepLdsSteps).  Counting the
-// steps costs the launch 2 % (4096^2 grid: 150 us, 155 counted by one, 153 by
-// two), so the largest chunks do without (path of 2^24 vertices: 13 ms, 1.4 with).
 constexpr int kWinEPT = 4;  // entries per thread per step (registers: two workgroups per CU)
 
-template <bool DEEP>
 __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict__ eu,
                                                       const int32_t* __restrict__ ev, int64_t m,
                                                       int32_t* pi, int32_t n, Ctrl* ctrl,
@@ -664,25 +680,8 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
         for (uint32_t x = tid; x < span; x += 2 * nthr) {
             const uint32_t y = x + nthr;
             const bool has_y = y < span;
-            uint32_t p1 = lds_ld(spi, x), p2 = lds_ld(spi, has_y ? y : x);
-            uint32_t g1 = lds_ld(spi, p1), g2 = lds_ld(spi, p2);
-            int k = 0;
-            while (g1 != p1 || g2 != p2) {
-                p1 = g1;
-                p2 = g2;
-                g1 = lds_ld(spi, p1);
-                g2 = lds_ld(spi, p2);
-                if (DEEP && (g1 != p1 || g2 != p2)) {  // counted by two
-                    p1 = g1;
-                    p2 = g2;
-                    if (++k > kDeepLdsSteps / 2) {
-                        lds_st(spi, x, p1);
-                        lds_st(spi, has_y ? y : x, p2);
-                    }
-                    g1 = lds_ld(spi, p1);
-                    g2 = lds_ld(spi, p2);
-                }
-            }
+            uint32_t p1, p2;
+            lds_climb(spi, x, has_y ? y : x, p1, p2);
             if (!last) {
                 lds_st(spi, x, p1);
                 if (has_y) lds_st(spi, y, p2);
@@ -718,22 +717,15 @@ static WindowShape window_shape(int64_t m) {
 hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
                               int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
     if (m <= 0) return hipSuccess;
-    static hipError_t once = [] {
-        for (const void* f : {reinterpret_cast<const void*>(&k_hook_window<true>),
-                              reinterpret_cast<const void*>(&k_hook_window<false>)}) {
-            const hipError_t e =
-                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 40960 * 2);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }();
+    static hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hook_window),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 40960 * 2);
     if (once != hipSuccess) return once;
     const WindowShape w = window_shape(m);
     const int64_t grid = (m + w.chunk - 1) / w.chunk;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    const auto kernel = w.chunk < 49152 ? &k_hook_window<true> : &k_hook_window<false>;
-    kernel<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots, w.segments,
-                                                far_limit);
+    k_hook_window<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots,
+                                                       w.segments, far_limit);
     return hipGetLastError();
 }
 

@@ -479,7 +479,7 @@ __global__ __launch_bounds__(1024, 8) void k_mj_local(int32_t* pi, int32_t n) {
 // one slot with workgroup scope (see settling in common.hpp).  Such passes leave
 // the chains that climbs shorten (kDeepSteps); the other form, after the
 // Atomic-Hook's path halving, does so on every fourth such step only (4096^2
-// grid: 26 us, 30 with each of them; path of 2^24 vertices 48 -> 13 ms).
+// grid: 26 us, 30 with each of them; path of 2^24 vertices 48 -> 1.3 ms).
 template <int V, bool SETTLE>
 __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint32_t* gate,
                                              uint32_t limit, Post post) {
