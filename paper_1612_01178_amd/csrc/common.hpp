@@ -17,8 +17,8 @@ struct Ctrl {
     int32_t filter_on;    // 1 when the giant-component bitmap is valid and worth using
     int32_t rounds;       // atomic-free Hook: rounds that found an active edge
     uint32_t count[2];    // atomic-free Hook: frontier sizes, ping-pong by round parity
-    uint32_t nofilter;    // giant sample: 1 when no component is large enough to filter
-    int32_t unused;
+    uint32_t windowed;    // that plan: 1 = it has, and window round and contracting hook solve it
+    uint32_t scattered;   // filtered plan with prefix rounds: 1 = the list has no locality
     int64_t active_round1;  // atomic-free Hook: frontier size after round 1
     int32_t hook_changed;   // host-loop form of Fig. 1: a Hook pass found an active edge
     int32_t jump_changed;   // host-loop form of Fig. 1: a Jump pass moved a pointer

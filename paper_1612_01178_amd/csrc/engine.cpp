@@ -77,6 +77,14 @@ int64_t segment_start(int64_t m, int64_t i, int64_t S) {
 // 170 us, uniform n = 65,536 743 us).  The launches after the rounds take
 // kPrefixStart * n entries and then kPrefixGrowth times more each.
 //
+// A list whose consecutive entries touch nearby ids (the init kernel looks at
+// 256 places of it) has no giant in that part, and hooking the rest entry by
+// entry is bound by the compare-and-swaps on few roots (2,000 cliques of 60: 238
+// us; band of 2^18 vertices, m = 4.2 M: 447).  The first round then is a window
+// round over the whole list, the contracting hook takes the whole list too, and
+// the launches after it find nothing to do (115 and 100 us; R-MAT 18 pays 2 us
+// for the look).
+//
 // The Atomic-Hook of the first n / 16 entries runs two entries per thread up
 // to kShortMaxN vertices, 8 per thread above, where more climbs at once
 // contend for the hubs (R-MAT 20 197 against 229 us, 22 667 and 670, 23
@@ -620,7 +628,10 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     };
     int hooks = 0, jumps = 0;
     const Post post = {ctrl, host};
-    TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
+    if (p.prefix)
+        TIMED(kPhaseOther, launch_init(pi, n, ctrl, s, u, v, m));
+    else
+        TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     if (p.filter != CC_FILTER_GIANT) {
         // Fig. 4: for each segment, Atomic-Hook the segment, then Multi-Jump all of V.
         for (int i = 0; i < S; ++i) {
@@ -634,12 +645,19 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
         const int fa = p.filter_after;
         // The part of the list that finds the giant.
         const int64_t prefix = std::min<int64_t>(m, n) & ~int64_t(3);
+        // Where consecutive entries touch nearby ids, that part holds none, and
+        // one window round and a contracting hook of all entries solve the list;
+        // the launches after them find ctrl->windowed set.
+        const uint32_t* scattered = &ctrl->scattered;
         for (int i = 0; p.prefix && i <= kPrefixRounds; ++i) {
-            if (i < kPrefixRounds)
-                TIMED(kPhaseHook, launch_hook_prefix(u, v, prefix, pi, n, i == 0, s));
+            if (i == 0)
+                TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, 0, s, prefix));
+            else if (i < kPrefixRounds)
+                TIMED(kPhaseHook, launch_hook_prefix(u, v, prefix, pi, n, s, scattered));
             else
-                TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, p.halve, s));
-            TIMED(kPhaseCompress, launch_mj1(pi, n, nullptr, s, i < kPrefixRounds));
+                TIMED(kPhaseHook, launch_hook_contract(u, v, 0, prefix, pi, n, ctrl, p.halve, s, nullptr, 0, m));
+            TIMED(kPhaseCompress, launch_mj1(pi, n, i == 0 || i == kPrefixRounds ? nullptr : scattered, s,
+                                             i < kPrefixRounds));
             ++hooks;
             ++jumps;
         }
@@ -757,7 +775,7 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, far_limit, s));
     TIMED(kPhaseCompress, launch_mj1(pi, n, longer ? far : nullptr, s, true, far_limit));
     for (int r = 0; r < rounds; ++r) {
-        TIMED(kPhaseHook, launch_hook_prefix(u, v, m, pi, n, false, s, far, far_limit));
+        TIMED(kPhaseHook, launch_hook_prefix(u, v, m, pi, n, s, far, far_limit));
         TIMED(kPhaseCompress, launch_mj1(pi, n, far, s, true, far_limit));
     }
     if (longer) {
@@ -1316,7 +1334,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
         int32_t* sv = rows + row_bytes / 4;
         TIMED(kPhaseOther, launch_csr_prep(row_ptr, col, n, m, ctrl, out, tile_row, rows, sv, s));
         TIMED(kPhaseCompress, launch_mj_deep(out, n, s));
-        TIMED(kPhaseHook, launch_hook_prefix(rows, sv, n, out, n, false, s));
+        TIMED(kPhaseHook, launch_hook_prefix(rows, sv, n, out, n, s));
         TIMED(kPhaseCompress, launch_mj1(out, n, nullptr, s, true));
         TIMED(kPhaseHook, launch_hook_contract(rows, sv, 0, n, out, n, ctrl, p.halve, s));
         TIMED(kPhaseCompress, launch_mj1(out, n, nullptr, s, false));

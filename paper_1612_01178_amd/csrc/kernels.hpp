@@ -6,7 +6,10 @@
 namespace hookcc {
 
 // pi[v] = v for v < n; resets the control block.  (Fig. 4, first step.)
-hipError_t launch_init(int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s);
+// With u non-null, ctrl->windowed or ctrl->scattered says whether consecutive
+// entries of the list touch nearby ids.
+hipError_t launch_init(int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s, const int32_t* u = nullptr,
+                       const int32_t* v = nullptr, int64_t m = 0);
 
 // Atomic-Hook (Fig. 3) of entries [begin, end).  When `bits` is non-null the
 // giant-component filter is applied (only if ctrl->filter_on is set);
@@ -22,11 +25,10 @@ hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin,
                               int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, bool sym,
                               hipStream_t s);
 // One atomic-free Hook (Fig. 2) pass over entries [0, m), which are hooked
-// again later; `first`: pi is the identity.  No range check.  Does nothing
-// when `gate` is non-null and *gate <= limit.
+// again later.  No range check.  Does nothing when `gate` is non-null and
+// *gate <= limit.
 hipError_t launch_hook_prefix(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi, int32_t n,
-                              bool first, hipStream_t s, const uint32_t* gate = nullptr,
-                              uint32_t limit = 0);
+                              hipStream_t s, const uint32_t* gate = nullptr, uint32_t limit = 0);
 
 // Where a call's last launch copies the control block for the host (pinned
 // memory); nothing is copied when host is null.
@@ -78,18 +80,23 @@ hipError_t launch_hook_plain(int round, const int32_t* u, const int32_t* v, int6
 // Window round of the hybrid plan: an atomic-free Hook round over all m
 // entries in which each workgroup first joins its chunk of entries inside an
 // LDS window of consecutive vertices (see kernels_batch.hip).  Range-checks
-// the entries.  Leaves pi a forest (not of stars).
+// the entries.  Leaves pi a forest (not of stars).  `prefix` > 0: where
+// ctrl->scattered is set, the atomic-free round over entries [0, prefix)
+// instead (pi the identity, no range check).
 hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s);
+                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s,
+                              int64_t prefix = 0);
+int32_t window_slots(int64_t m);  // ids that a window of that round holds
 // Atomic-Hook with path halving of the *count root pairs of a frontier.
 hipError_t launch_ahook_pairs(const int2* fr, const uint32_t* count, int64_t cap, int32_t* pi,
                               bool halve, int grid_cap, hipStream_t s);
 
 // Atomic-Hook of entries [begin, end) with each workgroup's active roots joined
 // in LDS first; pi a forest of stars with few roots left.  Gate as above.
+// `all` > end: entries [begin, all) when ctrl->windowed is set.
 hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
                                 int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
-                                const uint32_t* gate = nullptr, uint32_t limit = 0);
+                                const uint32_t* gate = nullptr, uint32_t limit = 0, int64_t all = 0);
 
 // tau: frontier rewrite threshold in thousandths (0xffffffff = every round).
 // Does nothing when `skip` is non-null and *skip > limit.

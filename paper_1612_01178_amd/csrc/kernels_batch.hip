@@ -588,10 +588,19 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
                                                       const int32_t* __restrict__ ev, int64_t m,
                                                       int32_t* pi, int32_t n, Ctrl* ctrl,
                                                       int32_t chunk, uint32_t slots,
-                                                      int32_t segments, uint32_t far_limit) {
+                                                      int32_t segments, uint32_t far_limit,
+                                                      int64_t prefix) {
     extern __shared__ uint16_t spi[];
     __shared__ int32_t wave_min[16];
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
+    if (prefix > 0 && ctrl->scattered) {
+        const int64_t e = (int64_t)blockIdx.x * nthr + tid;
+        for (int64_t i = e; i < prefix; i += (int64_t)gridDim.x * nthr) {
+            const int32_t x = __builtin_nontemporal_load(eu + i), y = __builtin_nontemporal_load(ev + i);
+            if (x != y && max((uint32_t)x, (uint32_t)y) < (uint32_t)n) st_rlx(pi + max(x, y), min(x, y));
+        }
+        return;
+    }
     const uint32_t lane = tid & 63, wave = tid >> 6, waves = nthr >> 6;
     const int64_t c0 = (int64_t)blockIdx.x * chunk;
     const int64_t c1 = min(m, c0 + chunk);
@@ -714,8 +723,11 @@ static WindowShape window_shape(int64_t m) {
     return {4096, 1, 8192};
 }
 
+int32_t window_slots(int64_t m) { return (int32_t)window_shape(m).slots; }
+
 hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi,
-                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s) {
+                              int32_t n, Ctrl* ctrl, uint32_t far_limit, hipStream_t s,
+                              int64_t prefix) {
     if (m <= 0) return hipSuccess;
     static hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hook_window),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -725,7 +737,7 @@ hipError_t launch_hook_window(const int32_t* u, const int32_t* v, int64_t m, int
     const int64_t grid = (m + w.chunk - 1) / w.chunk;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     k_hook_window<<<(int)grid, 1024, w.slots * 2, s>>>(u, v, m, pi, n, ctrl, w.chunk, w.slots,
-                                                       w.segments, far_limit);
+                                                       w.segments, far_limit, prefix);
     return hipGetLastError();
 }
 

@@ -89,8 +89,14 @@ __device__ __forceinline__ void atomic_hook(int32_t* pi, int32_t pu, int32_t pv)
 }
 
 // ----------------------------------------------------------------------------- K-INIT
+// With a list (eu non-null), the first workgroup also looks at 256 places of it,
+// two entries 1,023 apart each: ctrl->windowed is set where at three in four the
+// ids lie within `reach` of each other, else ctrl->scattered.
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_init(int32_t* __restrict__ pi, int32_t n, Ctrl* ctrl) {
+__global__ __launch_bounds__(256) void k_init(int32_t* __restrict__ pi, int32_t n, Ctrl* ctrl,
+                                              const int32_t* __restrict__ eu,
+                                              const int32_t* __restrict__ ev, int64_t m, double step,
+                                              int32_t reach) {
     const int64_t base = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (VEC && base + 3 < n) {
         v4i q = {(int32_t)base, (int32_t)base + 1, (int32_t)base + 2, (int32_t)base + 3};
@@ -100,19 +106,34 @@ __global__ __launch_bounds__(256) void k_init(int32_t* __restrict__ pi, int32_t 
         for (int j = 0; j < 4; ++j)
             if (base + j < n) pi[base + j] = (int32_t)(base + j);
     }
-    if (blockIdx.x == 0 && threadIdx.x < sizeof(Ctrl) / 4) {
+    if (blockIdx.x != 0) return;
+    int near = 0;
+    if (eu != nullptr) {
+        const int64_t e = min((int64_t)((double)threadIdx.x * step), m - 1), f = min(e + 1023, m - 1);
+        const uint32_t a = eu[e], b = ev[e], c = eu[f], d = ev[f];
+        const uint32_t lo = min(min(a, b), min(c, d)), hi = max(max(a, b), max(c, d));
+        near = __syncthreads_count(hi - lo < (uint32_t)reach);
+    }
+    if (threadIdx.x < sizeof(Ctrl) / 4) {
         // status, giant (-1), filter_on, rounds, counts, ... all zero
-        reinterpret_cast<int32_t*>(ctrl)[threadIdx.x] = (threadIdx.x == 1) ? -1 : 0;
+        int32_t x = threadIdx.x == offsetof(Ctrl, giant) / 4 ? -1 : 0;
+        if (eu != nullptr && threadIdx.x == offsetof(Ctrl, windowed) / 4) x = 4 * near >= 3 * (int)blockDim.x;
+        if (eu != nullptr && threadIdx.x == offsetof(Ctrl, scattered) / 4) x = 4 * near < 3 * (int)blockDim.x;
+        reinterpret_cast<int32_t*>(ctrl)[threadIdx.x] = x;
     }
 }
 
-hipError_t launch_init(int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s) {
+hipError_t launch_init(int32_t* pi, int32_t n, Ctrl* ctrl, hipStream_t s, const int32_t* u,
+                       const int32_t* v, int64_t m) {
     const int64_t groups = ((int64_t)n + 3) / 4;
     const int grid = (int)((groups + 255) / 256 > 0 ? (groups + 255) / 256 : 1);
+    const double step = (double)m / 256;
+    // inside a window; on graphs of a few windows any list would be near
+    const int32_t reach = std::min(n / 4, window_slots(m));
     if (((uintptr_t)pi & 15) == 0)
-        k_init<true><<<grid, 256, 0, s>>>(pi, n, ctrl);
+        k_init<true><<<grid, 256, 0, s>>>(pi, n, ctrl, u, v, m, step, reach);
     else
-        k_init<false><<<grid, 256, 0, s>>>(pi, n, ctrl);
+        k_init<false><<<grid, 256, 0, s>>>(pi, n, ctrl, u, v, m, step, reach);
     return hipGetLastError();
 }
 
@@ -272,11 +293,9 @@ hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin,
 // Atomic-free Hook (Fig. 2) of entries [0, m): a round over entries that are
 // all hooked again later, so a lost store costs nothing; a settling Multi-Jump
 // must follow.  Does nothing when `gate` is non-null and *gate <= limit.
-// FIRST: every vertex is its own parent (the init's values), no gather.
 // Invalid endpoints are skipped (the later pass reports them).
 constexpr int kPrefixEPT = 2;
 
-template <bool FIRST>
 __global__ __launch_bounds__(256) void k_hook_prefix(const int32_t* __restrict__ eu,
                                                      const int32_t* __restrict__ ev, int64_t m,
                                                      int32_t* pi, int32_t n, const uint32_t* gate,
@@ -292,32 +311,29 @@ __global__ __launch_bounds__(256) void k_hook_prefix(const int32_t* __restrict__
             b[j] = e < m ? __builtin_nontemporal_load(ev + e) : 0;
             if (max((uint32_t)a[j], (uint32_t)b[j]) >= (uint32_t)n) a[j] = b[j] = 0;
         }
-        if (!FIRST) {
 #pragma unroll
-            for (int j = 0; j < kPrefixEPT; ++j) {
-                a[j] = ld_rlx(pi + a[j]);
-                b[j] = ld_rlx(pi + b[j]);
-            }
+        for (int j = 0; j < kPrefixEPT; ++j) {
+            a[j] = ld_rlx(pi + a[j]);
+            b[j] = ld_rlx(pi + b[j]);
         }
 #pragma unroll
         for (int j = 0; j < kPrefixEPT; ++j) {
             if (a[j] == b[j]) continue;
             // many entries meet on a hub's root; most find a smaller id there
             const int32_t H = max(a[j], b[j]), L = min(a[j], b[j]);
-            if (FIRST || ld_rlx(pi + H) > L) st_rlx(pi + H, L);
+            if (ld_rlx(pi + H) > L) st_rlx(pi + H, L);
         }
     }
 }
 
 hipError_t launch_hook_prefix(const int32_t* u, const int32_t* v, int64_t m, int32_t* pi, int32_t n,
-                              bool first, hipStream_t s, const uint32_t* gate, uint32_t limit) {
+                              hipStream_t s, const uint32_t* gate, uint32_t limit) {
     if (m <= 0) return hipSuccess;
     // a gated launch may find nothing to do: at most 8 workgroups per CU
     int64_t grid64 = (m + 256 * kPrefixEPT - 1) / (256 * kPrefixEPT);
     if (gate) grid64 = std::min<int64_t>(grid64, device_cu_count() * 8);
     if (grid64 > 0x7fffffff) return hipErrorInvalidValue;
-    if (first) k_hook_prefix<true><<<(int)grid64, 256, 0, s>>>(u, v, m, pi, n, gate, limit);
-    else k_hook_prefix<false><<<(int)grid64, 256, 0, s>>>(u, v, m, pi, n, gate, limit);
+    k_hook_prefix<<<(int)grid64, 256, 0, s>>>(u, v, m, pi, n, gate, limit);
     return hipGetLastError();
 }
 
@@ -605,6 +621,7 @@ __global__ __launch_bounds__(kSamples) void k_sample(const int32_t* __restrict__
                                                      double step, const int32_t* pi, int32_t n,
                                                      Ctrl* ctrl, bool again) {
     if (again && ctrl->filter_on) return;
+    const uint32_t windowed = ctrl->windowed;
     constexpr int kSlots = 2 * kSamples;
     __shared__ int32_t keys[kSlots];
     __shared__ int32_t cnts[kSlots];
@@ -671,10 +688,9 @@ __global__ __launch_bounds__(kSamples) void k_sample(const int32_t* __restrict__
                 c = best_cnt[w];
                 k = best_key[w];
             }
-        const bool on = k >= 0 && c * 8 >= kSamples;
+        const bool on = k >= 0 && c * 8 >= kSamples && windowed == 0;
         ctrl->giant = on ? k : -1;
         ctrl->filter_on = on ? 1 : 0;
-        ctrl->nofilter = on ? 0u : 1u;
     }
 }
 
@@ -1203,8 +1219,15 @@ __device__ __forceinline__ uint32_t contract_slot(int32_t* keys, int32_t key, in
 template <bool HALVE>
 __global__ __launch_bounds__(kContractThreads) void k_hook_contract(
     const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t begin, int64_t end,
-    int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* gate, uint32_t limit) {
+    int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* gate, uint32_t limit, int64_t all,
+    int part_grid) {
     if (gate != nullptr && *gate <= limit) return;
+    int grid = gridDim.x;
+    if (all > end) {
+        if (ctrl->windowed) end = all;
+        else grid = part_grid;
+        if ((int)blockIdx.x >= grid) return;
+    }
     __shared__ int32_t keys[kContractSlots];
     __shared__ uint32_t par[kContractSlots];
     __shared__ int32_t count;  // keys in the table
@@ -1222,7 +1245,7 @@ __global__ __launch_bounds__(kContractThreads) void k_hook_contract(
         }
     };
     for (int64_t t0 = begin + (int64_t)blockIdx.x * kContractTile; t0 < end;
-         t0 += (int64_t)gridDim.x * kContractTile) {
+         t0 += (int64_t)grid * kContractTile) {
         int32_t a[kContractEPT], b[kContractEPT];
 #pragma unroll
         for (int j = 0; j < kContractEPT; ++j) {
@@ -1289,21 +1312,25 @@ __global__ __launch_bounds__(kContractThreads) void k_hook_contract(
 
 hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
                                 int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
-                                const uint32_t* gate, uint32_t limit) {
+                                const uint32_t* gate, uint32_t limit, int64_t all) {
     if (end <= begin) return hipSuccess;
     // At most two workgroups per CU, with equal shares of two tiles or more: on
     // short lists few roots are left and the workgroups' tables meet on them
     // (uniform n = 150,000, m = 300,000 after one round: 107 us on 64
     // workgroups, 128 on one per tile; n = 300,000, m = 2 M: 160 us for the
     // solve with four tiles each, 140 with two; n = 65,536, m = 524,672: 81 and 69).
-    const int64_t tiles = (end - begin + kContractTile - 1) / kContractTile;
-    const int64_t cap = 2 * (int64_t)device_cu_count();
-    const int64_t share = std::max<int64_t>(2, (tiles + cap - 1) / cap);
-    const int64_t grid64 = std::min<int64_t>(tiles, std::max<int64_t>(64, (tiles + share - 1) / share));
+    auto grid_of = [](int64_t entries) {
+        const int64_t tiles = (entries + kContractTile - 1) / kContractTile;
+        const int64_t cap = 2 * (int64_t)device_cu_count();
+        const int64_t share = std::max<int64_t>(2, (tiles + cap - 1) / cap);
+        return (int)std::min<int64_t>(tiles, std::max<int64_t>(64, (tiles + share - 1) / share));
+    };
+    const int part = grid_of(end - begin);
+    const int grid = all > end ? std::max(part, grid_of(all - begin)) : part;
     if (halve)
-        k_hook_contract<true><<<(int)grid64, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl, gate, limit);
+        k_hook_contract<true><<<grid, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl, gate, limit, all, part);
     else
-        k_hook_contract<false><<<(int)grid64, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl, gate, limit);
+        k_hook_contract<false><<<grid, kContractThreads, 0, s>>>(u, v, begin, end, pi, n, ctrl, gate, limit, all, part);
     return hipGetLastError();
 }
 

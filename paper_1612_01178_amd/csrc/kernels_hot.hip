@@ -476,6 +476,7 @@ __global__ __launch_bounds__(1024) void k_filter(const int32_t* __restrict__ eu,
                                                  const uint8_t* __restrict__ gtab, bool halve,
                                                  bool sym) {
     extern __shared__ uint32_t lds[];
+    if (ctrl->windowed) return;  // nothing is left to hook
     const bool filter = ctrl->filter_on != 0;
     const int32_t g = ctrl->giant;
     if (filter) {

@@ -505,3 +505,56 @@ def test_contracting_hook_spreads_over_the_roots(dev):
             assert np.array_equal(out.cpu().numpy(), want)
     print("contract", times, flush=True)
     assert times[0] <= 0.72 * times[1], times
+
+
+def cliques(count, size):
+    """Cliques of consecutive ids, their pairs in order."""
+    i, j = np.triu_indices(size, 1)
+    at = np.arange(count)[:, None] * size
+    return (at + i).ravel().astype(np.int32), (at + j).ravel().astype(np.int32)
+
+
+# Dense lists whose consecutive entries touch nearby ids.  Regression: the part
+# of such a list that the filtered plan starts with holds no giant, and the
+# launches after it hooked every entry (3.2 to 8.8 times as long as the hybrid
+# plan; 1.2 to 1.9 since, 2.5 is allowed).  With them, sizes of each chunk length
+# of the windows, a list that is two thirds such entries, and one without.
+@pytest.mark.parametrize("what", ["cliques 2000x60", "cliques 10x800", "band 200000", "band 524288",
+                                  "mixed", "random"])
+def test_dense_lists_with_locality(dev, what):
+    kind, _, size = what.partition(" ")
+    rng = np.random.default_rng(17)
+    if kind == "cliques":
+        count, k = map(int, size.split("x"))
+        n, (u, v) = count * k, cliques(count, k)
+    else:
+        n = int(size or 200000)
+        u, v = band(n, 9) if kind == "band" else band(n, 6)
+        if kind != "band":
+            at = rng.permutation(len(u))[: len(u) // 3] if kind == "mixed" else np.arange(len(u))
+            u[at], v[at] = rng.integers(0, n, (2, len(at)))
+    want = oracle.labels(u, v, n)
+    windows = kind in ("cliques", "band")
+    for offset in (0, 1):
+        du, dv = put(u, dev, offset), put(v, dev, offset)
+        for opt in (cc.Options(), cc.Options(path_halving="off"), cc.Options(graph=True)):
+            print("dense", what, offset, opt.path_halving, flush=True)
+            for _ in range(4):
+                out = torch.full((n + 1,), -7, dtype=torch.int32, device=dev)[1:]
+                _, st = cc.labels(du, dv, n, out=out, options=opt, return_stats=True,
+                                  stream=torch.cuda.Stream() if opt.graph else None)
+                assert np.array_equal(out.cpu().numpy(), want), opt
+            assert st["hook"] == 1 and st["filter_used"] == (0 if windows else 1)
+    if windows:
+        times = [median_us(lambda: cc.labels(du, dv, n, out=out, options=o), 15)
+                 for o in (cc.Options(), cc.Options(hook="hybrid"))]
+        print("dense times", what, times, flush=True)
+        assert times[0] <= 2.5 * times[1], times
+        listed = cc.labels_list([(du, dv, n), (du, dv, n)])
+        assert all(np.array_equal(x.cpu().numpy(), want) for x in listed)
+    for at in (0, len(u) // 2, len(u) - 1):
+        keep, v[at] = v[at], n
+        with pytest.raises(cc.CCError) as ei:
+            cc.labels(du, put(v, dev), n)
+        assert ei.value.code == cc.CC_ERR_RANGE
+        v[at] = keep
