@@ -764,12 +764,14 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     const uint32_t* far = &ctrl->win_far;
     const bool longer = p.frontier;
     // Uniform lists of fewer entries than vertices have no large component; on
-    // denser lists one round more leaves few enough roots (uniform n = 65,536,
-    // m = 1.5 M: 92 us with one, 122 with two; R-MAT 17, m = 1.8 M: 121 and 134;
-    // R-MAT 19, m = 3.5 M: 185 and 221; but uniform n = 300,000, m = 2 M: 166 and
-    // 155, n = 65,536, m = 150,000: 92 and 75).
+    // denser lists one round more leaves few enough roots (uniform, one and two
+    // rounds: n = 300,000, m = 1.95 M 131 and 147 us, n = 100,000, m = 750,000 82
+    // and 87, but n = 200,000, m = 1.1 M 119 and 112, n = 100,000, m = 300,000 82
+    // and 69; R-MAT 18, m = 1.7 M 108 and 126), and on long ones a second round's
+    // gathers cost more than it saves (n = 2^20, m = 4.4 M 357 and 393, none 404;
+    // R-MAT 20, m = 5.2 M 288 and 340).
     const int rounds = n > kHybridRoundsMaxN || 10 * m < 11 * (int64_t)n ? 0
-                       : m >= 6 * (int64_t)n                             ? 1
+                       : longer || m >= 6 * (int64_t)n                   ? 1
                                                                          : kHybridRounds;
     if (init) TIMED(kPhaseOther, launch_init(pi, n, ctrl, s));
     TIMED(kPhaseHook, launch_hook_window(u, v, m, pi, n, ctrl, far_limit, s));
