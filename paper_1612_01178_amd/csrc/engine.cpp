@@ -943,7 +943,7 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
         // one launch, which reports the status straight to pinned host memory
         // where the call waits for it
         HIPCHK(prepare_batch_lds());
-        const GraphDesc d = {u, v, out, m, n, lds_auto_segments(m, n)};
+        const GraphDesc d = {u, v, out, m, n, lds_auto_segments(m, n, true)};
         Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);
         const bool direct = pe && !p.no_sync;
         TIMED(kPhaseHook, launch_single_lds(d, direct ? &hctrl->status : &ctrl->status, p.halve, s));
@@ -1410,10 +1410,10 @@ size_t workspace_bytes_impl(int32_t n, int64_t m, const cc_options* opts) {
 
 // ---------------------------------------------------------------------- graph lists
 // Segments of an LDS-solved graph: min(cap, round(m / n)) (at least 1), or
-// round(m / n) for cap 0, the default rule for kSegAuto; small caps by
+// round(m / n) for cap 0, the default rule for kSegAuto*; small caps by
 // comparison, without a division.
 int32_t lds_segments(int64_t m, int64_t n, int32_t cap) {
-    if (cap == kSegAuto) return lds_auto_segments(m, n);
+    if (cap < 0) return lds_auto_segments(m, n, cap == kSegAutoFew);
     if (cap > 0 && cap <= 16 && m < (int64_t(1) << 61)) {
         int32_t k = cap;  // round(m / n) >= k  <=>  2m >= (2k - 1) n
         while (k > 1 && 2 * m < (2 * (int64_t)k - 1) * n) --k;
@@ -1481,7 +1481,7 @@ int32_t list_core(int32_t count, GraphAt&& graph_at, const cc_options* opts, hip
     int32_t lds_block = opts ? opts->block : 0;
     if (lds_block != 0 && (lds_block < 64 || lds_block > 1024 || lds_block % 64))
         return fail(CC_ERR_ARG, "cc_options.block must be a multiple of 64 in [64, 1024]");
-    if (seg_cap == 0 && lds_halve) seg_cap = kSegAuto;
+    if (seg_cap == 0 && lds_halve) seg_cap = count <= kFewGraphs ? kSegAutoFew : kSegAuto;
     if (st) {
         std::memset(st, 0, sizeof *st);
         st->giant_label = -1;
@@ -1746,7 +1746,7 @@ int32_t batch_lds_impl(int32_t B, const int64_t* vo, const int64_t* eo, const in
     const bool lds_halve = ph != CC_HALVE_OFF;
     int32_t seg_cap = opts ? opts->segments : 0;
     if (seg_cap < 0) return fail(CC_ERR_ARG, "cc_options.segments < 0");
-    if (seg_cap == 0 && lds_halve) seg_cap = kSegAuto;
+    if (seg_cap == 0 && lds_halve) seg_cap = B <= kFewGraphs ? kSegAutoFew : kSegAuto;
     int32_t lds_block = opts ? opts->block : 0;
     if (lds_block != 0 && (lds_block < 64 || lds_block > 1024 || lds_block % 64))
         return fail(CC_ERR_ARG, "cc_options.block must be a multiple of 64 in [64, 1024]");

@@ -241,17 +241,23 @@ bool batch_direct(int32_t count, int32_t max_n, int block, int cus);
 // Workgroup size of the LDS solver for a launch of `count` graphs of at most
 // max_n vertices.
 int batch_block(int32_t count, int32_t max_n);
-// Segment cap that stands for the default: lds_auto_segments per graph.
+// Segment caps that stand for the default: lds_auto_segments per graph, of many
+// graphs and of at most kFewGraphs.
 constexpr int32_t kSegAuto = -1;
+constexpr int32_t kSegAutoFew = -2;
+constexpr int32_t kFewGraphs = 256;
 // Segments of one LDS-solved graph.  A second one (a Multi-Jump half-way)
 // costs two barriers and a pass over the vertices and shortens the climbs of
 // the second half: it pays for large dense graphs only (alone, n = 1,000,
 // m = 65,536 30.0 against 33.5 us; n = 8,192, m = 131,072 46.0 against 54.0;
 // n = 8,192, m = 32,768 28.5 against 28.1).  Of 10,000 graphs of average
 // degree up to 16 none gets a second one (868 us; two where m / n >= 4 886,
-// two where m / n >= 1.5 925 us).
-__host__ __device__ inline int32_t lds_auto_segments(int64_t m, int64_t n) {
-    return m > 32768 && m / 8 > n ? 2 : 1;
+// two where m / n >= 1.5 925 us).  Where every graph has a CU of its own, the
+// longer climbs are not hidden by other graphs' work, and it pays from four
+// entries per vertex on (100 graphs, n = 60,000, m = 240,000 155 against 168 us;
+// n = 20,000, m = 80,000 57 against 58; but 400 of the latter 103 against 98).
+__host__ __device__ inline int32_t lds_auto_segments(int64_t m, int64_t n, bool few) {
+    return (m > 32768 && m / 8 > n) || (few && m > 65536 && m / 4 >= n) ? 2 : 1;
 }
 
 // One graph of at most 65,536 vertices solved by one workgroup in LDS

@@ -326,9 +326,9 @@ __device__ __forceinline__ int batch_size_class(uint64_t w) {
 }
 
 // min(cap, round(m / n)), at least 1 (cap 0: round(m / n) up to 2^20;
-// kSegAuto: the default rule)
+// negative: the default rule)
 __device__ __forceinline__ int32_t batch_segments(int64_t m, int64_t n, int32_t cap) {
-    if (cap == kSegAuto) return lds_auto_segments(m, n);
+    if (cap < 0) return lds_auto_segments(m, n, cap == kSegAutoFew);
     if (cap > 0 && cap <= 16 && m < (int64_t(1) << 61)) {
         int32_t k = cap;
         while (k > 1 && 2 * m < (2 * (int64_t)k - 1) * n) --k;

@@ -558,3 +558,21 @@ def test_dense_lists_with_locality(dev, what):
             cc.labels(du, put(v, dev), n)
         assert ei.value.code == cc.CC_ERR_RANGE
         v[at] = keep
+
+
+def test_few_dense_graphs_take_two_segments(dev):
+    """Regression: of a few graphs of four to eight entries per vertex each ran
+    one segment (164 us for five of 60,000 vertices, 150 with two)."""
+    n, count = 60000, 5
+    u, v = graphgen.uniform_pairs(4 * n, n, seed=9, stream=0)
+    du, dv = put(np.tile(u, count), dev), put(np.tile(v, count), dev)
+    vo, eo = np.arange(count + 1) * n, np.arange(count + 1) * len(u)
+    want = np.tile(oracle.labels(u, v, n), count)
+    out = torch.empty(count * n, dtype=torch.int32, device=dev)
+    times = {}
+    for k in (0, 2) * 3:
+        call = lambda: cc.labels_batch(du, dv, vo, eo, out=out, options=cc.Options(segments=k))  # noqa: E731
+        times[k] = min(times.get(k, 1e9), median_us(call, 15))
+        assert np.array_equal(out.cpu().numpy(), want)
+    print("segments", times, flush=True)
+    assert times[0] <= 1.05 * times[2], times
