@@ -68,7 +68,10 @@ extern "C" {
                             the Atomic-Hook with the symmetric flag.
                             The smallest lists (n <= 32,768, 2 n + m <= 131,072, none of
                             the three options set) are solved by one workgroup in LDS, in
-                            one launch, and counted as one round of the atomic-free Hook  */
+                            one launch, and counted as one round of the atomic-free Hook
+                            (no_sync: as the hybrid plan); so are the smallest CSR
+                            adjacencies without options of the segments, after the
+                            launches that expand them, counted as the hybrid plan         */
 #define CC_HOOK_ATOMIC 1 /* Atomic-Hook (Fig. 3, CAS on roots) + segmentation (Fig. 4) */
 #define CC_HOOK_PLAIN 2  /* atomic-free Hook (Fig. 2) rounds until no change (Fig. 1),
                             convergence test and active-edge frontier on the device   */

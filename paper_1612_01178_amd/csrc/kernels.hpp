@@ -260,10 +260,11 @@ __host__ __device__ inline int32_t lds_auto_segments(int64_t m, int64_t n, bool 
     return (m > 32768 && m / 8 > n) || (few && m > 65536 && m / 4 >= n) ? 2 : 1;
 }
 
-// One graph of at most 65,536 vertices solved by one workgroup in LDS
-// (prepare_batch_lds first); *status (device or pinned host) = 0 or
-// kStatusRange.
-hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hipStream_t s);
+// One graph of at most 32,768 vertices solved by one workgroup in LDS
+// (prepare_batch_lds first); *status (device or pinned host) = kStatusRange,
+// or *prior (0 when null).
+hipError_t launch_single_lds(const GraphDesc& d, const int32_t* prior, int32_t* status, bool halve,
+                             hipStream_t s);
 
 // Descriptors of a batch with device offsets, largest first (two launches,
 // one thread per graph, with a scan launch between them above 32,768

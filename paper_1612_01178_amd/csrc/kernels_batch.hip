@@ -290,19 +290,16 @@ __global__ __launch_bounds__(1024) void k_batch_lds(const GraphDesc* __restrict_
     if (bad) __hip_atomic_store(status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// One small graph, given by value, by one workgroup: the whole solve is this
-// launch.  *status receives 0 or kStatusRange (device or pinned host memory).
+// One small graph, given by value, by one workgroup.  *status (device or pinned
+// host memory) receives kStatusRange, or what *prior says.
 template <bool HALVE>
-__global__ __launch_bounds__(1024) void k_single_lds(GraphDesc d, int32_t* status) {
+__global__ __launch_bounds__(1024) void k_single_lds(GraphDesc d, const int32_t* prior, int32_t* status) {
     extern __shared__ uint16_t spi[];
     bool bad = false;
-    if ((uint32_t)d.n <= kWideMaxN)
-        solve_graph(reinterpret_cast<uint32_t*>(spi), d, HALVE, bad);
-    else
-        solve_graph(spi, d, HALVE, bad);
+    solve_graph(reinterpret_cast<uint32_t*>(spi), d, HALVE, bad);
     const int any = __syncthreads_or(bad);
     if (threadIdx.x == 0)
-        __hip_atomic_store(status, any ? kStatusRange : 0, __ATOMIC_RELAXED,
+        __hip_atomic_store(status, any ? kStatusRange : prior ? *prior : 0, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -766,12 +763,13 @@ static size_t lds_tree_bytes(int32_t n) {
     return (uint32_t)n <= kWideMaxN ? (size_t)n * 4 : (size_t)kWideMaxN * 4;
 }
 
-hipError_t launch_single_lds(const GraphDesc& d, int32_t* status, bool halve, hipStream_t s) {
-    if (d.n < 1 || d.n > 65536) return hipErrorInvalidValue;
+hipError_t launch_single_lds(const GraphDesc& d, const int32_t* prior, int32_t* status, bool halve,
+                             hipStream_t s) {
+    if (d.n < 1 || (uint32_t)d.n > kWideMaxN) return hipErrorInvalidValue;
     if (halve)
-        k_single_lds<true><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, status);
+        k_single_lds<true><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, prior, status);
     else
-        k_single_lds<false><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, status);
+        k_single_lds<false><<<1, 1024, lds_tree_bytes(d.n), s>>>(d, prior, status);
     return hipGetLastError();
 }
 

@@ -576,3 +576,63 @@ def test_few_dense_graphs_take_two_segments(dev):
         assert np.array_equal(out.cpu().numpy(), want)
     print("segments", times, flush=True)
     assert times[0] <= 1.05 * times[2], times
+
+
+# The last adjacencies solved by one workgroup in LDS and the first ones past
+# them, in a capture on a stream with the smallest scratch too
+@pytest.mark.parametrize("n,m", [(1, 0), (1, 5), (300, 130472), (32768, 65536), (32768, 65537),
+                                 (32769, 100)])
+def test_small_csr(dev, n, m):
+    u, v = graphgen.uniform_pairs(m, n, seed=n + m, stream=0)
+    want = torch.from_numpy(np.asarray(oracle.labels(u, v, n), dtype=np.int32)).to(dev)
+    rp, col = to_csr(u, v, n)
+    drp = torch.from_numpy(rp).to(dev)
+    stream = torch.cuda.Stream()
+    empty = torch.zeros(2, dtype=torch.int64, device=dev)
+    for offset in (0, 1):
+        dcol = put(col, dev, offset)
+        out = torch.full((n + 1,), -7, dtype=torch.int32, device=dev)[1:]
+        for opt in (cc.Options(), cc.Options(path_halving="off"), cc.Options(profile=True)):
+            out.fill_(-7)
+            cc.labels_csr(drp, dcol, n, out=out, options=opt)
+            assert torch.equal(out, want), opt
+        with torch.cuda.stream(stream):
+            cc.labels_csr(empty, dcol[:0], 1, options=cc.Options(no_sync=True), stream=stream)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            cc.labels_csr(drp, dcol, n, out=out, options=cc.Options(no_sync=True), stream=stream)
+        for _ in range(3):
+            out.fill_(-1)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+    if m:
+        for wrong in (np.where(np.arange(len(col)) == m // 2, n, col),
+                      np.where(np.arange(len(col)) == 0, -1, col)):
+            with pytest.raises(cc.CCError) as ei:
+                cc.labels_csr(drp, put(wrong, dev), n)
+            assert ei.value.code == cc.CC_ERR_RANGE
+        rp[n] += 1
+        for opt in (cc.Options(), cc.Options(no_sync=True)):
+            with pytest.raises(cc.CCError) as ei:
+                cc.labels_csr(torch.from_numpy(rp).to(dev), dcol, n, options=opt)
+                torch.cuda.synchronize()
+                cc.stream_status()
+            assert ei.value.code == cc.CC_ERR_RANGE
+
+
+def test_small_csr_latency(dev):
+    """Regression: the hybrid plan's chain of launches on the smallest
+    adjacencies (1.4 to 1.7 times the Atomic-Hook by segments)."""
+    for n in (30, 1000, 15000):
+        u, v = np.arange(n - 1, dtype=np.int32), np.arange(1, n, dtype=np.int32)
+        if n == 15000:
+            u[:] = 0  # a star
+        rp, col = to_csr(np.concatenate([u, v]), np.concatenate([v, u]), n)
+        drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+        times = [median_us(lambda: cc.labels_csr(drp, dcol, n, options=o), 31)
+                 for o in (cc.Options(), cc.Options(hook="atomic"))]
+        print("small csr", n, times, flush=True)
+        assert times[0] <= 1.1 * times[1], (n, times)
