@@ -190,11 +190,16 @@ void cc_options_init(cc_options* opts);
 
 /* Per-call statistics (optional output of cc_labels_ex). */
 typedef struct cc_stats {
-    int32_t hook;          /* variant that ran (CC_HOOK_ATOMIC or CC_HOOK_PLAIN)       */
-    int32_t segments;      /* Atomic-Hook: segments used                               */
+    int32_t hook;          /* variant that ran (CC_HOOK_ATOMIC, CC_HOOK_PLAIN or
+                              CC_HOOK_HYBRID)                                          */
+    int32_t segments;      /* Atomic-Hook: segments used; where atomic-free rounds find the
+                              giant (CC_HOOK_AUTO), the launches that then pass over the
+                              list (CSR: 1); 0 for the other variants                   */
     int32_t filter_used;   /* 1 if the giant-component filter was active              */
-    int32_t rounds;        /* atomic-free Hook: Hook rounds run until no change        */
-    int64_t active_edges;  /* atomic-free Hook: edges still active after round 1       */
+    int32_t rounds;        /* atomic-free Hook: Hook rounds run until no change (1 for a
+                              list solved in LDS); 0 for the other variants            */
+    int64_t active_edges;  /* atomic-free Hook: edges still active after round 1 (0 for a
+                              list solved in LDS); 0 for the other variants            */
     int32_t giant_label;   /* filter: label of the sampled giant component (or -1)     */
     int32_t host_syncs;    /* host synchronisations made inside the call               */
     int32_t hook_launches; /* edge-pass kernels launched (Atomic-Hook / Hook / compaction) */

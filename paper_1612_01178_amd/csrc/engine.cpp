@@ -66,7 +66,6 @@ int64_t segment_start(int64_t m, int64_t i, int64_t S) {
     return (int64_t)(((__int128)m * i) / S) & ~int64_t(3);
 }
 
-
 // The automatic filtered plan starts with kPrefixRounds atomic-free rounds
 // over the first n entries and a contracting hook of the same entries up to
 // kPrefixMaxN vertices, and with an Atomic-Hook of the first n / 16 entries
@@ -94,6 +93,12 @@ constexpr int32_t kPrefixMaxN = 1 << 19;
 constexpr int kPrefixRounds = 3;
 constexpr int64_t kPrefixStart = 2;
 constexpr int64_t kPrefixGrowth = 8;
+
+// End of the launch of that rest which starts at `from`.
+int64_t prefix_end(int64_t from, int64_t take, int64_t m) {
+    const int64_t to = std::min<int64_t>(m, (from + take) & ~int64_t(3));
+    return m - to < take / 2 ? m : to;
+}
 
 // Hybrid plan (see enqueue_hybrid).
 constexpr int kHybridRounds = 2;
@@ -694,8 +699,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
         while (from < m) {
             int64_t to;
             if (p.prefix) {
-                to = std::min<int64_t>(m, (from + take) & ~int64_t(3));
-                if (m - to < take / 2) to = m;
+                to = prefix_end(from, take, m);
                 take *= kPrefixGrowth;
             } else {
                 g = std::min<int64_t>(S, g + step);
@@ -1010,11 +1014,19 @@ int32_t run_solve(int32_t n, const int32_t* u, const int32_t* v, int64_t m, int3
     return rc;
 }
 
-void init_stats(cc_stats* st, const Plan& p) {
+void init_stats(cc_stats* st, const Plan& p, int32_t n, int64_t m) {
     if (!st) return;
     std::memset(st, 0, sizeof *st);
     st->hook = p.hook;
     st->segments = p.hook == CC_HOOK_ATOMIC ? p.segments : 0;
+    if (p.prefix) {  // the launches that the rest of the list is taken in
+        st->segments = 0;
+        for (int64_t from = std::min<int64_t>(m, n) & ~int64_t(3), take = kPrefixStart * (int64_t)n; from < m;
+             take *= kPrefixGrowth) {
+            from = prefix_end(from, take, m);
+            ++st->segments;
+        }
+    }
     st->giant_label = -1;
 }
 
@@ -1028,7 +1040,7 @@ int32_t labels_impl(int32_t n, const int32_t* u, const int32_t* v, int64_t m, in
     Plan p;
     rc = make_plan(n, m, opts, p);
     if (rc != CC_OK) return rc;
-    init_stats(st, p);
+    init_stats(st, p, n, m);
     if (n == 0) {
         if (m > 0) return fail(CC_ERR_RANGE, "edge endpoint outside [0, n) (n == 0)");
         return CC_OK;
@@ -1099,7 +1111,7 @@ int32_t labels_noalloc_impl(int32_t n, const int32_t* u, const int32_t* v, int64
                                       " bytes of workspace; the fixed buffer holds " +
                                       std::to_string((size_t)CC_NOALLOC_SCRATCH_BYTES) +
                                       " (use cc_labels_ex, or the automatic hook)");
-    init_stats(st, p);
+    init_stats(st, p, n, m);
     if (n == 0) {
         if (m > 0) return fail(CC_ERR_RANGE, "edge endpoint outside [0, n) (n == 0)");
         return CC_OK;
@@ -1307,7 +1319,7 @@ int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t 
     if (rc != CC_OK) return rc;
     if (st) {
         st->hook = p.hook;
-        st->segments = p.hook == CC_HOOK_ATOMIC ? p.segments : 0;
+        st->segments = p.hook != CC_HOOK_ATOMIC ? 0 : p.auto_filter ? 1 : p.segments;
     }
     char* ws = static_cast<char*>(pe->dev);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws);

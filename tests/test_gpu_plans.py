@@ -636,3 +636,44 @@ def test_small_csr_latency(dev):
                  for o in (cc.Options(), cc.Options(hook="atomic"))]
         print("small csr", n, times, flush=True)
         assert times[0] <= 1.1 * times[1], (n, times)
+
+
+# Each side of the limits of the automatic choice: the plan that runs, its
+# edge passes and the segments it reports.
+def test_automatic_plans(dev):
+    def pairs(n, m):
+        return graphgen.uniform_pairs(m, n, seed=n % 97, stream=0)
+
+    def stats(n, m, csr, **opt):
+        u, v = pairs(n, m)
+        want = oracle.labels(u, v, n)
+        if csr:
+            rp, col = to_csr(u, v, n)
+            lab, st = cc.labels_csr(torch.from_numpy(rp).to(dev), put(col, dev), n,
+                                    options=cc.Options(**opt), return_stats=True)
+        else:
+            lab, st = cc.labels(put(u, dev), put(v, dev), n, options=cc.Options(**opt), return_stats=True)
+        assert np.array_equal(lab.cpu().numpy(), want), (n, m, csr)
+        print("automatic plan", n, m, csr, opt, st["hook"], st["segments"], st["filter_used"],
+              st["hook_launches"], flush=True)
+        return st["hook"], st["segments"], st["filter_used"], st["hook_launches"]
+
+    # (hook, segments, filter used, edge passes); 1 Atomic-Hook, 2 atomic-free, 3 hybrid
+    assert stats(32768, 65536, False) == (2, 0, 0, 1)       # one workgroup in LDS
+    assert stats(32768, 65537, False) == (3, 0, 0, 4)       # window round, two more, contraction
+    assert stats(32769, 20000, False) == (3, 0, 0, 2)       # no further round
+    assert stats(100000, 600000, False) == (3, 0, 0, 3)     # one further round
+    assert stats(1 << 18, (1 << 21) - 1, False)[0] == 3
+    # four rounds over the first n entries, then up to 3 n and the rest
+    assert stats(1 << 18, 1 << 21, False) == (1, 2, 1, 6)
+    assert stats(1 << 19, 1 << 22, False) == (1, 2, 1, 6)
+    assert stats(5000, 1 << 21, False) == (1, 4, 1, 8)
+    # above 2^19 vertices segments of n / 16 entries: 1, 2, 8, 32, 128 and 85 of them
+    assert stats((1 << 19) + 1, 1 << 23, False) == (1, 256, 1, 6)
+    assert stats(1 << 20, (1 << 22) - 1, False)[3] == 4
+    assert stats(1 << 20, 1 << 22, False)[3] == 5            # and the pairs of long lists
+    assert stats(32768, 65536, True) == (3, 0, 0, 1)
+    assert stats(32768, 65537, True) == (3, 0, 0, 4)
+    assert stats(1 << 17, (1 << 20) - 1, True)[0] == 3
+    assert stats(1 << 17, 1 << 20, True) == (1, 1, 1, 3)
+    assert stats(1 << 17, 1 << 20, True, segments=8)[:2] == (1, 8)
