@@ -677,3 +677,90 @@ def test_automatic_plans(dev):
     assert stats(1 << 17, (1 << 20) - 1, True)[0] == 3
     assert stats(1 << 17, 1 << 20, True) == (1, 1, 1, 3)
     assert stats(1 << 17, 1 << 20, True, segments=8)[:2] == (1, 8)
+
+
+# Rows of up to several thousand entries that are not inside a giant: on both
+# sides of the longest row that one lane marks (32), of a wave, of a tile of
+# 1,024 entries; the filter off (64 equal components) and on (a giant beside
+# them, in rows of its own and mixed with theirs).
+@pytest.mark.parametrize("what", ["equal", "beside", "mixed"])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_csr_long_rows(dev, what, offset):
+    rng = np.random.default_rng(41)
+    if what == "equal":
+        n = 64 * 256
+        rows = np.repeat(np.arange(n, dtype=np.int64), rng.integers(30, 60, n))
+        u, v = rows, rows // 256 * 256 + rng.integers(0, 256, len(rows))
+    else:
+        size = 60000
+        degrees = [31, 32, 33, 34, 63, 64, 65, 256, 1000, 1023, 1024, 1025, 3000, 5000]
+        u, v = [rng.integers(0, size, 10 * size)], [rng.integers(0, size, 10 * size)]
+        n = size
+        for d in degrees:  # a star whose hub repeats its leaves, beside a component of such rows
+            u += [np.full(d, n), np.repeat(n + 50 + np.arange(20), d // 2)]
+            v += [n + 1 + np.arange(d) % 49, n + 50 + rng.integers(0, 20, 20 * (d // 2))]
+            n += 70
+        u, v = np.concatenate(u), np.concatenate(v)
+        if what == "mixed":
+            relabel = rng.permutation(n)
+            u, v = relabel[u], relabel[v]
+    u, v = np.concatenate([u, v]).astype(np.int32), np.concatenate([v, u]).astype(np.int32)
+    assert len(u) >= 1 << 20 and len(u) >= 8 * n
+    want = oracle.labels(u, v, n)
+    rp, col = to_csr(u, v, n)
+    drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev, offset)
+    for opt in (cc.Options(), cc.Options(symmetric=True), cc.Options(path_halving="off")):
+        for _ in range(3):
+            lab, st = cc.labels_csr(drp, dcol, n, options=opt, return_stats=True)
+            assert np.array_equal(lab.cpu().numpy(), want), (what, opt)
+        assert (st["hook"], st["segments"], st["filter_used"]) == (1, 1, int(what != "equal"))
+
+
+# `out` one word past a 16-byte boundary, its neighbours untouched, on every
+# automatic plan: further rounds, the pairs of long lists, both filtered plans
+# of pair lists (bitmap in LDS, half of it, vertex table), both of CSR.
+@pytest.mark.parametrize("n,m", [(100003, 300001), (1 << 20, (1 << 22) + 1), (1 << 18, (1 << 21) + 3),
+                                 ((1 << 19) + 5, (1 << 22) + 77), (1400003, 11300001),
+                                 (2700001, 21700001)])
+@pytest.mark.parametrize("local", [False, True])
+def test_unaligned_labels(dev, n, m, local):
+    u, v = graphgen.uniform_pairs(m, n, seed=m % 89, stream=0)
+    if local:  # consecutive entries touch nearby ids
+        u = (np.arange(m, dtype=np.int64) * n // m).astype(np.int32)
+        v = np.minimum(u + v % 5, n - 1).astype(np.int32)
+    want = torch.from_numpy(np.asarray(oracle.labels(u, v, n), dtype=np.int32)).to(dev)
+    du, dv = put(u, dev), put(v, dev)
+    buf = torch.empty(n + 2, dtype=torch.int32, device=dev)
+    for opt in (cc.Options(), cc.Options(hook="hybrid")):
+        buf.fill_(-7)
+        cc.labels(du, dv, n, out=buf[1:-1], options=opt)
+        assert torch.equal(buf[1:-1], want) and buf[0] == -7 and buf[-1] == -7, opt
+    if m < 1 << 22:
+        rp, col = to_csr(u, v, n)
+        drp, dcol = torch.from_numpy(rp).to(dev), put(col, dev)
+        buf.fill_(-7)
+        cc.labels_csr(drp, dcol, n, out=buf[1:-1])
+        assert torch.equal(buf[1:-1], want) and buf[0] == -7 and buf[-1] == -7
+
+
+# Long lists with locality: the compaction and the pairs, chosen and asked for
+@pytest.mark.parametrize("what", ["grid", "band", "shuffled"])
+def test_long_lists_with_locality(dev, what):
+    if what == "grid":
+        u, v, n = graphgen.grid(2000, 1990)
+    else:
+        n = 1 << 21
+        u = np.repeat(np.arange(n, dtype=np.int32), 3)
+        v = np.minimum(u + np.random.default_rng(3).integers(1, 9, len(u)), n - 1).astype(np.int32)
+        if what == "shuffled":  # its entries in another order: the contracting hook
+            order = np.random.default_rng(4).permutation(len(u))
+            u, v = u[order], v[order]
+    assert len(u) >= 1 << 22
+    want = oracle.labels(u, v, n)
+    for offset in (0, 1):
+        du, dv = put(u, dev, offset), put(v, dev, offset)
+        for opt in (cc.Options(), cc.Options(hook="hybrid"), cc.Options(hook="hybrid", path_halving="off")):
+            for _ in range(3):
+                lab, st = cc.labels(du, dv, n, options=opt, return_stats=True)
+                assert np.array_equal(lab.cpu().numpy(), want), opt
+            assert (st["hook"], st["hook_launches"]) == (3, 4), opt
