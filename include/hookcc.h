@@ -96,8 +96,9 @@ typedef struct cc_options {
                                  max(1, round(m / n)) (16x that when CC_HOOK_AUTO picks the
                                  filtered Atomic-Hook, so the first segment is ~n/16
                                  entries; up to 2^19 vertices atomic-free rounds over the
-                                 first n entries take its place); clamped to
-                                 [1, ceil(m / 4)]                                       */
+                                 first n entries take its place, or one over the whole
+                                 list where consecutive entries touch nearby ids); clamped
+                                 to [1, ceil(m / 4)]                                    */
     int32_t filter;           /* CC_FILTER_* (Atomic-Hook only); default CC_FILTER_AUTO  */
     int32_t filter_after;     /* segments hooked before the giant-component sample
                                  (0 = default 1)                                        */
@@ -132,8 +133,9 @@ typedef struct cc_options {
                                  while they are in the giant component); CC_HOT_LARGE:
                                  32,768 bitmap-word slots (160 KiB); CC_HOT_ON: 16,384
                                  word slots; CC_HOT_OFF: none.  CC_HOT_AUTO (default):
-                                 the whole bitmap in LDS for n <= 1,310,720, then
-                                 CC_HOT_VERTEX for n <= 255 * 81920, else CC_HOT_LARGE  */
+                                 the whole bitmap in LDS for n <= 1,310,720, its first
+                                 160 KiB for n <= 2,621,440, then CC_HOT_VERTEX for
+                                 n <= 255 * 81920, else CC_HOT_LARGE                    */
     int32_t path_halving;     /* Atomic-Hook climb: CC_HALVE_AUTO (default, on), CC_HALVE_ON
                                  or CC_HALVE_OFF (Fig. 3 exactly) -- re-point a non-root
                                  passed on the way up at its grandparent, on every 4th
@@ -144,7 +146,8 @@ typedef struct cc_options {
                                  then skips the entries with u > v, which changes nothing in
                                  the result for such lists and halves the tree accesses.
                                  Wrong labels if the guarantee does not hold.  Never on by
-                                 default; with CC_HOOK_AUTO it forces the Atomic-Hook.    */
+                                 default; with CC_HOOK_AUTO it forces the Atomic-Hook for
+                                 pair lists.                                             */
     int32_t graph;            /* 1 = capture the call's launch sequence in a hipGraph on the
                                  call's stream the first time and replay it on later
                                  calls with the same arrays, sizes and plan (Atomic-Hook
@@ -154,8 +157,9 @@ typedef struct cc_options {
                                  null stream, else ignored; profile = 1 disables it)   */
     int32_t no_sync;          /* cc_labels_ex and cc_labels_csr only: 1 = enqueue the whole
                                  solve on the call's stream and return without waiting
-                                 (Atomic-Hook only: CC_HOOK_AUTO then picks it, and
-                                 CC_HOOK_PLAIN or profile = 1 is CC_ERR_ARG).  Argument
+                                 (CC_HOOK_AUTO picks the Atomic-Hook, the hybrid plan or
+                                 the LDS solve; CC_HOOK_PLAIN or profile = 1 is
+                                 CC_ERR_ARG).  Argument
                                  errors still return at once; the device-detected status
                                  (CC_ERR_RANGE) is read with cc_stream_status.  The
                                  caller keeps every array alive and unchanged until the

@@ -17,8 +17,9 @@ struct Ctrl {
     int32_t filter_on;    // 1 when the giant-component bitmap is valid and worth using
     int32_t rounds;       // atomic-free Hook: rounds that found an active edge
     uint32_t count[2];    // atomic-free Hook: frontier sizes, ping-pong by round parity
-    uint32_t windowed;    // that plan: 1 = it has, and window round and contracting hook solve it
-    uint32_t scattered;   // filtered plan with prefix rounds: 1 = the list has no locality
+    // filtered plan with prefix rounds (written by the init kernel):
+    uint32_t windowed;    // 1 = the list has locality: a window round and a contracting hook solve it
+    uint32_t scattered;   // 1 = it has none
     int64_t active_round1;  // atomic-free Hook: frontier size after round 1
     int32_t hook_changed;   // host-loop form of Fig. 1: a Hook pass found an active edge
     int32_t jump_changed;   // host-loop form of Fig. 1: a Jump pass moved a pointer
@@ -46,6 +47,12 @@ struct GraphDesc {
     int32_t segments;
 };
 static_assert(sizeof(GraphDesc) == 40, "descriptor layout");
+
+// Number of set bits of `mask` in lanes below this one (wave64 lane prefix).
+__device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
 
 // Accesses of the tree array pi.
 //

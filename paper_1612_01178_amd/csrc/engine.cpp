@@ -81,8 +81,8 @@ int64_t segment_start(int64_t m, int64_t i, int64_t S) {
 // entry is bound by the compare-and-swaps on few roots (2,000 cliques of 60: 238
 // us; band of 2^18 vertices, m = 4.2 M: 447).  The first round then is a window
 // round over the whole list, the contracting hook takes the whole list too, and
-// the launches after it find nothing to do (115 and 100 us; R-MAT 18 pays 2 us
-// for the look).
+// the launches after it find nothing to do (115 and 100 us; R-MAT 18 pays 3 to 5
+// us for the look and the gates).
 //
 // The Atomic-Hook of the first n / 16 entries runs two entries per thread up
 // to kShortMaxN vertices, 8 per thread above, where more climbs at once
@@ -752,7 +752,7 @@ int32_t enqueue_atomic(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
 // device by win_far, which exceeds far_limit when more than a quarter of the
 // entries (or a whole chunk) were hooked outside the windows.
 //
-// Short lists: Multi-Jump, and where there is no locality kHybridRounds more
+// Short lists: Multi-Jump, and where there is no locality up to kHybridRounds more
 // atomic-free rounds (each round leaves about a sixteenth of the roots, so
 // that the last pass joins few; up to kHybridRoundsMaxN vertices, above which
 // a round's gathers cost more than the compare-and-swaps it saves), then the
@@ -1248,9 +1248,10 @@ int32_t stream_impl(int32_t n, const int32_t* hu, const int32_t* hv, int64_t m, 
 // against 466 for growing segments of rows, whose first ones contend for the
 // hubs; a split pass with a bitmap refresh in between 193.
 //
-// With options of its own (segments, filter_after, ...) the Atomic-Hook runs
-// segments of the col[] array, each followed by a Multi-Jump; with the giant
-// filter the growing super-segments of enqueue_atomic.
+// The smallest lists are solved by one workgroup in LDS.  With options of its own
+// (segments, filter_after, filter) the Atomic-Hook runs segments of the col[]
+// array, each followed by a Multi-Jump; with the giant filter the growing
+// super-segments of enqueue_atomic.
 int32_t csr_impl(int32_t n, const int64_t* row_ptr, const int32_t* col, int64_t m, int32_t* out,
                  const cc_options* opts, hipStream_t s, cc_stats* st) {
     if (n < 0 || m < 0) return fail(CC_ERR_ARG, "n < 0 or m < 0");

@@ -19,7 +19,7 @@ hipError_t launch_ahook(const int32_t* u, const int32_t* v, int64_t begin, int64
                         int32_t* pi, int32_t n, Ctrl* ctrl, const uint32_t* bits, int block,
                         int ept, bool coherent, bool halve, bool sym, hipStream_t s);
 
-// Atomic-Hook of entries [begin, end), one entry per thread, no filter (short
+// Atomic-Hook of entries [begin, end), two entries per thread, no filter (short
 // segments).
 hipError_t launch_ahook_short(const int32_t* u, const int32_t* v, int64_t begin, int64_t end,
                               int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, bool sym,
@@ -74,9 +74,6 @@ hipError_t launch_hook_plain(int round, const int32_t* u, const int32_t* v, int6
                              const int2* f0, const int2* f1, int32_t* pi, int32_t n, Ctrl* ctrl,
                              int block, int ept, int grid_cap, hipStream_t s);
 
-// Frontier compaction after the Compress of round `round`: keeps the entries
-// whose endpoints still have different roots, written as root pairs to
-// `dst` (capacity cap), size accumulated in ctrl->count[round & 1].
 // Window round of the hybrid plan: an atomic-free Hook round over all m
 // entries in which each workgroup first joins its chunk of entries inside an
 // LDS window of consecutive vertices (see kernels_batch.hip).  Range-checks
@@ -98,6 +95,9 @@ hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begi
                                 int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
                                 const uint32_t* gate = nullptr, uint32_t limit = 0, int64_t all = 0);
 
+// Frontier compaction after the Compress of round `round`: keeps the entries
+// whose endpoints still have different roots, written as root pairs to f0 or
+// f1 (capacity cap), size accumulated in ctrl->count[round & 1].
 // tau: frontier rewrite threshold in thousandths (0xffffffff = every round).
 // Does nothing when `skip` is non-null and *skip > limit.
 hipError_t launch_compact(int round, const int32_t* u, const int32_t* v, int64_t m, int2* f0,

@@ -22,12 +22,6 @@ typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 // ----------------------------------------------------------------------------- helpers
-// Number of set bits of `mask` in lanes below this one (wave64 lane prefix).
-__device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 // Loads EPT entries of one edge array for this thread: EPT/4 groups of 4
 // consecutive entries, group k at e0 + k * stride.  Slots outside [.., end)
 // read as vertex 0 and are reported in `valid`.
@@ -1314,7 +1308,8 @@ hipError_t launch_hook_contract(const int32_t* u, const int32_t* v, int64_t begi
                                 int32_t* pi, int32_t n, Ctrl* ctrl, bool halve, hipStream_t s,
                                 const uint32_t* gate, uint32_t limit, int64_t all) {
     if (end <= begin) return hipSuccess;
-    // At most two workgroups per CU, with equal shares of two tiles or more: on
+    // At most two workgroups per CU, with equal shares of two tiles or more
+    // (64 workgroups on lists of 64 to 127 tiles, one tile each on shorter ones): on
     // short lists few roots are left and the workgroups' tables meet on them
     // (uniform n = 150,000, m = 300,000 after one round: 107 us on 64
     // workgroups, 128 on one per tile; n = 300,000, m = 2 M: 160 us for the

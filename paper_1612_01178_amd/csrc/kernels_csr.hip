@@ -3,7 +3,8 @@
 // (Fig. 4), so the solve is the same as for pair lists; only the way an
 // entry's first endpoint is found differs.  The automatic plans use the
 // kernels by tiles further down; k_ahook_csr serves calls that set segments or
-// the filter's options themselves.
+// the filter's options themselves, or that ask for the Atomic-Hook, and those for
+// which the other plans' scratch cannot be had.
 //
 // k_ahook_csr finds rows on the fly.  Each workgroup takes a tile of
 // consecutive entries and finds the rows spanning it (row_ptr is int64 and

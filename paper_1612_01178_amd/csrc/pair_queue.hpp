@@ -5,12 +5,6 @@
 
 namespace hookcc {
 
-// Number of set bits of `mask` in lanes below this one.
-__device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 // A wave's pending entries, one per lane in lanes 0 .. count - 1.  The
 // entries a filtered launch keeps are a few per wave and step, and hooking
 // them where they are found costs the whole wave their chain of dependent
