@@ -489,9 +489,14 @@ __global__ __launch_bounds__(1024, 8) void k_mj_local(int32_t* pi, int32_t n) {
 // one slot with workgroup scope (see settling in common.hpp).  Such passes leave
 // the chains that climbs shorten (kDeepSteps); the other form, after the
 // Atomic-Hook's path halving, does so on every fourth such step only (4096^2
-// grid: 26 us, 30 with each of them; path of 2^24 vertices 48 -> 1.3 ms).
+// grid: 26 us, 30 with each of them; path of 2^24 vertices 48 -> 1.3 ms).  Above
+// kDeepMaxN vertices the first three such steps of a climb are passed over: a
+// tree array of more than the L2s' 32 MB makes them dearer (solves by Fig. 1's
+// host loop, 4096^2 grid 1.41 and 1.29 ms, 3000^2 848 and 852 us; path of 2^22
+// vertices in falling order 308 and 330).
+constexpr int32_t kDeepMaxN = 1 << 23;
 template <int V, bool SETTLE>
-__global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint32_t* gate,
+__global__ __launch_bounds__(512) void k_mj1(int32_t* pi, int32_t n, const uint32_t* gate,
                                              uint32_t limit, Post post) {
     post_ctrl(post);
     if (gate != nullptr && *gate <= limit) return;
@@ -520,7 +525,7 @@ __global__ __launch_bounds__(256) void k_mj1(int32_t* pi, int32_t n, const uint3
         int steps = 0;
         while (more) {
             more = false;
-            if (++steps % (SETTLE ? kDeepSteps : 4 * kDeepSteps) == 0) {
+            if (++steps % (SETTLE ? kDeepSteps : 4 * kDeepSteps) == 0 && (!SETTLE || n <= kDeepMaxN || steps >= 4 * kDeepSteps)) {
 #pragma unroll
                 for (int k = 0; k < V; ++k)  // a climb under way: its vertex is below n
                     if (g[k] != r[k]) st_tree<true>(pi + v + (int64_t)k * blockDim.x, g[k]);
@@ -554,18 +559,19 @@ static hipError_t mj1_launch(int32_t* pi, int32_t n, const uint32_t* gate, uint3
                              bool settle, hipStream_t s, Post post = {}) {
     const int64_t cus = device_cu_count();
     const int V = (int64_t)n >= 256 * 4 * 8 * cus ? 4 : 2;
-    int64_t grid = ((int64_t)n + 256 * V - 1) / (256 * V);
     // A gated launch may find nothing to do: a large grid then costs more than
-    // it has to.  Above 32 workgroups per CU the 8 that are resident stride over
-    // the vertices, all of them through the same range of ids at a time: with
-    // workgroups that start only when others have passed over all ranges, the
-    // ranges they skip stay chains (path of 2^24 vertices, entries shuffled: 8.4 s
-    // at 32 per CU, 26 ms).
-    if (gate && grid > cus * 32) grid = cus * 8;
-    if (V == 4 && settle) k_mj1<4, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
-    else if (V == 4) k_mj1<4, false><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
-    else if (settle) k_mj1<2, true><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
-    else k_mj1<2, false><<<(int)grid, 256, 0, s>>>(pi, n, gate, limit, post);
+    // it has to, so that above 32 workgroups per CU they are of 512 threads
+    // (4096^2 grid: 331 us, 334 with 256 threads, 329 with 8 workgroups per CU
+    // striding over the vertices).  The workgroups start in the order of their
+    // ids and none takes ids from several places: what those that are not
+    // resident yet would have shortened stays a chain (path of 2^24 vertices,
+    // entries shuffled: 1.6 ms, 27 with 8 per CU, 8.4 s with 32).
+    const int threads = gate && n > 32 * cus * 256 * V ? 512 : 256;
+    const int64_t grid = ((int64_t)n + threads * V - 1) / (threads * V);
+    if (V == 4 && settle) k_mj1<4, true><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
+    else if (V == 4) k_mj1<4, false><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
+    else if (settle) k_mj1<2, true><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
+    else k_mj1<2, false><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
     return hipGetLastError();
 }
 
