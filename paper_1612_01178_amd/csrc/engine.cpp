@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -788,8 +789,10 @@ int32_t enqueue_hybrid(int32_t n, const int32_t* u, const int32_t* v, int64_t m,
     }
     if (longer) {
         int2* F = reinterpret_cast<int2*>(ws + L.f0);
+        // one workgroup per tile: 2,048 of them striding over 4096^2's 5,733 end
+        // unevenly (56.0 us, 54.5 now)
         TIMED(kPhaseHook, launch_compact(1, u, v, m, F, F, L.cap, pi, n, ctrl, 0xffffffffu, p.block,
-                                         p.ept, grid_cap, s, far, far_limit));
+                                         p.ept, INT_MAX, s, far, far_limit));
         TIMED(kPhaseHook, launch_ahook_pairs(F, &ctrl->count[1], L.cap, pi, p.halve, grid_cap, s));
     }
     TIMED(kPhaseHook, launch_hook_contract(u, v, 0, m, pi, n, ctrl, p.halve, s,

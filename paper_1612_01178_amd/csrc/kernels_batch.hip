@@ -606,9 +606,11 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
     g_cint* gv = (g_cint*)ev;
     int32_t a[kWinEPT], b[kWinEPT], na[kWinEPT], nb[kWinEPT];
     // the window starts at the smallest endpoint among the first blockDim.x
-    // entries
+    // entries; the LDS is set while they are loaded
     const int64_t first_end = c0 + (c1 - c0) / segments;
     edge_step_loads<kWinEPT>(gu, gv, c0, first_end, step, a, b);
+    uint32_t* w32 = reinterpret_cast<uint32_t*>(spi);
+    for (uint32_t w = tid; w < slots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
     const bool first = c0 + tid < first_end && max((uint32_t)a[0], (uint32_t)b[0]) < (uint32_t)n;
     int32_t lo = first ? min(a[0], b[0]) : INT32_MAX;
 #pragma unroll
@@ -638,9 +640,6 @@ __global__ __launch_bounds__(1024) void k_hook_window(const int32_t* __restrict_
         if (bad) atomicOr(&ctrl->status, kStatusRange);
         return;
     }
-    uint32_t* w32 = reinterpret_cast<uint32_t*>(spi);
-    for (uint32_t w = tid; w < slots / 2; w += nthr) w32[w] = ((2 * w + 1) << 16) | (2 * w);
-    __syncthreads();
     uint32_t far = 0;  // entries hooked outside the window
     // The chunk in `segments` segments, each followed by a Multi-Jump over
     // the window (the schedule of Fig. 4 inside the chunk) so that later
