@@ -559,14 +559,16 @@ static hipError_t mj1_launch(int32_t* pi, int32_t n, const uint32_t* gate, uint3
                              bool settle, hipStream_t s, Post post = {}) {
     const int64_t cus = device_cu_count();
     const int V = (int64_t)n >= 256 * 4 * 8 * cus ? 4 : 2;
-    // A gated launch may find nothing to do: a large grid then costs more than
-    // it has to, so that above 32 workgroups per CU they are of 512 threads
-    // (4096^2 grid: 331 us, 334 with 256 threads, 329 with 8 workgroups per CU
-    // striding over the vertices).  The workgroups start in the order of their
-    // ids and none takes ids from several places: what those that are not
-    // resident yet would have shortened stays a chain (path of 2^24 vertices,
-    // entries shuffled: 1.6 ms, 27 with 8 per CU, 8.4 s with 32).
-    const int threads = gate && n > 32 * cus * 256 * V ? 512 : 256;
+    // The hybrid plan's gate (the one with a limit) skips the launch on lists with
+    // locality: a large grid then costs more than it has to, so that above 32
+    // workgroups per CU they are of 512 threads (4096^2 grid: 331 us, 334 with 256
+    // threads, 329 with 8 workgroups per CU striding over the vertices; rounds
+    // alone, whose launches mostly run: 1,031, 1,007 and 1,042).  The workgroups
+    // start in the order of their ids and none takes ids from several places:
+    // what those that are not resident yet would have shortened stays a chain
+    // (path of 2^24 vertices, entries shuffled: 1.6 ms, 27 with 8 per CU, 8.4 s
+    // with 32).
+    const int threads = limit > 0 && n > 32 * cus * 256 * V ? 512 : 256;
     const int64_t grid = ((int64_t)n + threads * V - 1) / (threads * V);
     if (V == 4 && settle) k_mj1<4, true><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
     else if (V == 4) k_mj1<4, false><<<(int)grid, threads, 0, s>>>(pi, n, gate, limit, post);
